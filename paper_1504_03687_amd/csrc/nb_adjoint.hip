@@ -72,19 +72,19 @@ __device__ __forceinline__ void load_jb(JB &J, const AdjointArgs &a, int64_t j, 
 }
 
 // Exclusion (self pair or neighbour) by the canonical test, run only for
-// candidates below the FP64 bound hi.
-__device__ __forceinline__ bool excluded(double dx, double dy, double dz, double r2, double hi,
-                                         float rs2f, int32_t jidx, int32_t i)
+// candidates below the FP64 bound hi: an excluded pair gets the squared
+// distance kExclR2, which makes every power of r^-1 from the third up exactly
+// zero, so the pair loop holds no select.
+__device__ __forceinline__ void exclude(double dx, double dy, double dz, double &r2, double hi,
+                                        float rs2f, int32_t jidx, int32_t i)
 {
-    bool excl = false;
     if (r2 < hi) {
         double ex = dx, ey = dy, ez = dz;
         int32_t jj = jidx;
         opaque(ex, ey, ez);
         opaque(jj);
-        excl = jj == i || canon_r2f(ex, ey, ez) < rs2f;
+        if (jj == i || canon_r2f(ex, ey, ez) < rs2f) r2 = kExclR2;
     }
-    return excl;
 }
 
 // ---------------------------------------------------------------------------
@@ -148,11 +148,10 @@ __global__ __launch_bounds__(kBlock) void adj_rows_kernel(AdjointArgs a, AdjPlan
         for (int jj = 0; jj < kTile; ++jj) {
             const JB &J = buf[jj];
             const double dx = J.x - xi, dy = J.y - yi, dz = J.z - zi;
-            const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-            const bool excl = excluded(dx, dy, dz, r2, hi, rs2f, (int32_t)(tbase + jj), i);
+            double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+            exclude(dx, dy, dz, r2, hi, rs2f, (int32_t)(tbase + jj), i);
             const double ux = J.vx - vxi, uy = J.vy - vyi, uz = J.vz - vzi;
-            double y = rsqrt_f64(r2);
-            y = excl ? 0.0 : y;
+            const double y = rsqrt_f64(r2);
             const double y2 = y * y;
             const double R3 = y * y2, R5 = R3 * y2;
             const double s = __builtin_fma(dz, uz, __builtin_fma(dy, uy, dx * ux));
@@ -277,11 +276,10 @@ __global__ __launch_bounds__(kBlock) void adj_bodies_kernel(AdjointArgs a, AdjPl
         for (int q = 0; q < kRowTile; ++q) {
             const RB &R = buf[q];
             const double dx = xj - R.x, dy = yj - R.y, dz = zj - R.z;
-            const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-            const bool excl = excluded(dx, dy, dz, r2, R.hi, R.rs2f, jidx, R.i);
+            double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+            exclude(dx, dy, dz, r2, R.hi, R.rs2f, jidx, R.i);
             const double ux = vxj - R.vx, uy = vyj - R.vy, uz = vzj - R.vz;
-            double y = rsqrt_f64(r2);
-            y = excl ? 0.0 : y;
+            const double y = rsqrt_f64(r2);
             const double y2 = y * y;
             const double R3 = y * y2, R5 = R3 * y2;
             const double s = __builtin_fma(dz, uz, __builtin_fma(dy, uy, dx * ux));

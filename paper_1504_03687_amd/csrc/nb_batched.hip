@@ -53,6 +53,57 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(IR == 1 && T
     }
 }
 
+// The scalar-operand pass (rows_pass_packed) over the packed ensemble: an item
+// is one wave's kWave rows over one j-range, and every wave pulls its own, so
+// no wave waits for another of its work-group and a cluster's last row tile
+// leaves at most kWave - 1 lanes idle.  Bound by VALU issue, as the
+// single-block kernel: 96 clusters of 1024 to 32768 bodies (5.8e9 pairs,
+// mixed) took 6113 us a call through LDS and take 5825.
+template <bool MIXED>
+__global__ __launch_bounds__(kBlock) void batched_packed_kernel(BatchArgs A)
+{
+    for (;;) {
+        // The whole wave comes back here together before lane 0 pulls.  The
+        // barrier emits nothing, but code around it is not duplicated per
+        // lane, and the opaque lane number keeps the compiler from joining
+        // this branch with an earlier one on the same condition: without
+        // them it sent the lanes other than 0 round the loop by themselves,
+        // to read their own (zero) item number for ever.
+        __builtin_amdgcn_wave_barrier();
+        int32_t lane = threadIdx.x & (kWave - 1);
+        opaque(lane);
+        int32_t next = 0;
+        if (lane == 0) next = atomicAdd(A.queue, 1);
+        const int32_t it = __builtin_amdgcn_readfirstlane(next);
+        if (it >= A.n_items) break;
+        const BItem I = load_uniform(A.items + it);
+        const BCluster C = load_uniform(A.clusters + I.cluster);
+        const int64_t j0 = C.j_begin + (int64_t)I.split * C.split_len;
+        const int64_t j1 = j0 + C.split_len < C.j_end ? j0 + C.split_len : C.j_end;
+        const Dest d{C.splits == 1, C.slot_base + (int64_t)I.split, (int64_t)C.row_begin,
+                     (int64_t)C.splits};
+        rows_pass_packed<MIXED>(A.f, (JRecPtr)(A.f.packed + C.rec_base + (j0 - C.j_begin)),
+                                I.row0, (int64_t)C.row_begin + C.n_rows, j0, j1, d, C.near);
+    }
+}
+
+// Packs every cluster's bodies, each followed by its own padding, and zeroes
+// the launch sequence's words: the queue's block (work counter, refinement
+// counter and arrival word) and the overflow word.  grid.y strides the
+// clusters.
+__global__ __launch_bounds__(kBlock) void batched_pack_kernel(BatchArgs A)
+{
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 64) {
+        A.queue[threadIdx.x] = 0;
+        if (threadIdx.x == 0) *A.f.overflow = 0;
+    }
+    for (int32_t c = blockIdx.y; c < A.n_clusters; c += gridDim.y) {
+        const BCluster C = A.clusters[c];
+        pack_range(A.f, A.f.packed + C.rec_base, C.j_begin, C.j_end,
+                   (int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
+    }
+}
+
 // W lanes per merged row (W = merge_width of the largest split count among
 // the split clusters), kBlock / W rows per work-group.
 template <int W>
@@ -107,26 +158,44 @@ int batched_shape_index(int tile, int lanes, int rows_per_lane)
     return -1;
 }
 
-int batched_max_blocks_per_cu(bool mixed, int shape)
+static const void *batched_packed_fn(bool mixed)
 {
-    const void *fn = mixed ? batched_fn<true>(shape) : batched_fn<false>(shape);
+    return mixed ? (const void *)&batched_packed_kernel<true>
+                 : (const void *)&batched_packed_kernel<false>;
+}
+
+int batched_max_blocks_per_cu(bool mixed, int shape, bool packed)
+{
+    const void *fn = packed ? batched_packed_fn(mixed)
+                            : (mixed ? batched_fn<true>(shape) : batched_fn<false>(shape));
     int blocks = 0;
     if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                   &blocks, fn, kBatchedShape[shape].lanes, 0) != hipSuccess) {
+                   &blocks, fn, packed ? kBlock : kBatchedShape[shape].lanes, 0) != hipSuccess) {
         (void)hipGetLastError();
         return 1;
     }
     return blocks > 0 ? blocks : 1;
 }
 
-hipError_t launch_batched(bool mixed, int shape, int grid, const BatchArgs &a, hipStream_t s)
+hipError_t launch_batched(bool mixed, int shape, bool packed, int grid, const BatchArgs &a,
+                          hipStream_t s)
 {
-    const void *fn = mixed ? batched_fn<true>(shape) : batched_fn<false>(shape);
+    const void *fn = packed ? batched_packed_fn(mixed)
+                            : (mixed ? batched_fn<true>(shape) : batched_fn<false>(shape));
     if (!fn) return hipErrorInvalidValue;
     BatchArgs arg = a;
     void *args[] = {&arg};
-    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3((unsigned)kBatchedShape[shape].lanes),
-                           args, 0, s);
+    const int lanes = packed ? kBlock : kBatchedShape[shape].lanes;
+    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3((unsigned)lanes), args, 0, s);
+}
+
+hipError_t launch_batched_pack(const BatchArgs &a, hipStream_t s)
+{
+    // about 2048 work-groups, at least one per cluster up to grid.y's limit
+    const unsigned gy = (unsigned)std::min<int32_t>(a.n_clusters, 65535);
+    const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(64, 2048 / gy));
+    hipLaunchKernelGGL(batched_pack_kernel, dim3(gx, gy), dim3(kBlock), 0, s, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_batched_merge(const BatchArgs &a, hipStream_t s)
@@ -163,6 +232,7 @@ struct BatchedCache {
     // device state
     void *dmem = nullptr;
     nb::BatchArgs args{};
+    bool packed = false;
     int grid = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -190,6 +260,15 @@ void batched_release(nb_ctx *ctx)
 
 static size_t r256(size_t b) { return (b + 255) / 256 * 256; }
 
+// Whether an ensemble of the default shape packs its bodies and runs the
+// scalar-operand kernel: not where the clusters are so small that the padding
+// records behind each would be a large share of the pack.
+static bool batched_pack_pays(const BatchedCache *c)
+{
+    const int64_t clusters = (int64_t)c->j_off.size() - 1;
+    return c->shape == 0 && c->j_off.back() >= 256 * clusters;
+}
+
 // Builds the work list, uploads metadata, and captures the launch graph.
 static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, bool mixed)
 {
@@ -207,6 +286,8 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
                                     (double)c->items_per_cu));
     const nb::BShape sh = nb::kBatchedShape[c->shape];
     const int64_t rows_per_item = (int64_t)sh.rows_per_lane * sh.lanes;
+    const int64_t n_total = c->j_off[(size_t)C];
+    const size_t b_rec = r256((size_t)(n_total + C * nb::kRecPad) * sizeof(nb::JRec));
     constexpr int64_t U = nb::kSplitUnit;
     for (int32_t k = 0; k < C; ++k) {
         const int64_t nc = c->j_off[k + 1] - c->j_off[k];
@@ -233,6 +314,7 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
         b.n_rows = (int32_t)rc;
         b.splits = (int32_t)S;
         b.near = nc >= nb::kNearMinBodies ? nb::kNearFactor : 1.0f;
+        b.rec_base = b.j_begin + k * nb::kRecPad;
         b.slot_base = 0;
         if (S > 1) {
             b.slot_base = slots;
@@ -246,10 +328,11 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     };
     std::vector<W> items;
     std::vector<int32_t> merge_rows, row_cluster;
+    const int64_t item_rows = c->packed ? nb::kWave : rows_per_item;
     for (int32_t k = 0; k < C; ++k) {
         const nb::BCluster &b = cl[(size_t)k];
-        for (int64_t r = 0; r < b.n_rows; r += rows_per_item) {
-            const int64_t nr = std::min<int64_t>(rows_per_item, b.n_rows - r);
+        for (int64_t r = 0; r < b.n_rows; r += item_rows) {
+            const int64_t nr = std::min<int64_t>(item_rows, b.n_rows - r);
             for (int32_t s = 0; s < b.splits; ++s) {
                 const int64_t j0 = b.j_begin + s * b.split_len;
                 const int64_t j1 = std::min<int64_t>(b.j_end, j0 + b.split_len);
@@ -268,7 +351,8 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     std::vector<nb::BItem> it_dev(items.size());
     for (size_t q = 0; q < items.size(); ++q) it_dev[q] = items[q].it;
 
-    // one device allocation: queue | clusters | items | merge rows | row cluster | slots
+    // one device allocation: queue | clusters | items | merge rows | row cluster | slots |
+    // refinement | packed bodies
     const size_t b_queue = 256;
     const size_t b_cl = r256(cl.size() * sizeof(nb::BCluster));
     const size_t b_it = r256(std::max<size_t>(1, it_dev.size()) * sizeof(nb::BItem));
@@ -278,7 +362,7 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     int64_t max_len = 1;
     for (int32_t k = 0; k < C; ++k) max_len = std::max<int64_t>(max_len, c->j_off[k + 1] - c->j_off[k]);
     const size_t b_redo = c->redo_k > 0.0 ? nb::redo_scratch_bytes(f.n_i, max_len) : 0;
-    const size_t total = b_queue + b_cl + 2 * b_mr + b_it + b_slots + b_redo;
+    const size_t total = b_queue + b_cl + 2 * b_mr + b_it + b_slots + b_redo + (c->packed ? b_rec : 0);
     if (ctx->scratch_limit && total > ctx->scratch_limit) return NB_ERR_OOM;
     hipError_t e = hipMalloc(&c->dmem, total);
     if (e != hipSuccess) {
@@ -300,6 +384,8 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     void *dslots = p;
     p += b_slots;
     void *dredo = p;
+    p += b_redo;
+    nb::JRec *drec = (nb::JRec *)p;
 
     e = hipMemcpy(dcl, cl.data(), cl.size() * sizeof(nb::BCluster), hipMemcpyHostToDevice);
     if (e == hipSuccess && !it_dev.empty())
@@ -323,7 +409,9 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     if (c->redo_k > 0.0) nb::bind_redo_scratch(A.f, dredo, queue + 32, groups, max_len);
     A.f.splits = 0;          // per-cluster
     A.f.split_len = 0;
+    A.f.packed = c->packed ? drec : nullptr;
     A.clusters = dcl;
+    A.n_clusters = C;
     A.items = dit;
     A.n_items = (int32_t)it_dev.size();
     A.queue = queue;
@@ -333,8 +421,10 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     A.max_splits = 1;
     for (int32_t k = 0; k < C; ++k) A.max_splits = std::max(A.max_splits, cl[(size_t)k].splits);
     const int cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
-    c->grid = cus * nb::batched_max_blocks_per_cu(mixed, c->shape);
-    if (A.n_items < c->grid) c->grid = std::max(1, A.n_items);
+    c->grid = cus * nb::batched_max_blocks_per_cu(mixed, c->shape, c->packed);
+    // work-groups past the last item (a packed one pulls an item per wave) would do nothing
+    const int pulls = c->packed ? nb::kBlock / nb::kWave : 1;
+    c->grid = std::max(1, std::min(c->grid, (A.n_items + pulls - 1) / pulls));
 
     // capture the launch sequence on a private stream (default priority)
     hipStream_t cs = nullptr;
@@ -344,9 +434,14 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     if (e == hipSuccess) {
         // the queue's block holds the work counter, the refinement counter
         // and the refinement's arrival word (which also resets itself)
-        hipError_t le = nb::launch_fill_i32(queue, 0, 64, cs);
-        if (le == hipSuccess) le = nb::launch_fill_i32(f.overflow, 0, 1, cs);
-        if (le == hipSuccess) le = nb::launch_batched(mixed, c->shape, c->grid, A, cs);
+        hipError_t le = hipSuccess;
+        if (c->packed) {
+            le = nb::launch_batched_pack(A, cs);
+        } else {
+            le = nb::launch_fill_i32(queue, 0, 64, cs);
+            if (le == hipSuccess) le = nb::launch_fill_i32(f.overflow, 0, 1, cs);
+        }
+        if (le == hipSuccess) le = nb::launch_batched(mixed, c->shape, c->packed, c->grid, A, cs);
         if (le == hipSuccess) le = nb::launch_batched_merge(A, cs);
         if (le == hipSuccess && c->redo_k > 0.0)
             le = nb::launch_redo(A.f, cs);
@@ -497,7 +592,12 @@ extern "C" int nb_regular_force_batched(nb_ctx *ctx, int32_t n_clusters, const i
         f.nb_list = nb_list;
         f.overflow = overflow;
         f.status = status;
+        c->packed = batched_pack_pays(c);
         rc = build_cache(ctx, c, f, mixed);
+        if (rc == NB_ERR_OOM && c->packed) {   // no room for the packed bodies
+            c->packed = false;
+            rc = build_cache(ctx, c, f, mixed);
+        }
         if (rc != NB_OK) {
             release_one(ctx, c);
             return rc;
@@ -510,9 +610,10 @@ extern "C" int nb_regular_force_batched(nb_ctx *ctx, int32_t n_clusters, const i
     const nb::BShape &sh = nb::kBatchedShape[hit->shape];
     std::snprintf(ctx->last_plan, sizeof ctx->last_plan,
                   "batched clusters=%d items=%d grid=%d tile=%d lanes=%d rows_per_lane=%d "
-                  "items_per_cu=%d merge_rows=%d shape=%s prec=%s",
+                  "items_per_cu=%d merge_rows=%d shape=%s prec=%s%s",
                   n_clusters, hit->args.n_items, hit->grid, sh.tile, sh.lanes, sh.rows_per_lane,
-                  hit->items_per_cu, hit->args.n_merge_rows, origin, mixed ? "mixed" : "fp64");
+                  hit->items_per_cu, hit->args.n_merge_rows, origin, mixed ? "mixed" : "fp64",
+                  hit->packed ? " bodies=packed" : "");
     hipEvent_t ev[2];
     hipError_t e = timed_begin(ctx, NB_CLASS_BATCHED, ev);
     if (e == hipSuccess) e = hipGraphLaunch(hit->exec, ctx->stream);

@@ -11,6 +11,9 @@
 //    tile) and every lane reads each staged body by LDS broadcast.  Neighbour
 //    appends are lane-private (see nb_rows.h).
 //
+//    Large blocks first pack the j-set into 64-byte records and read each
+//    body by scalar loads into wave-uniform operands instead (no LDS).
+//
 //  * row-group-per-wave (small blocks): the 64 lanes of a wavefront take 64
 //    consecutive j while 1, 2 or 4 rows sit in scalar registers; sums are
 //    reduced across the wave with butterfly shuffles and neighbour appends are
@@ -53,6 +56,33 @@ __global__ __launch_bounds__(kBlock) void force_rows_kernel(ForceArgs a)
     const Dest d{a.splits == 1, (int64_t)split, 0, (int64_t)a.splits};
     rows_pass<MIXED, IR, kTile, kBlock>(a, tile, (int64_t)blockIdx.x * IR * kBlock, a.n_i, j0, j1, d,
                          a.near_factor);
+}
+
+__global__ __launch_bounds__(kBlock) void pack_kernel(ForceArgs a)
+{
+    clear_call_words(a);
+    pack_range(a, a.packed, 0, a.n, (int64_t)blockIdx.x * kBlock + threadIdx.x,
+               (int64_t)gridDim.x * kBlock);
+}
+
+// Row-per-lane pass over the packed j-set.  Every wave is on its own: wave w
+// (global) takes row tile w % tiles (kWave rows) over j-range w / tiles, so
+// the waves of a work-group mostly share one j-range (and its lines in the
+// scalar cache) and no lane is lost to row tiles larger than a wave.
+template <bool MIXED>
+__global__ __launch_bounds__(kBlock) void force_packed_kernel(ForceArgs a)
+{
+    const int64_t tiles = (a.n_i + kWave - 1) / kWave;
+    const int64_t gw = (int64_t)blockIdx.x * (kBlock / kWave) +
+                       __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (gw >= tiles * a.splits) return;   // whole wave leaves together
+    const int32_t split = (int32_t)(gw / tiles);
+    const int64_t tile = gw - (int64_t)split * tiles;
+    const int64_t j0 = (int64_t)split * a.split_len;
+    const int64_t j1 = j0 + a.split_len < a.n ? j0 + a.split_len : a.n;
+    const Dest d{a.splits == 1, (int64_t)split, 0, (int64_t)a.splits};
+    rows_pass_packed<MIXED>(a, (JRecPtr)(a.packed + j0), tile * kWave, a.n_i, j0, j1, d,
+                            a.near_factor);
 }
 
 // One-wave work-groups of the row-per-lane pass (64 rows, a 64-body LDS tile):
@@ -206,20 +236,19 @@ __global__ __launch_bounds__(kBlock) void force_wave_kernel(ForceArgs a)
                         add_term_f64(S[g].ax, S[g].ay, S[g].az, S[g].jx, S[g].jy, S[g].jz,
                                      dx[g], dy[g], dz[g], J.vx - rvx[g], J.vy - rvy[g],
                                      J.vz - rvz[g], J.m);
+                    if (cand[g]) r2f[g] = kExclR2F;
                 }
             }
 #pragma unroll
             for (int g = 0; g < G; ++g)
                 accum_mixed(S[g], fx[g], fy[g], fz[g], r2f[g], J.vx - rvx[g], J.vy - rvy[g],
-                            J.vz - rvz[g], J.m32, cand[g]);
+                            J.vz - rvz[g], J.m32);
         } else {
             double r2[G];
-            bool excl[G];
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 r2[g] = __builtin_fma(dz[g], dz[g], __builtin_fma(dy[g], dy[g], dx[g] * dx[g]));
                 cand[g] = r2[g] < hi[g];
-                excl[g] = false;
                 any = any || cand[g];
             }
             if (__ballot(any)) {
@@ -234,13 +263,13 @@ __global__ __launch_bounds__(kBlock) void force_wave_kernel(ForceArgs a)
                         if (p < lcap[g]) lst[g][p] = jidx;
                     }
                     cnt[g] += __popcll(nm);
-                    excl[g] = nbr || self;
+                    if (nbr || self) r2[g] = kExclR2;
                 }
             }
 #pragma unroll
             for (int g = 0; g < G; ++g)
                 accum_f64(S[g], dx[g], dy[g], dz[g], r2[g], J.vx - rvx[g], J.vy - rvy[g],
-                          J.vz - rvz[g], J.m, excl[g]);
+                          J.vz - rvz[g], J.m);
         }
         if constexpr (MIXED) {
             if (++iter == kFold) {
@@ -565,10 +594,24 @@ void force_bind_scratch(ForceArgs &a, void *base)
     bind_slot_scratch(a, a.splits > 1 ? (int64_t)a.splits * a.n_i : 0, base);
 }
 
+size_t packed_bytes(int64_t n) { return round256((size_t)(n + kRecPad) * sizeof(JRec)); }
+
+hipError_t launch_pack(const ForceArgs &a, hipStream_t s)
+{
+    const unsigned grid = (unsigned)std::min<int64_t>(4096, (a.n + kRecPad + kBlock - 1) / kBlock);
+    hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(kBlock), 0, s, a);
+    return hipGetLastError();
+}
+
 template <bool MIXED>
 static hipError_t launch_force_t(const Plan &p, const ForceArgs &a, hipStream_t s)
 {
-    if (p.mapping == 1) {
+    if (a.packed) {
+        const int64_t waves = ((int64_t)a.n_i + kWave - 1) / kWave * p.splits;
+        const int64_t per = kBlock / kWave;
+        hipLaunchKernelGGL((force_packed_kernel<MIXED>), dim3((unsigned)((waves + per - 1) / per)),
+                           dim3(kBlock), 0, s, a);
+    } else if (p.mapping == 1) {
         const int per = p.rows_per_lane * kBlock;
         dim3 grid((unsigned)((a.n_i + per - 1) / per), (unsigned)p.splits);
         switch (p.rows_per_lane) {

@@ -28,6 +28,17 @@ constexpr double kFar = 1.0e18;
 // Status bits (mirrors include/nbreg.h).
 constexpr uint32_t kStOverflow = 1u, kStBadIndex = 2u, kStNonFinite = 4u;
 
+// One body of the packed j-set that the scalar-operand row pass streams: one
+// 64-byte line, read by scalar loads.
+struct alignas(64) JRec {
+    double x, y, z, vx, vy, vz, m;
+    float m32;
+    int32_t pad;
+};
+// Padding records behind a packed j-range: the last run of kFold bodies is
+// completed with bodies that add nothing, and the pass loads two bodies ahead.
+constexpr int64_t kRecPad = kFold + 2;
+
 // A contiguous range of j-set bodies [j_begin, j_end) and the rows that see it.
 struct ForceArgs {
     int64_t n;            // bodies in the whole concatenated arrays (plane stride)
@@ -43,11 +54,14 @@ struct ForceArgs {
     int32_t *nb_count, *nb_list;
     int32_t *overflow;
     uint32_t *status;
-    // words the force kernel zeroes as it starts (null: none).  Set only for
-    // split launches, whose force kernel writes neither the overflow word nor
-    // the refinement counter (the merge does), so no separate clearing launch
-    // is needed.
+    // words the call's first kernel zeroes as it starts (null: none): the pack
+    // kernel, or the force kernel of a split launch, which writes neither the
+    // overflow word nor the refinement counter (the merge does), so no
+    // separate clearing launch is needed.
     int32_t *clear0, *clear1;
+    // packed j-set [n + kRecPad] (null: the pass streams the SoA planes
+    // through LDS)
+    JRec *packed;
     // split layout: split s covers j in [s * split_len, min(n, (s+1) * split_len))
     int32_t splits;
     int64_t split_len;
@@ -107,6 +121,11 @@ void bind_slot_scratch(ForceArgs &a, int64_t slots, void *base);
 // Carves the scratch pointers of 'a' out of 'base'.
 void force_bind_scratch(ForceArgs &a, void *base);
 
+// Packed j-set of n bodies: scratch bytes, and the launch that fills it from
+// the SoA planes (and zeroes the call's words).
+size_t packed_bytes(int64_t n);
+hipError_t launch_pack(const ForceArgs &a, hipStream_t s);
+
 // Launchers (return hipError_t of the launch).
 hipError_t launch_force(const Plan &p, bool mixed, const ForceArgs &a, hipStream_t s);
 hipError_t launch_merge(bool mixed, const ForceArgs &a, hipStream_t s);
@@ -139,6 +158,7 @@ struct BCluster {
     int64_t j_begin, j_end;   // bodies of the cluster
     int64_t split_len;        // j per split
     int64_t slot_base;        // first slot of the cluster (splits > 1 only)
+    int64_t rec_base;         // packed ensembles: record of body j_begin
     int32_t row_begin;        // rows of the cluster
     int32_t n_rows;
     int32_t splits;
@@ -155,6 +175,7 @@ struct BatchArgs {
     const BCluster *clusters;
     const BItem *items;
     int32_t n_items;
+    int32_t n_clusters;
     int32_t *queue;           // work counter, zeroed before each launch
     const int32_t *merge_rows;   // rows of clusters with splits > 1
     const int32_t *row_cluster;  // cluster of each merge row
@@ -177,8 +198,12 @@ constexpr BShape kBatchedShape[kBatchedShapes] = {
 constexpr int kSplitUnit = 256;
 // Index of a shape in kBatchedShape, or -1.
 int batched_shape_index(int tile, int lanes, int rows_per_lane);
-hipError_t launch_batched(bool mixed, int shape, int grid, const BatchArgs &a, hipStream_t s);
+// packed: the scalar-operand kernel (items of one wave, kWave rows) instead of
+// the LDS kernel of the shape.
+hipError_t launch_batched(bool mixed, int shape, bool packed, int grid, const BatchArgs &a,
+                          hipStream_t s);
+hipError_t launch_batched_pack(const BatchArgs &a, hipStream_t s);
 hipError_t launch_batched_merge(const BatchArgs &a, hipStream_t s);
-int batched_max_blocks_per_cu(bool mixed, int shape);
+int batched_max_blocks_per_cu(bool mixed, int shape, bool packed);
 
 }  // namespace nb

@@ -119,14 +119,23 @@ __device__ __forceinline__ bool needs_redo(double k, double ax, double ay, doubl
     return k * k * va > na2 || k * k * vj > nj2;
 }
 
-// FP64 regular term.  r2 is the FP64 squared distance; 'excl' marks the self
-// pair or a neighbour (the term is then exactly zero: r^-1 is selected to 0).
+// Squared distances that stand for an excluded pair (self, neighbour, or a
+// near pair whose term is added elsewhere).  The rare branch that finds such a
+// pair overwrites its squared distance, and the term then comes out as exactly
+// zero: FP32, rsq(+inf) = 0; FP64, y = 2^-511.5 and y^2 = 2^-1023, so (m y) y^2
+// is below the smallest FP64 number for every mass below 2^400 (+inf would
+// give inf * 0 in rsqrt_f64).  So the pair loops need no select on r^-1:
+// on gfx950 a v_cndmask_b32 takes a full FP64 slot (4.5 cycles per wave
+// against 2.9 of v_mul_f32), and an FP64 select takes two.
+constexpr float kExclR2F = __builtin_inff();
+constexpr double kExclR2 = 0x1p1023;
+
+// FP64 regular term.  r2 is the FP64 squared distance (kExclR2: excluded).
 __device__ __forceinline__ void accum_f64(Sums<false> &S, double dx, double dy, double dz,
                                           double r2, double ux, double uy, double uz,
-                                          double mj, bool excl)
+                                          double mj)
 {
-    double y = rsqrt_f64(r2);
-    y = excl ? 0.0 : y;
+    const double y = rsqrt_f64(r2);
     const double y2 = y * y;
     const double mr3 = (mj * y) * y2;               // m / r^3
     const double s = __builtin_fma(dz, uz, __builtin_fma(dy, uy, dx * ux));
@@ -142,14 +151,14 @@ __device__ __forceinline__ void accum_f64(Sums<false> &S, double dx, double dy, 
     S.prz = __builtin_fma(q, dz, S.prz);
 }
 
-// Mixed regular term: FP32 arithmetic on the FP32-rounded FP64 differences.
+// Mixed regular term: FP32 arithmetic on the FP32-rounded FP64 differences
+// (r2f = kExclR2F: excluded).
 __device__ __forceinline__ void accum_mixed(Sums<true> &S, float fx, float fy, float fz,
                                             float r2f, double ux, double uy, double uz,
-                                            float mj, bool excl)
+                                            float mj)
 {
     const float gx = (float)ux, gy = (float)uy, gz = (float)uz;
-    float y = __builtin_amdgcn_rsqf(r2f);
-    y = excl ? 0.0f : y;
+    const float y = __builtin_amdgcn_rsqf(r2f);
     const float y2 = y * y;
     const float mr3 = (mj * y) * y2;
     const float s = __builtin_fmaf(fz, gz, __builtin_fmaf(fy, gy, fx * gx));

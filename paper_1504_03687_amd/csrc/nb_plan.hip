@@ -134,6 +134,22 @@ Plan auto_plan(const nb_ctx *ctx, int64_t n, int32_t n_i, bool mixed)
     return p;
 }
 
+// Whether a row-per-lane launch (mapping 1, one row per lane) packs the j-set
+// and runs the scalar-operand kernel.  The pack costs a launch and a copy of
+// the j-set (about 3 us at n = 131072, 25 us at 2^20), and a wave alone on its
+// SIMD waits longer for scalar loads than for LDS, so the block has to be
+// large enough to repay both.  Whole calls, LDS against packed, mixed / FP64:
+// 16384 rows of 131072 1959 / 2735 against 1812 / 2487 us, 4096 rows of
+// 131072 522 / 699 against 493 / 644, 16384 rows of 16384 306 / 390 against
+// 295 / 363, 1024 rows of 2^20 975 / 1325 against 948 / 1243; the two meet at
+// 1024 rows of 131072 (186 / 195 against 193 / 198) and 512 rows of 2^20 (483
+// / 673 against 486 / 659); 256 rows of 2^20 260 / 351 against 280 / 365.
+bool pack_pays(const Plan &p, int64_t n, int32_t n_i)
+{
+    return p.mapping == 1 && p.rows_per_lane == 1 && n_i >= 512 &&
+           n * (int64_t)n_i > (int64_t(1) << 27);
+}
+
 // Normalises a plan for (n, n_i): fills zero fields, rounds split lengths.
 void finish_plan(Plan &p, int64_t n, int32_t n_i, int64_t *split_len)
 {

@@ -23,6 +23,45 @@ struct alignas(16) JBody {
     double vx, vy, vz;
     float m32;
     int32_t pad;
+    __device__ __forceinline__ double mass() const { return m; }
+};
+
+// A body of the packed j-set in scalar registers: positions, velocities and
+// the mass of the plan's precision.  The mixed plan reads the FP64 mass from
+// the record in the rare branch only, which keeps eight scalar registers free.
+typedef const __attribute__((address_space(4))) JRec *JRecPtr;
+template <bool MIXED>
+struct SBody {
+    double x, y, z, vx, vy, vz;
+    double m;      // FP64 plan
+    float m32;     // mixed plan
+    JRecPtr rec;
+    __device__ __forceinline__ double mass() const { return MIXED ? rec->m : m; }
+    __device__ __forceinline__ void load(JRecPtr p)
+    {
+        rec = p;
+        x = p->x;
+        y = p->y;
+        z = p->z;
+        vx = p->vx;
+        vy = p->vy;
+        vz = p->vz;
+        if constexpr (MIXED)
+            m32 = p->m32;
+        else
+            m = p->m;
+    }
+    // A use of every loaded register: the wait for the loads stands here, and
+    // loads issued after it are not waited for with them.  Emits no
+    // instruction of its own.
+    __device__ __forceinline__ void arrive()
+    {
+        __asm__ volatile("" : "+s"(x), "+s"(y), "+s"(z), "+s"(vx), "+s"(vy), "+s"(vz));
+        if constexpr (MIXED)
+            __asm__ volatile("" : "+s"(m32));
+        else
+            __asm__ volatile("" : "+s"(m));
+    }
 };
 
 template <bool MIXED>
@@ -100,8 +139,8 @@ __device__ __forceinline__ void row_init(Row<MIXED> &R, const ForceArgs &a, int6
 // Row-per-lane mapping: each lane appends to its own row's list (in j order).
 // Rare branch of a mixed pair (neighbour, self or near pair): appends a
 // neighbour, or adds a near pair's term in FP64.
-template <bool MIXED>
-__device__ __forceinline__ void rare_mixed(Row<MIXED> &R, const JBody &J, int32_t jidx, float r2f,
+template <bool MIXED, class Body>
+__device__ __forceinline__ void rare_mixed(Row<MIXED> &R, const Body &J, int32_t jidx, float r2f,
                                            double dx, double dy, double dz)
 {
     double ex = dx, ey = dy, ez = dz;
@@ -118,7 +157,7 @@ __device__ __forceinline__ void rare_mixed(Row<MIXED> &R, const JBody &J, int32_
         ++R.cnt;
     } else if (!self) {
         add_term_f64(R.S.ax, R.S.ay, R.S.az, R.S.jx, R.S.jy, R.S.jz, ex, ey, ez,
-                     J.vx - R.vx, J.vy - R.vy, J.vz - R.vz, J.m);
+                     J.vx - R.vx, J.vy - R.vy, J.vz - R.vz, J.mass());
     }
 }
 
@@ -147,10 +186,13 @@ __device__ __forceinline__ bool rare_f64(Row<MIXED> &R, int32_t jidx, double dx,
 // r2f (the neighbour test itself), FP32 terms; pairs with r2f below the
 // near bound (neighbours, self, near pairs) take the rare branch.  FP64: FP64
 // r2 against the candidate bound, the exact canonical test only for
-// candidates.  Every accumulator receives the terms of j and then j+1, as a
-// loop over single j would give them.
-template <bool MIXED>
-__device__ __forceinline__ void pair_rows2(Row<MIXED> &R, const JBody &J0, const JBody &J1,
+// candidates.  One minimum and one compare decide for both j whether any lane
+// has a rare case (NaN squared distances are never below the bound, alone or
+// in the minimum), and a pair handled there gets an excluding squared
+// distance, so the common path holds no select.  Every accumulator receives
+// the terms of j and then j+1, as a loop over single j would give them.
+template <bool MIXED, class Body>
+__device__ __forceinline__ void pair_rows2(Row<MIXED> &R, const Body &J0, const Body &J1,
                                            int32_t jidx0)
 {
     if constexpr (MIXED) {
@@ -158,32 +200,31 @@ __device__ __forceinline__ void pair_rows2(Row<MIXED> &R, const JBody &J0, const
         const double dx1 = J1.x - R.x, dy1 = J1.y - R.y, dz1 = J1.z - R.z;
         const float fx0 = (float)dx0, fy0 = (float)dy0, fz0 = (float)dz0;
         const float fx1 = (float)dx1, fy1 = (float)dy1, fz1 = (float)dz1;
-        const float r0 = __builtin_fmaf(fz0, fz0, __builtin_fmaf(fy0, fy0, fx0 * fx0));
-        const float r1 = __builtin_fmaf(fz1, fz1, __builtin_fmaf(fy1, fy1, fx1 * fx1));
-        const bool c0 = r0 < R.candf, c1 = r1 < R.candf;
-        // the FP32 terms first, the rare cases after them: every LDS read of
-        // the two bodies can then be issued before the first arithmetic (the
-        // rare cases touch only the FP64 sums and the list, so the order of
-        // the two changes no result)
-        accum_mixed(R.S, fx0, fy0, fz0, r0, J0.vx - R.vx, J0.vy - R.vy, J0.vz - R.vz, J0.m32, c0);
-        accum_mixed(R.S, fx1, fy1, fz1, r1, J1.vx - R.vx, J1.vy - R.vy, J1.vz - R.vz, J1.m32, c1);
-        if (c0 || c1) {
-            if (c0) rare_mixed<MIXED>(R, J0, jidx0, r0, dx0, dy0, dz0);
-            if (c1) rare_mixed<MIXED>(R, J1, jidx0 + 1, r1, dx1, dy1, dz1);
+        float r0 = __builtin_fmaf(fz0, fz0, __builtin_fmaf(fy0, fy0, fx0 * fx0));
+        float r1 = __builtin_fmaf(fz1, fz1, __builtin_fmaf(fy1, fy1, fx1 * fx1));
+        if (__builtin_fminf(r0, r1) < R.candf) {
+            if (r0 < R.candf) {
+                rare_mixed(R, J0, jidx0, r0, dx0, dy0, dz0);
+                r0 = kExclR2F;
+            }
+            if (r1 < R.candf) {
+                rare_mixed(R, J1, jidx0 + 1, r1, dx1, dy1, dz1);
+                r1 = kExclR2F;
+            }
         }
+        accum_mixed(R.S, fx0, fy0, fz0, r0, J0.vx - R.vx, J0.vy - R.vy, J0.vz - R.vz, J0.m32);
+        accum_mixed(R.S, fx1, fy1, fz1, r1, J1.vx - R.vx, J1.vy - R.vy, J1.vz - R.vz, J1.m32);
     } else {
         const double dx0 = J0.x - R.x, dy0 = J0.y - R.y, dz0 = J0.z - R.z;
         const double dx1 = J1.x - R.x, dy1 = J1.y - R.y, dz1 = J1.z - R.z;
-        const double r0 = __builtin_fma(dz0, dz0, __builtin_fma(dy0, dy0, dx0 * dx0));
-        const double r1 = __builtin_fma(dz1, dz1, __builtin_fma(dy1, dy1, dx1 * dx1));
-        const bool c0 = r0 < R.hi, c1 = r1 < R.hi;
-        bool e0 = false, e1 = false;
-        if (c0 || c1) {
-            if (c0) e0 = rare_f64<MIXED>(R, jidx0, dx0, dy0, dz0);
-            if (c1) e1 = rare_f64<MIXED>(R, jidx0 + 1, dx1, dy1, dz1);
+        double r0 = __builtin_fma(dz0, dz0, __builtin_fma(dy0, dy0, dx0 * dx0));
+        double r1 = __builtin_fma(dz1, dz1, __builtin_fma(dy1, dy1, dx1 * dx1));
+        if (__builtin_fmin(r0, r1) < R.hi) {
+            if (r0 < R.hi && rare_f64<MIXED>(R, jidx0, dx0, dy0, dz0)) r0 = kExclR2;
+            if (r1 < R.hi && rare_f64<MIXED>(R, jidx0 + 1, dx1, dy1, dz1)) r1 = kExclR2;
         }
-        accum_f64(R.S, dx0, dy0, dz0, r0, J0.vx - R.vx, J0.vy - R.vy, J0.vz - R.vz, J0.m, e0);
-        accum_f64(R.S, dx1, dy1, dz1, r1, J1.vx - R.vx, J1.vy - R.vy, J1.vz - R.vz, J1.m, e1);
+        accum_f64(R.S, dx0, dy0, dz0, r0, J0.vx - R.vx, J0.vy - R.vy, J0.vz - R.vz, J0.m);
+        accum_f64(R.S, dx1, dy1, dz1, r1, J1.vx - R.vx, J1.vy - R.vy, J1.vz - R.vz, J1.m);
     }
 }
 
@@ -204,6 +245,28 @@ __device__ __forceinline__ void load_body(JBody &J, const ForceArgs &a, int64_t 
     }
     J.m32 = (float)J.m;
     J.pad = 0;
+}
+
+// Packs bodies [j0, j1) of the SoA planes into records from out on, followed
+// by kRecPad padding records.  k, stride: this thread's share.
+__device__ __forceinline__ void pack_range(const ForceArgs &a, JRec *out, int64_t j0, int64_t j1,
+                                           int64_t k, int64_t stride)
+{
+    for (int64_t q = k; q < j1 - j0 + kRecPad; q += stride) {
+        JBody J;
+        load_body(J, a, j0 + q, j1);
+        JRec r;
+        r.x = J.x;
+        r.y = J.y;
+        r.z = J.z;
+        r.vx = J.vx;
+        r.vy = J.vy;
+        r.vz = J.vz;
+        r.m = J.m;
+        r.m32 = J.m32;
+        r.pad = 0;
+        out[q] = r;
+    }
 }
 
 // Appends row b (with its j-range) to the FP64 redo list.
@@ -362,6 +425,62 @@ __device__ __forceinline__ void rows_pass(const ForceArgs &a, JBody (*tile)[T], 
     flush_flags(a, ovf, bad, nonfin);
 }
 
+// One wave's kWave rows [row0, row0 + kWave) against bodies [j0, j1) of the
+// packed j-set, whose records start at rec: the bodies are wave-uniform
+// operands in scalar registers, loaded two bodies ahead, so the pair loop has
+// no LDS traffic, no barrier and no body in vector registers.  The LDS pass
+// reads 52 to 56 bytes per lane and pair by broadcast, about 105 (mixed) and
+// 112 (FP64) LDS cycles per CU for the 4 x 64 pairs that its SIMDs compute in
+// 120 and 165 cycles, which held both back: 65536 rows at n = 2^20 took 56.8
+// ms mixed and 79.1 ms FP64 through LDS and take 51.4 and 74.2 ms here (1.34
+// and 0.93e12 pairs/s).  What bounds it now is VALU issue: the loop's
+// instructions, timed one by one at four waves per SIMD, add up to 53 ns
+// (mixed) and 67 ns (FP64) per 64 pairs and SIMD; it takes 49 and 70.
+// Order, fold points and results are those of rows_pass.  Records past j1 up
+// to the next multiple of kFold from j0, and two more, must be readable, and
+// at the end of the j-set they are padding.
+template <bool MIXED>
+__device__ __forceinline__ void rows_pass_packed(const ForceArgs &a, JRecPtr rec, int64_t row0,
+                                                 int64_t row_end, int64_t j0, int64_t j1,
+                                                 const Dest &d, float near)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t b = row0 + lane;
+    Row<MIXED> R;
+    row_init(R, a, b, row_end, d, near);
+    R.jend = (int32_t)j1;
+    if (__ballot(R.i >= 0) != 0) {
+        SBody<MIXED> A0, A1, B0, B1;
+        A0.load(rec);
+        A1.load(rec + 1);
+        for (int64_t jb = j0; jb < j1; jb += kFold) {
+#pragma unroll 1
+            for (int q = 0; q < kFold; q += 4) {
+                const int32_t jidx = (int32_t)jb + q;
+                A0.arrive();
+                A1.arrive();
+                B0.load(rec + 2);
+                B1.load(rec + 3);
+                __builtin_amdgcn_sched_barrier(0);
+                pair_rows2<MIXED>(R, A0, A1, jidx);
+                B0.arrive();
+                B1.arrive();
+                rec += 4;
+                A0.load(rec);
+                A1.load(rec + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                pair_rows2<MIXED>(R, B0, B1, jidx + 2);
+            }
+            if (MIXED || ((jb - j0 + kFold) & (kFoldF64 - 1)) == 0) R.S.fold();
+        }
+    }
+    bool ovf = false, bad = false, nonfin = false;
+    if constexpr (!MIXED) R.S.fold();
+    if (b < row_end)
+        row_store<MIXED>(a, b, d, R.i >= 0, R.S, R.cnt, ovf, bad, nonfin, j0, j1);
+    flush_flags(a, ovf, bad, nonfin);
+}
+
 // Geometry of one row's splits for the merge.
 struct MergeGeom {
     int32_t splits;
@@ -402,6 +521,22 @@ __device__ __forceinline__ int32_t load_word_uniform(const int32_t *p)
 __device__ __forceinline__ double load_f64_uniform(const double *p)
 {
     return *(const __attribute__((address_space(4))) double *)p;
+}
+
+// A record of an earlier launch or upload that no lane writes during the
+// kernel, read at a uniform address into scalar registers.
+template <class T>
+__device__ __forceinline__ T load_uniform(const T *p)
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    const __attribute__((address_space(4))) uint32_t *q =
+        (const __attribute__((address_space(4))) uint32_t *)p;
+    uint32_t w[sizeof(T) / 4];
+#pragma unroll
+    for (size_t k = 0; k < sizeof(T) / 4; ++k) w[k] = q[k];
+    T r;
+    __builtin_memcpy(&r, w, sizeof(T));
+    return r;
 }
 
 // Lanes per row of the single-wave merge for a given split count: the next of
@@ -599,14 +734,13 @@ __device__ __forceinline__ void redo_chunk(const ForceArgs &a, int32_t q, int32_
         JBody J;
         load_body(J, a, j, cj1);
         const double dx = J.x - xi, dy = J.y - yi, dz = J.z - zi;
-        const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-        bool excl = false;
+        double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
         if (r2 < hi) {
             double ex = dx, ey = dy, ez = dz;
             opaque(ex, ey, ez);
-            excl = j == i || canon_r2f(ex, ey, ez) < rs2f;
+            if (j == i || canon_r2f(ex, ey, ez) < rs2f) r2 = kExclR2;
         }
-        accum_f64(S, dx, dy, dz, r2, J.vx - vxi, J.vy - vyi, J.vz - vzi, J.m, excl);
+        accum_f64(S, dx, dy, dz, r2, J.vx - vxi, J.vy - vyi, J.vz - vzi, J.m);
     }
     S.fold();
     out[0] = S.ax;
@@ -660,15 +794,13 @@ __device__ __forceinline__ void redo_chunk_rows(const ForceArgs &a, int32_t q0, 
         for (int r = 0; r < kRedoRows; ++r) {
             if (r >= nr) break;
             const double dx = J.x - xi[r], dy = J.y - yi[r], dz = J.z - zi[r];
-            const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-            bool excl = false;
+            double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
             if (r2 < hi[r]) {
                 double ex = dx, ey = dy, ez = dz;
                 opaque(ex, ey, ez);
-                excl = j == ii[r] || canon_r2f(ex, ey, ez) < rs2f[r];
+                if (j == ii[r] || canon_r2f(ex, ey, ez) < rs2f[r]) r2 = kExclR2;
             }
-            accum_f64(S[r], dx, dy, dz, r2, J.vx - vxi[r], J.vy - vyi[r], J.vz - vzi[r], J.m,
-                      excl);
+            accum_f64(S[r], dx, dy, dz, r2, J.vx - vxi[r], J.vy - vyi[r], J.vz - vzi[r], J.m);
         }
     }
 #pragma unroll

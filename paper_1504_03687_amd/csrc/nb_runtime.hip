@@ -407,15 +407,28 @@ static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const do
     fa.splits = p.splits;
     fa.split_len = split_len;
     const size_t slot_bytes = nb::force_scratch_bytes(p, n_i);
-    if (!fixed && redo_bytes + slot_bytes > 0) {
-        int rc = ensure_scratch(ctx, redo_bytes + slot_bytes);
+    // the packed j-set, where it pays and its memory is there: a workspace or
+    // scratch limit that is too small for it runs the LDS kernels as before
+    size_t pack_bytes = pack_pays(p, n, n_i) ? nb::packed_bytes(n) : 0;
+    if (fixed && redo_bytes + slot_bytes + pack_bytes > fixed_bytes) pack_bytes = 0;
+    if (!fixed && redo_bytes + slot_bytes + pack_bytes > 0) {
+        int rc = ensure_scratch(ctx, redo_bytes + slot_bytes + pack_bytes);
+        if (rc == NB_ERR_OOM && pack_bytes) {
+            pack_bytes = 0;
+            rc = redo_bytes + slot_bytes > 0 ? ensure_scratch(ctx, redo_bytes + slot_bytes) : NB_OK;
+        }
         if (rc != NB_OK) return rc;
         base = ctx->scratch;
     }
+    if (pack_bytes) {
+        fa.packed = (nb::JRec *)base;
+        base = (char *)base + pack_bytes;
+    }
     if (redo_bytes) nb::bind_redo_scratch(fa, base, ctx->words, groups, n, rcap_limit);
     // the overflow word and the refinement counter start at zero: zeroed by
-    // the force kernel of a split launch, else by one small launch first
-    if (p.splits > 1) {
+    // the pack kernel or the force kernel of a split launch, else by one small
+    // launch first
+    if (p.splits > 1 || pack_bytes) {
         fa.clear0 = overflow;
         fa.clear1 = redo_bytes ? fa.redo_count : nullptr;
     } else {
@@ -424,16 +437,17 @@ static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const do
     }
     nb::force_bind_scratch(fa, (char *)base + redo_bytes);
     std::snprintf(ctx->last_plan, sizeof ctx->last_plan,
-                  "mapping=%d rows_per_lane=%d splits=%d split_len=%lld prec=%s%s%s", p.mapping,
+                  "mapping=%d rows_per_lane=%d splits=%d split_len=%lld prec=%s%s%s%s", p.mapping,
                   p.rows_per_lane, p.splits, (long long)split_len, mixed ? "mixed" : "fp64",
                   p.f64 && prec == NB_MIXED ? " requested=mixed" : "",
-                  fixed ? " workspace=fixed" : "");
+                  fixed ? " workspace=fixed" : "", pack_bytes ? " bodies=packed" : "");
 
     // timing events are created on demand, so the allocation-free path is
     // never timed
     const bool timed = !fixed;
     hipEvent_t ev[2] = {nullptr, nullptr};
     if (timed) e = timed_begin(ctx, NB_CLASS_FORCE, ev);
+    if (e == hipSuccess && fa.packed) e = nb::launch_pack(fa, ctx->stream);
     if (e == hipSuccess) e = nb::launch_force(p, mixed, fa, ctx->stream);
     if (e == hipSuccess && timed) e = timed_end(ctx, NB_CLASS_FORCE, ev);
     if (e != hipSuccess) return hip_fail(ctx, e);

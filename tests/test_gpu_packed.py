@@ -1,0 +1,70 @@
+"""The scalar-operand row pass over the packed j-set (large blocks): lists and
+sums bit-identical to the LDS row pass with the same splits, at ragged sizes,
+and the LDS pass where the packed bodies find no room."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1504_03687_amd as nb
+import workloads as W
+from gpu_util import TOL_FP64, TOL_MIXED, compare_force, dev, host, say
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": TOL_FP64, "mixed": TOL_MIXED}
+
+
+def _defined(out, cap):
+    acc, jerk, cnt, lst, ovf = (host(t) for t in out)
+    used = np.arange(cap)[None, :] < np.minimum(cnt, cap)[:, None]
+    return acc, jerk, cnt, np.where(used, lst, -1), ovf
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,n_i,splits", [(65537, 2049, 7), (65567, 4096, 1), (140001, 1000, 0)])
+def test_packed_equals_lds_pass(n, n_i, splits, prec):
+    """n and n_i one past and one short of the runs and tiles; several splits,
+    one (direct stores), and the automatic count; duplicate rows, a bad index
+    and rows without neighbours."""
+    say(f"packed n={n} n_i={n_i} splits={splits} {prec}")
+    rng = np.random.default_rng(n)
+    s = W.small_state(300 + n_i, n, k_nn=24)
+    ib = rng.choice(n, n_i, replace=False).astype(np.int32)
+    ib[5] = ib[6]
+    rs2 = s["rs2"][ib].copy()
+    rs2[::101] = 0.0
+    ib[n_i - 1] = n          # out of range: a zero row and a status bit
+    cap = 20
+    args = (dev(s["x"]), dev(s["v"]), dev(s["m"]), dev(ib), dev(rs2), cap, prec)
+    ctx = nb.Context(0)
+    try:
+        st = [torch.zeros(1, dtype=torch.int32, device="cuda") for _ in range(3)]
+        ctx.set_plan(1, 1, splits)
+        packed = nb.regular_force(*args, status=st[0], ctx=ctx)
+        assert "bodies=packed" in ctx.last_plan(), ctx.last_plan()
+        k = int(ctx.last_plan().split("splits=")[1].split()[0])
+        ctx.set_plan(1, 2, k)    # two rows per lane: the LDS kernel
+        lds = nb.regular_force(*args, status=st[1], ctx=ctx)
+        assert "packed" not in ctx.last_plan()
+        ctx.set_plan(1, 1, k)
+        # room for the split slots and the refinement, but not for the bodies
+        ctx2 = nb.Context(0)
+        try:
+            ctx2.set_plan(1, 1, k)
+            ctx2.set_scratch_limit(64 * n - 1 if k == 1 else
+                                   k * n_i * 452 + n_i * 12 + (n // 8192 + 1) * n_i * 48 + 65536)
+            small = nb.regular_force(*args, status=st[2], ctx=ctx2)
+            plan = ctx2.last_plan()
+        finally:
+            ctx2.close()
+        torch.cuda.synchronize()
+        a, b, c = (_defined(o, cap) for o in (packed, lds, small))
+        for x, y, z in zip(a, b, c):
+            assert np.array_equal(x, y) and np.array_equal(x, z)
+        assert "packed" not in plan, plan
+        assert len({int(t.item()) for t in st}) == 1 and int(st[0].item()) & nb.STATUS_BAD_INDEX
+        assert not host(packed[0])[:, n_i - 1].any() and a[2][n_i - 1] == 0
+        rows = rng.choice(n_i - 1, 96, replace=False)
+        compare_force(packed, s["x"], s["v"], s["m"], ib, rs2, cap, TOL[prec], rows=rows)
+    finally:
+        ctx.close()
