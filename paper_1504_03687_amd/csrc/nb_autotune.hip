@@ -79,7 +79,7 @@ static int load_table(nb_ctx *ctx, const char *path, int64_t n_bucket, bool *fou
             !(rows == 1 || rows == 2 || rows == 4) || f64 < 0 || f64 > 1)
             continue;
         ctx->tuned[std::make_tuple(prec, (int64_t)nb, (int64_t)nib)] =
-            nb::Plan{mapping, rows, splits, prec == 1 ? f64 : 0};
+            nb::Plan{mapping, rows, splits, prec == 1 ? f64 : 0, 0};
         if (nb == n_bucket) *found = true;
     }
     std::fclose(f);
@@ -163,9 +163,10 @@ extern "C" int nb_autotune(nb_ctx *ctx, int64_t n, const char *cache_path, int f
                     // the automatic split count of this mapping, halved and doubled
                     const int64_t base = default_splits(ctx, n, ni, mapping, rows);
                     for (int64_t sc : {base / 2, base, base * 2}) {
-                        const int64_t maxs = max_splits(n, mapping);
+                        const int64_t maxs =
+                            max_splits(n, mapping, pack_pays(mapping, rows, n, ni));
                         const int s = (int)std::max<int64_t>(1, std::min<int64_t>(sc, maxs));
-                        nb::Plan p{mapping, rows, s, 0};
+                        nb::Plan p{mapping, rows, s, 0, fine_splits(mapping, s, n)};
                         bool dup = false;
                         for (auto &q : cands)
                             dup |= q.mapping == p.mapping && q.rows_per_lane == p.rows_per_lane &&

@@ -111,6 +111,7 @@ struct Plan {
     int rows_per_lane;  // mapping 1: 1, 2, 4;  mapping 2: rows per wave 1, 2, 4
     int splits;         // j-ranges (mapping 1: per work-group; mapping 2: per wave)
     int f64;            // 1: a mixed-precision request runs the FP64 kernels
+    int fine;           // 1 (mapping 1): splits in steps of kWave bodies, not kTile
 };
 
 // Scratch bytes needed for a plan (0 when splits == 1).

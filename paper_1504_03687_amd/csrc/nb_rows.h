@@ -387,7 +387,11 @@ __device__ __forceinline__ void rows_pass(const ForceArgs &a, JBody (*tile)[T], 
             __syncthreads();
         }
         const JBody *buf = tile[cur];
-        for (int jj = 0; jj < (wave_busy ? T : 0); jj += kFold) {
+        // whole runs of kFold up to the last body of the range (a split may
+        // be much shorter than a tile)
+        const int64_t left = (j1 - tbase + kFold - 1) & ~(int64_t)(kFold - 1);
+        const int live = !wave_busy ? 0 : (left < T ? (int)left : T);
+        for (int jj = 0; jj < live; jj += kFold) {
             for (int q = 0; q < kFold; q += 2) {
                 const int32_t jidx = (int32_t)(tbase + jj + q);
 #pragma unroll

@@ -244,7 +244,7 @@ int nb_ctx_set_plan(nb_ctx *ctx, int mapping, int rows_per_lane, int splits)
     if (mapping < 0 || mapping > 3 || splits < 0) return NB_ERR_INVALID_ARG;
     if (!(rows_per_lane == 0 || rows_per_lane == 1 || rows_per_lane == 2 || rows_per_lane == 4))
         return NB_ERR_INVALID_ARG;
-    ctx->forced = Plan{mapping, rows_per_lane, splits};
+    ctx->forced = Plan{mapping, rows_per_lane, splits, 0, 0};
     ctx->has_forced = mapping != 0 || rows_per_lane != 0 || splits != 0;
     return NB_OK;
 }
@@ -359,6 +359,7 @@ static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const do
         if (ctx->forced.mapping) p.mapping = ctx->forced.mapping;
         if (ctx->forced.rows_per_lane) p.rows_per_lane = ctx->forced.rows_per_lane;
         if (ctx->forced.splits) p.splits = ctx->forced.splits;
+        if (ctx->forced.splits || p.mapping != 1) p.fine = ctx->forced.fine;
         p.f64 = ctx->forced.f64;   // a forced plan runs the requested kernels
     }
     const bool mixed = prec == NB_MIXED && !p.f64;
@@ -409,7 +410,7 @@ static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const do
     const size_t slot_bytes = nb::force_scratch_bytes(p, n_i);
     // the packed j-set, where it pays and its memory is there: a workspace or
     // scratch limit that is too small for it runs the LDS kernels as before
-    size_t pack_bytes = pack_pays(p, n, n_i) ? nb::packed_bytes(n) : 0;
+    size_t pack_bytes = pack_pays(p.mapping, p.rows_per_lane, n, n_i) ? nb::packed_bytes(n) : 0;
     if (fixed && redo_bytes + slot_bytes + pack_bytes > fixed_bytes) pack_bytes = 0;
     if (!fixed && redo_bytes + slot_bytes + pack_bytes > 0) {
         int rc = ensure_scratch(ctx, redo_bytes + slot_bytes + pack_bytes);

@@ -1,6 +1,7 @@
-"""The scalar-operand row pass over the packed j-set (large blocks): lists and
-sums bit-identical to the LDS row pass with the same splits, at ragged sizes,
-and the LDS pass where the packed bodies find no room."""
+"""Row-per-lane plans.  The scalar-operand pass over the packed j-set (large
+blocks): lists and sums bit-identical to the LDS row pass with the same splits,
+at ragged sizes, and the LDS pass where the packed bodies find no room.  Short
+splits of small blocks: against the oracle and the unsplit launch."""
 import numpy as np
 import pytest
 import torch
@@ -66,5 +67,34 @@ def test_packed_equals_lds_pass(n, n_i, splits, prec):
         assert not host(packed[0])[:, n_i - 1].any() and a[2][n_i - 1] == 0
         rows = rng.choice(n_i - 1, 96, replace=False)
         compare_force(packed, s["x"], s["v"], s["m"], ib, rs2, cap, TOL[prec], rows=rows)
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,n_i,mapping", [(65, 64, 3), (1000, 250, 1), (1024, 1024, 1),
+                                           (4033, 300, 3), (4097, 1000, 1)])
+def test_short_splits(n, n_i, mapping, prec):
+    """Automatic plans of small blocks cut the j-set into splits of 64 bodies:
+    a part of a 256-body tile in mapping 1, a ragged last split."""
+    say(f"short splits n={n} n_i={n_i} {prec}")
+    rng = np.random.default_rng(n + 1)
+    s = W.small_state(400 + n_i, n, k_nn=20)
+    ib = rng.choice(n, n_i, replace=False).astype(np.int32)
+    rs2 = s["rs2"][ib]
+    cap = 24
+    args = (dev(s["x"]), dev(s["v"]), dev(s["m"]), dev(ib), dev(rs2), cap, prec)
+    ctx = nb.Context(0)
+    try:
+        auto = nb.regular_force(*args, ctx=ctx)
+        plan = ctx.last_plan()
+        assert f"mapping={mapping}" in plan and "split_len=64" in plan, plan
+        assert f"splits={(n + 63) // 64}" in plan, plan
+        ctx.set_plan(1, 1, 1)
+        one = nb.regular_force(*args, ctx=ctx)
+        torch.cuda.synchronize()
+        for x, y in zip(_defined(auto, cap)[2:], _defined(one, cap)[2:]):
+            assert np.array_equal(x, y)
+        compare_force(auto, s["x"], s["v"], s["m"], ib, rs2, cap, TOL[prec])
     finally:
         ctx.close()
