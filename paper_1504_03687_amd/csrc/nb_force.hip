@@ -280,41 +280,42 @@ __global__ __launch_bounds__(kBlock) void force_wave_kernel(ForceArgs a)
         }
     }
     }
-    // the wave sums of all rows' eight components in one butterfly pass
-    double r[G * 8];
+    // the wave sums of all rows: part p of the wave gets row p's, and the
+    // part's first lane stores that row
+    double r[G][8];
+    int32_t my_ri = ri[0], my_cnt = cnt[0];
+    const int part = lane / (kWave / G);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         S[g].fold();
-        r[g * 8 + 0] = S[g].ax;
-        r[g * 8 + 1] = S[g].ay;
-        r[g * 8 + 2] = S[g].az;
-        r[g * 8 + 3] = S[g].jx;
-        r[g * 8 + 4] = S[g].jy;
-        r[g * 8 + 5] = S[g].jz;
-        r[g * 8 + 6] = S[g].va;
-        r[g * 8 + 7] = S[g].vj;
-    }
-    group_sums<kWave, G * 8>(r);
-    bool ovf = false, bad = false, nonfin = false;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        Sums<MIXED> T = S[g];
-        T.ax = r[g * 8 + 0];
-        T.ay = r[g * 8 + 1];
-        T.az = r[g * 8 + 2];
-        T.jx = r[g * 8 + 3];
-        T.jy = r[g * 8 + 4];
-        T.jz = r[g * 8 + 5];
-        T.va = r[g * 8 + 6];
-        T.vj = r[g * 8 + 7];
-        const int64_t b = group * G + g;
-        if (lane == 0 && b < a.n_i) {
-            bool o = false, bd = false, f = false;
-            row_store<MIXED>(a, b, d, ri[g] >= 0, T, cnt[g], o, bd, f, j0, j1);
-            ovf |= o;
-            bad |= bd;
-            nonfin |= f;
+        r[g][0] = S[g].ax;
+        r[g][1] = S[g].ay;
+        r[g][2] = S[g].az;
+        r[g][3] = S[g].jx;
+        r[g][4] = S[g].jy;
+        r[g][5] = S[g].jz;
+        r[g][6] = S[g].va;
+        r[g][7] = S[g].vj;
+        if (g == part) {
+            my_ri = ri[g];
+            my_cnt = cnt[g];
         }
+    }
+    group_sums_spread<G, 8>(r);
+    bool ovf = false, bad = false, nonfin = false;
+    const int64_t b = group * G + part;
+    if ((lane & (kWave / G - 1)) == 0 && b < a.n_i) {
+        Sums<MIXED> T;
+        T.zero();
+        T.ax = r[0][0];
+        T.ay = r[0][1];
+        T.az = r[0][2];
+        T.jx = r[0][3];
+        T.jy = r[0][4];
+        T.jz = r[0][5];
+        T.va = r[0][6];
+        T.vj = r[0][7];
+        row_store<MIXED>(a, b, d, my_ri >= 0, T, my_cnt, ovf, bad, nonfin, j0, j1);
     }
     flush_flags(a, ovf, bad, nonfin);
 }

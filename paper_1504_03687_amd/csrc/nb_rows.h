@@ -493,22 +493,103 @@ struct MergeGeom {
     int64_t j_begin, j_end, split_len;
 };
 
+// The partner's value of a butterfly level inside a row of 16 lanes, moved by
+// DPP: quad permutes for offsets 1 and 2, row rotations for 4 and 8.  (Once
+// the levels above have run, the sums repeat every 2 * O lanes, so a rotation
+// by O reads the same sum as an exchange with lane ^ O.)
+template <int O>
+__device__ __forceinline__ double row_partner(double v)
+{
+    constexpr int ctrl = O == 1 ? 0xB1 : O == 2 ? 0x4E : 0x120 + O;
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, ctrl, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(u >> 32), ctrl, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Exchange of 32-lane halves (O = 32) or of neighbouring 16-lane rows (O = 16)
+// between two values: x becomes {x low, y low}, y {x high, y high}, where low
+// and high are the halves, or the even and the odd rows.
+template <int O>
+__device__ __forceinline__ void swap_lanes(double &x, double &y)
+{
+    const uint64_t a = __builtin_bit_cast(uint64_t, x), b = __builtin_bit_cast(uint64_t, y);
+    uint32_t r[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t p = (uint32_t)(a >> (32 * h)), q = (uint32_t)(b >> (32 * h));
+        const auto t = O == 32 ? __builtin_amdgcn_permlane32_swap(p, q, false, false)
+                               : __builtin_amdgcn_permlane16_swap(p, q, false, false);
+        r[0][h] = t[0];
+        r[1][h] = t[1];
+    }
+    x = __builtin_bit_cast(double, ((uint64_t)r[0][1] << 32) | r[0][0]);
+    y = __builtin_bit_cast(double, ((uint64_t)r[1][1] << 32) | r[1][0]);
+}
+
+template <int O, int K>
+__device__ __forceinline__ void row_levels(double (&v)[K])
+{
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] += row_partner<O>(v[k]);
+    if constexpr (O > 1) row_levels<O / 2, K>(v);
+}
+
 // Sums of K values over the W aligned lanes of a lane group (butterfly,
-// largest offset first; every lane of the group gets the results).  The
-// butterflies run level by level across the K values, so the K shuffles of a
-// level are issued together and a level waits on one cross-lane permute
-// latency instead of K (value after value, eight values took about 2 us).
-// Each value gets the pairs and order of its own butterfly.
+// largest offset first; every lane of the group gets the results).  Lanes
+// exchange through the VALU (swaps of halves and rows, DPP), not through LDS:
+// with ds_bpermute_b32 each level of a double cost two trips through the LDS
+// pipe and their latency (a 1-row block at N = 2^20 spent 2.2 us of its merge
+// in them).  Each value gets the pairs and order of its own butterfly.
 template <int W, int K>
 __device__ __forceinline__ void group_sums(double (&v)[K])
 {
+    static_assert(W == 4 || W == 16 || W == kWave, "lane group");
+    if constexpr (W == kWave) {
 #pragma unroll
-    for (int o = W / 2; o > 0; o >>= 1) {
-        double t[K];
+        for (int k = 0; k < K; ++k) {
+            double t = v[k];
+            swap_lanes<32>(v[k], t);
+            v[k] += t;
+        }
 #pragma unroll
-        for (int k = 0; k < K; ++k) t[k] = __shfl_xor(v[k], o, kWave);
+        for (int k = 0; k < K; ++k) {
+            double t = v[k];
+            swap_lanes<16>(v[k], t);
+            v[k] += t;
+        }
+    }
+    row_levels<(W == 4 ? 2 : 8), K>(v);
+}
+
+// The same sums of G groups of K values over a whole wave, handed out: the
+// lanes of part p of the wave (p = lane * G / 64) get the K sums of group p
+// in v[0][..].  The first levels halve the values with the lanes (one swap
+// serves two values), so four groups of eight cost a quarter of 32 whole
+// butterflies.  Same pairs and order per value as group_sums.
+template <int G, int K>
+__device__ __forceinline__ void group_sums_spread(double (&v)[G][K])
+{
+    static_assert(G == 1 || G == 2 || G == 4, "groups per wave");
+    if constexpr (G == 1) {
+        group_sums<kWave, K>(v[0]);
+        return;
+    } else {
 #pragma unroll
-        for (int k = 0; k < K; ++k) v[k] += t[k];
+        for (int g = 0; g < G / 2; ++g)
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                swap_lanes<32>(v[g][k], v[g + G / 2][k]);
+                v[g][k] += v[g + G / 2][k];
+            }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            double t = v[0][k];
+            if constexpr (G == 4) t = v[1][k];
+            swap_lanes<16>(v[0][k], t);
+            v[0][k] += t;
+        }
+        row_levels<8, K>(v[0]);
     }
 }
 
