@@ -361,8 +361,17 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     const int32_t groups = nb::redo_groups_for(ctx->cu_count);
     int64_t max_len = 1;
     for (int32_t k = 0; k < C; ++k) max_len = std::max<int64_t>(max_len, c->j_off[k + 1] - c->j_off[k]);
-    const size_t b_redo = c->redo_k > 0.0 ? nb::redo_scratch_bytes(f.n_i, max_len) : 0;
-    const size_t total = b_queue + b_cl + 2 * b_mr + b_it + b_slots + b_redo + (c->packed ? b_rec : 0);
+    const size_t b_other = b_queue + b_cl + 2 * b_mr + b_it + b_slots + (c->packed ? b_rec : 0);
+    // under a scratch limit the refinement buffers fewer rows
+    int32_t rcap_limit = 0;
+    size_t b_redo = c->redo_k > 0.0 ? nb::redo_scratch_bytes(f.n_i, max_len) : 0;
+    for (int32_t rows = f.n_i; ctx->scratch_limit && b_redo && b_other + b_redo > ctx->scratch_limit &&
+                               rows > 1;) {
+        rows /= 2;
+        rcap_limit = rows;
+        b_redo = nb::redo_scratch_bytes(f.n_i, max_len, rcap_limit);
+    }
+    const size_t total = b_other + b_redo;
     if (ctx->scratch_limit && total > ctx->scratch_limit) return NB_ERR_OOM;
     hipError_t e = hipMalloc(&c->dmem, total);
     if (e != hipSuccess) {
@@ -406,7 +415,7 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     A.f.redo_k = c->redo_k;
     // the refinement counter sits in the queue's 256-byte block, away from the
     // work counter's word
-    if (c->redo_k > 0.0) nb::bind_redo_scratch(A.f, dredo, queue + 32, groups, max_len);
+    if (c->redo_k > 0.0) nb::bind_redo_scratch(A.f, dredo, queue + 32, groups, max_len, rcap_limit);
     A.f.splits = 0;          // per-cluster
     A.f.split_len = 0;
     A.f.packed = c->packed ? drec : nullptr;
@@ -444,7 +453,7 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
         if (le == hipSuccess) le = nb::launch_batched(mixed, c->shape, c->packed, c->grid, A, cs);
         if (le == hipSuccess) le = nb::launch_batched_merge(A, cs);
         if (le == hipSuccess && c->redo_k > 0.0)
-            le = nb::launch_redo(A.f, cs);
+            le = nb::launch_redo(A.f, false, cs);
         e = hipStreamEndCapture(cs, &c->graph);
         if (e == hipSuccess) e = le;
     }

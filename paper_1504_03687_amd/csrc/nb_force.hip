@@ -352,123 +352,131 @@ __device__ __forceinline__ void write_forces(const ForceArgs &a, int64_t b, cons
     a.jerk[2 * (int64_t)a.n_i + b] = v[5];
 }
 
-// Final sums of the buffered rows: six lanes per row, a lane per force
-// component, each adding the row's chunk partials of its component in chunk
-// order (kFinalBatch of them loaded before any is added).  Starting from zero
-// in chunk order, this is the sum of the unbuffered route.  slot / slots: this
-// lane's row slot and the number of slots (rows q = slot, slot + slots, ...).
-constexpr int kFinalBatch = 32;
-constexpr int kFinalRowsPerGroup = kBlock / 6;
-
+// Final sums of the buffered rows, a wave per row: lane l adds the chunk
+// partials l, l + 64, ... in order, then the wave's butterfly (the sum that the
+// unbuffered route forms).  slot / slots: this wave's row slot and the number
+// of slots (rows q = slot, slot + slots, ...).
 __device__ __forceinline__ void redo_final_rows(const ForceArgs &a, int32_t par, int32_t slot,
                                                 int32_t slots)
 {
-    const int k = (int)(threadIdx.x % 6);
-    if (threadIdx.x >= kFinalRowsPerGroup * 6) return;
+    const int lane = threadIdx.x & (kWave - 1);
     for (int32_t q = slot; q < par; q += slots) {
         const int32_t nc = redo_row_chunks(a, q);
-        const int64_t row = a.redo_rows[q];
-        const double *p = a.redo_part + (int64_t)q * a.redo_chunks * 6 + k;
-        double s = 0.0;
-        for (int32_t c0 = 0; c0 < nc; c0 += kFinalBatch) {
-            double t[kFinalBatch];
+        const double2 *p = reinterpret_cast<const double2 *>(
+            a.redo_part + (int64_t)q * a.redo_chunks * 6);
+        double v[6] = {0, 0, 0, 0, 0, 0};
+        for (int32_t c = lane; c < nc; c += kWave)
 #pragma unroll
-            for (int u = 0; u < kFinalBatch; ++u) t[u] = c0 + u < nc ? p[(int64_t)(c0 + u) * 6] : 0.0;
-#pragma unroll
-            for (int u = 0; u < kFinalBatch; ++u)
-                if (c0 + u < nc) s += t[u];
-        }
-        double *dst = k < 3 ? a.acc + (int64_t)k * a.n_i : a.jerk + (int64_t)(k - 3) * a.n_i;
-        dst[row] = s;
+            for (int k = 0; k < 3; ++k) {
+                const double2 t = p[(int64_t)c * 3 + k];
+                v[2 * k] += t.x;
+                v[2 * k + 1] += t.y;
+            }
+        group_sums<kWave, 6>(v);
+        if (lane == 0) write_forces(a, load_word_uniform(a.redo_rows + q), v);
     }
+}
+
+// How many of the listed rows go through chunk partials: those that fit the
+// buffer, but in a batched call (R = 1) none where every work-group has rows
+// of its own to do: an item then is a row with its data loaded once, and no
+// chunk number past a short row's range is looked at (the listed rows of 96
+// clusters: 322 us as chunk items, 243 us as rows).
+template <int R>
+__device__ __forceinline__ int32_t redo_buffered(const ForceArgs &a, int32_t count)
+{
+    if (R == 1 && count >= a.redo_groups) return 0;
+    return count < a.redo_rcap ? count : a.redo_rcap;
 }
 
 // Refinement of the listed rows.  Pass 1: the first redo_rcap listed rows as
 // (row group, chunk) items over the whole grid (chunk partials to scratch);
-// any further rows one work-group each, chunks in order.  Pass 2 adds each
-// buffered row's chunk partials in chunk order and overwrites its forces:
-// with FUSED, the work-group that finishes pass 1 last does it (one launch,
-// for calls that can list few rows); otherwise redo_final_kernel, launched
-// next, spreads it over the GPU.  Both routes give the same chunk-ordered
-// sum.  A group is kRedoRows consecutive listed rows: when they share one
-// j-range (always in a single-block call) they are summed together, each body
-// loaded once; otherwise row by row.  Chunks past a row's own range are
-// skipped.  With no listed row every work-group leaves at once (no fence, no
-// atomic), which is the common case of small blocks.
-template <bool FUSED>
+// any further rows one work-group each, chunk after chunk.  Pass 2 adds each
+// buffered row's chunk partials and overwrites its forces: with FUSED, the
+// work-group that finishes pass 1 last does it (one launch, for calls that can
+// list few rows); otherwise redo_final_kernel, launched next, spreads it over
+// the GPU.  Both routes give the same sum.  A group is R consecutive listed
+// rows, which must share one j-range if R > 1 (single-block calls, R =
+// kRedoRows: each body loaded once for all); a batched call's rows (R = 1) are
+// items of their own, chunks past a row's range skipped.  Work-groups without
+// an item leave at once: no fence, no atomic, and the arrival counts only the
+// others (counting all of 1024 in took 20 us of a call that refined ten rows).
+template <bool FUSED, int R>
 __global__ __launch_bounds__(kBlock) void redo_kernel(ForceArgs a)
 {
-    __shared__ double lds[kRedoRows * 6][kBlock / kWave];
+    __shared__ double lds[2][R][6][kBlock / kWave];
     __shared__ int32_t last;
+    int buf = 0;
     const int32_t count = load_word_uniform(a.redo_count);
     if (count == 0) return;
-    const int32_t par = count < a.redo_rcap ? count : a.redo_rcap;
+    const int32_t par = redo_buffered<R>(a, count);
     const int32_t C = a.redo_chunks;
-    const int32_t G = (par + kRedoRows - 1) / kRedoRows;
+    const int32_t G = (par + R - 1) / R;
     const int64_t items = (int64_t)G * C;
-    double v[kRedoRows * 6], v1[6];
+    const int64_t most = items > (int64_t)count - par ? items : (int64_t)count - par;
+    const int32_t busy = most < gridDim.x ? (int32_t)most : (int32_t)gridDim.x;
+    if ((int32_t)blockIdx.x >= busy) return;
+    const int tid = threadIdx.x;
     // chunk-major order: work-groups running at the same time share a chunk
     // of bodies (L2 reuse across the refined rows)
     for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
-        const int32_t c = (int32_t)(it / G), q0 = (int32_t)(it % G) * kRedoRows;
-        const int nr = par - q0 < kRedoRows ? par - q0 : kRedoRows;
-        bool same = true;   // uniform over the work-group
-        for (int r = 1; r < nr; ++r)
-            same = same && a.redo_j0[q0 + r] == a.redo_j0[q0] && a.redo_j1[q0 + r] == a.redo_j1[q0];
-        if (same) {
-            if (c >= redo_row_chunks(a, q0)) continue;
-            redo_chunk_rows(a, q0, nr, c, lds, v);
-            if (threadIdx.x == 0)
-                for (int r = 0; r < nr; ++r)
-#pragma unroll
-                    for (int k = 0; k < 6; ++k)
-                        a.redo_part[((int64_t)(q0 + r) * C + c) * 6 + k] = v[r * 6 + k];
-        } else {
-            for (int r = 0; r < nr; ++r) {
-                const int32_t q = q0 + r;
-                if (c >= redo_row_chunks(a, q)) continue;
-                redo_chunk(a, q, c, lds, v1);
-                if (threadIdx.x == 0)
-#pragma unroll
-                    for (int k = 0; k < 6; ++k) a.redo_part[((int64_t)q * C + c) * 6 + k] = v1[k];
-            }
+        const int32_t c = (int32_t)(it / G), q0 = (int32_t)(it % G) * R;
+        const int nr = par - q0 < R ? par - q0 : R;
+        if (c >= redo_row_chunks(a, q0)) continue;
+        RedoRows<R> Q;
+        Q.load(a, q0, nr);
+        redo_chunk_rows<R>(a, Q, c, lds[buf]);
+        if (tid < nr * 6) {
+            const int r = tid / 6, k = tid % 6;
+            a.redo_part[((int64_t)(q0 + r) * C + c) * 6 + k] = redo_chunk_sum(lds[buf][r][k]);
         }
+        buf ^= 1;
     }
     for (int64_t q = (int64_t)par + blockIdx.x; q < count; q += gridDim.x) {
-        double acc[6] = {0, 0, 0, 0, 0, 0};
+        double v[6] = {0, 0, 0, 0, 0, 0};
         const int32_t nc = redo_row_chunks(a, (int32_t)q);
+        RedoRows<R> Q;
+        Q.load(a, (int32_t)q, 1);
         for (int32_t c = 0; c < nc; ++c) {
-            redo_chunk(a, (int32_t)q, c, lds, v1);
+            redo_chunk_rows<R>(a, Q, c, lds[buf]);
+            if (tid == (c & (kWave - 1)))
 #pragma unroll
-            for (int k = 0; k < 6; ++k) acc[k] += v1[k];
+                for (int k = 0; k < 6; ++k) v[k] += redo_chunk_sum(lds[buf][0][k]);
+            buf ^= 1;
         }
-        if (threadIdx.x == 0) write_forces(a, a.redo_rows[q], acc);
+        if (tid < kWave) {   // one whole wave
+            group_sums<kWave, 6>(v);
+            if (tid == 0) write_forces(a, a.redo_rows[q], v);
+        }
     }
     if (!FUSED || par == 0) return;   // par == 0: nothing buffered (uniform over the grid)
 
-    // arrival: the chunk partials were written by lane 0, which publishes
-    // them device-wide before it counts this work-group in
+    // arrival: the chunk partials were written by the first lanes of wave 0,
+    // whose lane 0 publishes them device-wide before it counts this
+    // work-group in
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         __threadfence();
-        last = atomicAdd(a.redo_arrive, 1) == (int32_t)gridDim.x - 1;
+        last = atomicAdd(a.redo_arrive, 1) == busy - 1;
     }
     __syncthreads();
     if (!last) return;
     __threadfence();   // every work-group's partials are visible from here
-    if (threadIdx.x == 0) *a.redo_arrive = 0;   // every work-group has arrived
-    redo_final_rows(a, par, (int32_t)(threadIdx.x / 6), kFinalRowsPerGroup);
+    if (tid == 0) *a.redo_arrive = 0;   // every work-group has arrived
+    redo_final_rows(a, par, (int32_t)__builtin_amdgcn_readfirstlane(tid / kWave), kBlock / kWave);
 }
 
 // Pass 2 of the refinement as a launch of its own, spread over the grid: for
 // calls that can list many rows, where one work-group adding them all would
 // take longer than the rest of the refinement.
+template <int R>
 __global__ __launch_bounds__(kBlock) void redo_final_kernel(ForceArgs a)
 {
-    const int32_t count = load_word_uniform(a.redo_count);
-    const int32_t par = count < a.redo_rcap ? count : a.redo_rcap;
-    redo_final_rows(a, par, (int32_t)(blockIdx.x * kFinalRowsPerGroup + threadIdx.x / 6),
-                    (int32_t)(gridDim.x * kFinalRowsPerGroup));
+    const int32_t par = redo_buffered<R>(a, load_word_uniform(a.redo_count));
+    redo_final_rows(a, par,
+                    (int32_t)(blockIdx.x * (kBlock / kWave) +
+                              __builtin_amdgcn_readfirstlane(threadIdx.x / kWave)),
+                    (int32_t)(gridDim.x * (kBlock / kWave)));
 }
 
 __global__ void fill_i32_kernel(int32_t *p, int32_t value, int64_t count)
@@ -500,13 +508,15 @@ size_t slot_scratch_bytes(int64_t slots)
 }
 
 // Calls that can buffer at most this many refined rows add them up in the
-// work-group that finishes pass 1 last (42 rows at a time); larger ones
-// launch redo_final_kernel.  The 256-cluster ensemble
-// (about 1.2e4 buffered rows) took 0.25 ms longer per call with one
-// work-group adding them all.
+// work-group that finishes pass 1 last (a row per wave); larger ones launch
+// redo_final_kernel.  The 256-cluster ensemble (about 1.2e4 buffered rows)
+// took 0.25 ms longer per call with one work-group adding them all.
 constexpr int64_t kFusedRedoRows = 1024;
 
-int32_t redo_groups_for(int cu_count) { return (cu_count > 0 ? cu_count : 256) * 4; }
+// Eight work-groups per CU, more than are resident, so that short and long
+// items even out: 1500 rows of 2^20 bodies 3.83 ms against 4.04 with four, the
+// rows of 96 clusters 243 us against 265.
+int32_t redo_groups_for(int cu_count) { return (cu_count > 0 ? cu_count : 256) * 8; }
 
 static int32_t redo_chunks_for(int64_t max_len)
 {
@@ -548,23 +558,30 @@ void bind_redo_scratch(ForceArgs &a, void *base, int32_t *counter, int32_t group
     a.redo_rcap = redo_rcap_for(a.n_i, a.redo_chunks, rcap_limit);
 }
 
-hipError_t launch_redo(const ForceArgs &a, hipStream_t s)
+template <int R>
+static hipError_t launch_redo_t(const ForceArgs &a, hipStream_t s)
 {
     // no more work-groups than the most items a call of n_i rows can list
     const int64_t rows = std::max<int64_t>(a.n_i, 1);
     const int64_t par = std::min<int64_t>(rows, a.redo_rcap);
-    const int64_t items = (par + kRedoRows - 1) / kRedoRows * a.redo_chunks + (rows - par);
+    const int64_t items = std::max((par + R - 1) / R * a.redo_chunks, rows - par);
     const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(a.redo_groups, items));
     if (par <= kFusedRedoRows) {
-        hipLaunchKernelGGL(redo_kernel<true>, dim3((unsigned)grid), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL((redo_kernel<true, R>), dim3((unsigned)grid), dim3(kBlock), 0, s, a);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(redo_kernel<false>, dim3((unsigned)grid), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL((redo_kernel<false, R>), dim3((unsigned)grid), dim3(kBlock), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t fgrid = std::min<int64_t>(a.redo_groups, (par + kFinalRowsPerGroup - 1) / kFinalRowsPerGroup);
-    hipLaunchKernelGGL(redo_final_kernel, dim3((unsigned)fgrid), dim3(kBlock), 0, s, a);
+    constexpr int64_t per = kBlock / kWave;   // a wave per row
+    const int64_t fgrid = std::min<int64_t>(a.redo_groups, (par + per - 1) / per);
+    hipLaunchKernelGGL(redo_final_kernel<R>, dim3((unsigned)fgrid), dim3(kBlock), 0, s, a);
     return hipGetLastError();
+}
+
+hipError_t launch_redo(const ForceArgs &a, bool one_range, hipStream_t s)
+{
+    return one_range ? launch_redo_t<kRedoRows>(a, s) : launch_redo_t<1>(a, s);
 }
 
 void bind_slot_scratch(ForceArgs &a, int64_t slots, void *base)

@@ -89,7 +89,8 @@ struct ForceArgs {
 
 // Refinement works on fixed chunks of kRedoChunk bodies so that a refined
 // row's FP64 sum does not depend on how many rows were refined in the call.
-constexpr int64_t kRedoChunk = 8192;
+constexpr int64_t kRedoChunk = 2048;
+constexpr int kRedoRows = 2;   // refined rows of one j-range summed together
 constexpr int64_t kRedoPartItems = int64_t(1) << 20;   // chunk partials held at most
 
 // Components per slot: acc x,y,z, jerk x,y,z, and the two error-scale sums.
@@ -104,7 +105,8 @@ int32_t redo_groups_for(int cu_count);
 size_t redo_scratch_bytes(int32_t n_i, int64_t max_len, int32_t rcap_limit = 0);
 void bind_redo_scratch(ForceArgs &a, void *base, int32_t *counter, int32_t groups,
                        int64_t max_len, int32_t rcap_limit = 0);
-hipError_t launch_redo(const ForceArgs &a, hipStream_t s);
+// one_range: every row of the launch has the same j-range (single-block calls).
+hipError_t launch_redo(const ForceArgs &a, bool one_range, hipStream_t s);
 
 struct Plan {
     int mapping;        // 1 = row per lane (LDS j-tiles), 2 = row group per wave

@@ -766,139 +766,117 @@ __device__ __forceinline__ void merge_row(const ForceArgs &a, int64_t b, bool ha
     flush_flags(a, ovf, bad && l == 0, nonfin);
 }
 
-// Fixed-order sums of K values over the 256 lanes of a work-group (all lanes
-// must call it): each value is summed over its wave by a butterfly, then the
-// four wave sums are added in wave order; every lane gets the results.
-template <int K>
-__device__ __forceinline__ void block_sums(double (&v)[K], double (*lds)[kBlock / kWave])
-{
-    group_sums<kWave, K>(v);
-    const int w = threadIdx.x / kWave;
-    __syncthreads();   // earlier readers of lds are done
-    if ((threadIdx.x & (kWave - 1)) == 0)
-#pragma unroll
-        for (int k = 0; k < K; ++k) lds[k][w] = v[k];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        double t = 0.0;
-#pragma unroll
-        for (int q = 0; q < kBlock / kWave; ++q) t += lds[k][q];
-        v[k] = t;
-    }
-}
-
 // Chunks of refined row q: its j-range cut into kRedoChunk bodies.
 __device__ __forceinline__ int32_t redo_row_chunks(const ForceArgs &a, int32_t q)
 {
-    const int64_t len = (int64_t)a.redo_j1[q] - a.redo_j0[q];
+    const int64_t len = (int64_t)load_word_uniform(a.redo_j1 + q) -
+                        (int64_t)load_word_uniform(a.redo_j0 + q);
     return len > 0 ? (int32_t)((len + kRedoChunk - 1) / kRedoChunk) : 0;
 }
 
-// FP64 sums over chunk c [j0 + c*kRedoChunk, ...) of refined row q, by a whole
-// work-group in a fixed pattern; every lane gets the six sums (acc, jerk).
-// The chunk must lie inside the row's j-range (c < redo_row_chunks).
-__device__ __forceinline__ void redo_chunk(const ForceArgs &a, int32_t q, int32_t c,
-                                          double (*lds)[kBlock / kWave], double (&out)[6])
-{
-    // q is uniform: the row's data go to scalar registers
-    const int64_t b = load_word_uniform(a.redo_rows + q);
-    const int64_t j0 = load_word_uniform(a.redo_j0 + q), j1 = load_word_uniform(a.redo_j1 + q);
-    const int64_t cj0 = j0 + (int64_t)c * kRedoChunk;
-    const int64_t cj1 = cj0 + kRedoChunk < j1 ? cj0 + kRedoChunk : j1;
-    const int64_t i = load_word_uniform(a.i_block + b);
-    const double xi = load_f64_uniform(a.xp + i), yi = load_f64_uniform(a.xp + a.n + i),
-                 zi = load_f64_uniform(a.xp + 2 * a.n + i);
-    const double vxi = load_f64_uniform(a.vp + i), vyi = load_f64_uniform(a.vp + a.n + i),
-                 vzi = load_f64_uniform(a.vp + 2 * a.n + i);
-    const float rs2f = (float)load_f64_uniform(a.rs2 + b);
-    const double hi = cand_bound_f64(rs2f);
-    Sums<false> S;
-    S.zero();
-    for (int64_t j = cj0 + threadIdx.x; j < cj1; j += kBlock) {
-        JBody J;
-        load_body(J, a, j, cj1);
-        const double dx = J.x - xi, dy = J.y - yi, dz = J.z - zi;
-        double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-        if (r2 < hi) {
-            double ex = dx, ey = dy, ez = dz;
-            opaque(ex, ey, ez);
-            if (j == i || canon_r2f(ex, ey, ez) < rs2f) r2 = kExclR2;
+// The data of refined rows q0 .. q0+nr-1 (nr <= R), uniform over the
+// work-group: scalar registers.
+template <int R>
+struct RedoRows {
+    double x[R], y[R], z[R], vx[R], vy[R], vz[R], hi[R];
+    float rs2f[R];
+    int64_t i[R];
+    int64_t j0, j1;   // j-range of row q0
+    int nr;
+    __device__ __forceinline__ void load(const ForceArgs &a, int32_t q0, int n_rows)
+    {
+        nr = n_rows;
+        j0 = load_word_uniform(a.redo_j0 + q0);
+        j1 = load_word_uniform(a.redo_j1 + q0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int32_t q = q0 + (r < nr ? r : 0);
+            const int64_t b = load_word_uniform(a.redo_rows + q);
+            const int64_t k = load_word_uniform(a.i_block + b);
+            i[r] = k;
+            x[r] = load_f64_uniform(a.xp + k);
+            y[r] = load_f64_uniform(a.xp + a.n + k);
+            z[r] = load_f64_uniform(a.xp + 2 * a.n + k);
+            vx[r] = load_f64_uniform(a.vp + k);
+            vy[r] = load_f64_uniform(a.vp + a.n + k);
+            vz[r] = load_f64_uniform(a.vp + 2 * a.n + k);
+            rs2f[r] = (float)load_f64_uniform(a.rs2 + b);
+            hi[r] = cand_bound_f64(rs2f[r]);
         }
-        accum_f64(S, dx, dy, dz, r2, J.vx - vxi, J.vy - vyi, J.vz - vzi, J.m);
     }
-    S.fold();
-    out[0] = S.ax;
-    out[1] = S.ay;
-    out[2] = S.az;
-    out[3] = S.jx;
-    out[4] = S.jy;
-    out[5] = S.jz;
-    block_sums<6>(out, lds);
+};
+
+// FP64 wave sums over chunk c (c < the chunk count) of rows that share one
+// j-range, by a whole work-group: lds[r][k][w] gets component k (acc, jerk) of
+// row r over the bodies of wave w.  A lane takes bodies kBlock apart,
+// kRedoBatch of them loaded before any is used (a refined row is a chain of
+// memory round trips: one body at a time, an 8192-body chunk took 20 us for 2
+// us of arithmetic; four at a time or four rows cost a wave of occupancy and
+// gave 4.9 and 4.0 ms on 1500 rows of 2^20 bodies against 4.0), and every
+// body serves all rows.  Per row the lane order
+// and the reductions do not depend on R or nr, so a row gets the same bits in
+// any group.  Ends with the work-group synchronised; the caller alternates
+// between two lds buffers, so one barrier per chunk is enough.
+constexpr int kRedoBatch = 2;
+static_assert(kRedoChunk % (kBlock * kRedoBatch) == 0, "whole batches per chunk");
+
+template <int R>
+__device__ __forceinline__ void redo_chunk_rows(const ForceArgs &a, const RedoRows<R> &Q,
+                                               int32_t c, double (*lds)[6][kBlock / kWave])
+{
+    const int64_t cj0 = Q.j0 + (int64_t)c * kRedoChunk;
+    const int64_t cj1 = cj0 + kRedoChunk < Q.j1 ? cj0 + kRedoChunk : Q.j1;
+    Sums<false> S[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) S[r].zero();
+    for (int64_t jb = cj0 + threadIdx.x; jb - threadIdx.x < cj1; jb += kBlock * kRedoBatch) {
+        JBody J[kRedoBatch];
+#pragma unroll
+        for (int u = 0; u < kRedoBatch; ++u) load_body(J[u], a, jb + u * kBlock, cj1);
+#pragma unroll
+        for (int u = 0; u < kRedoBatch; ++u) {
+            const int64_t j = jb + u * kBlock;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (r >= Q.nr) break;
+                const double dx = J[u].x - Q.x[r], dy = J[u].y - Q.y[r], dz = J[u].z - Q.z[r];
+                double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+                if (r2 < Q.hi[r]) {
+                    double ex = dx, ey = dy, ez = dz;
+                    opaque(ex, ey, ez);
+                    if (j == Q.i[r] || canon_r2f(ex, ey, ez) < Q.rs2f[r]) r2 = kExclR2;
+                }
+                accum_f64(S[r], dx, dy, dz, r2, J[u].vx - Q.vx[r], J[u].vy - Q.vy[r],
+                          J[u].vz - Q.vz[r], J[u].m);
+            }
+        }
+    }
+    double v[R][6];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        S[r].fold();
+        v[r][0] = S[r].ax;
+        v[r][1] = S[r].ay;
+        v[r][2] = S[r].az;
+        v[r][3] = S[r].jx;
+        v[r][4] = S[r].jy;
+        v[r][5] = S[r].jz;
+    }
+    group_sums_spread<R, 6>(v);
+    const int lane = threadIdx.x & (kWave - 1);
+    if ((lane & (kWave / R - 1)) == 0)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) lds[lane / (kWave / R)][k][threadIdx.x / kWave] = v[0][k];
+    __syncthreads();
 }
 
-// Refined rows sharing one j-range are summed kRedoRows at a time: each lane
-// loads a body once for all of them.  Per row the lane order and the
-// reduction are those of redo_chunk, so every row gets the same bits.
-constexpr int kRedoRows = 2;
-
-// Chunk c of refined rows q0 .. q0+nr-1 (nr <= kRedoRows), which all have
-// the j-range of row q0 and c < its chunk count; out[r][k] for row q0 + r.
-__device__ __forceinline__ void redo_chunk_rows(const ForceArgs &a, int32_t q0, int nr, int32_t c,
-                                               double (*lds)[kBlock / kWave],
-                                               double (&out)[kRedoRows * 6])
+// A chunk's sum of one component: its wave sums in wave order.
+__device__ __forceinline__ double redo_chunk_sum(const double (&w)[kBlock / kWave])
 {
-    const int64_t j0 = load_word_uniform(a.redo_j0 + q0), j1 = load_word_uniform(a.redo_j1 + q0);
-    const int64_t cj0 = j0 + (int64_t)c * kRedoChunk;
-    const int64_t cj1 = cj0 + kRedoChunk < j1 ? cj0 + kRedoChunk : j1;
-    double xi[kRedoRows], yi[kRedoRows], zi[kRedoRows], vxi[kRedoRows], vyi[kRedoRows],
-        vzi[kRedoRows], hi[kRedoRows];
-    float rs2f[kRedoRows];
-    int64_t ii[kRedoRows];
-    Sums<false> S[kRedoRows];
+    double t = 0.0;
 #pragma unroll
-    for (int r = 0; r < kRedoRows; ++r) {
-        S[r].zero();
-        const int32_t q = q0 + (r < nr ? r : 0);   // uniform: scalar registers
-        const int64_t b = load_word_uniform(a.redo_rows + q);
-        const int64_t i = load_word_uniform(a.i_block + b);
-        ii[r] = i;
-        xi[r] = load_f64_uniform(a.xp + i);
-        yi[r] = load_f64_uniform(a.xp + a.n + i);
-        zi[r] = load_f64_uniform(a.xp + 2 * a.n + i);
-        vxi[r] = load_f64_uniform(a.vp + i);
-        vyi[r] = load_f64_uniform(a.vp + a.n + i);
-        vzi[r] = load_f64_uniform(a.vp + 2 * a.n + i);
-        rs2f[r] = (float)load_f64_uniform(a.rs2 + b);
-        hi[r] = cand_bound_f64(rs2f[r]);
-    }
-    for (int64_t j = cj0 + threadIdx.x; j < cj1; j += kBlock) {
-        JBody J;
-        load_body(J, a, j, cj1);
-#pragma unroll
-        for (int r = 0; r < kRedoRows; ++r) {
-            if (r >= nr) break;
-            const double dx = J.x - xi[r], dy = J.y - yi[r], dz = J.z - zi[r];
-            double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-            if (r2 < hi[r]) {
-                double ex = dx, ey = dy, ez = dz;
-                opaque(ex, ey, ez);
-                if (j == ii[r] || canon_r2f(ex, ey, ez) < rs2f[r]) r2 = kExclR2;
-            }
-            accum_f64(S[r], dx, dy, dz, r2, J.vx - vxi[r], J.vy - vyi[r], J.vz - vzi[r], J.m);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < kRedoRows; ++r) {
-        S[r].fold();
-        out[r * 6 + 0] = S[r].ax;
-        out[r * 6 + 1] = S[r].ay;
-        out[r * 6 + 2] = S[r].az;
-        out[r * 6 + 3] = S[r].jx;
-        out[r * 6 + 4] = S[r].jy;
-        out[r * 6 + 5] = S[r].jz;
-    }
-    block_sums<kRedoRows * 6>(out, lds);
+    for (int q = 0; q < kBlock / kWave; ++q) t += w[q];
+    return t;
 }
 
 constexpr int kMergeBatch = 8;    // strides of split partials loaded per batch

@@ -408,6 +408,15 @@ static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const do
     fa.splits = p.splits;
     fa.split_len = split_len;
     const size_t slot_bytes = nb::force_scratch_bytes(p, n_i);
+    // under a scratch limit the refinement's chunk partials shrink as well
+    if (!fixed && ctx->scratch_limit) {
+        int32_t rows = rcap_limit > 0 ? std::min(rcap_limit, n_i) : n_i;
+        while (redo_bytes && redo_bytes + slot_bytes > ctx->scratch_limit && rows > 1) {
+            rows /= 2;
+            rcap_limit = rows;
+            redo_bytes = nb::redo_scratch_bytes(n_i, n, rcap_limit);
+        }
+    }
     // the packed j-set, where it pays and its memory is there: a workspace or
     // scratch limit that is too small for it runs the LDS kernels as before
     size_t pack_bytes = pack_pays(p.mapping, p.rows_per_lane, n, n_i) ? nb::packed_bytes(n) : 0;
@@ -460,7 +469,7 @@ static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const do
     }
     if (redo_bytes) {
         if (timed) e = timed_begin(ctx, NB_CLASS_REDO, ev);
-        if (e == hipSuccess) e = nb::launch_redo(fa, ctx->stream);
+        if (e == hipSuccess) e = nb::launch_redo(fa, true, ctx->stream);
         if (e == hipSuccess && timed) e = timed_end(ctx, NB_CLASS_REDO, ev);
         if (e != hipSuccess) return hip_fail(ctx, e);
         ctx->last_redo_counter = fa.redo_count;
