@@ -236,6 +236,162 @@ __global__ __launch_bounds__(kBlock) void potential_kernel(int64_t n, const doub
     if (i < n) out[(int64_t)split * n + i] = phi;
 }
 
+// The same sums with every pair of bodies evaluated once for both of them
+// (the plain kernel above spends 64 SIMD cycles on each direction, 16 of them
+// in v_rsq_f64).  Bodies are cut into blocks of 64 R W; a work-group of W
+// waves takes one pair of blocks (p, q), p <= q.  Each lane holds R bodies of
+// p in registers; block q passes through LDS in chunks, and at step s lane l
+// meets body l ^ s of a 64-body tile, so the lanes of a wave work on 64
+// different bodies and add their shares for them into the wave's own LDS sums
+// without conflict, in a fixed order.  The shares of the R bodies are added in
+// registers first: R = 4 needs one LDS atomic and two 16-byte reads for 256
+// pairs, about half of the LDS time that the VALU work leaves.
+// Item (p, q) writes what p's bodies get from q to A[q - s0][i] and what q's
+// get from p to B[p][j - b0] (the waves' sums in wave order); a diagonal item
+// only the former, over all its ordered pairs.  A later launch adds a body's
+// entries in block order, so results are deterministic.  FP64 VALU bound:
+// n = 131072 7.31 -> 3.94 ms, 2^20 473 -> 257 ms.
+struct PotPairs {
+    int64_t n;
+    const double *x, *m;
+    int32_t s0;             // first q of this panel of blocks
+    double *A;              // [panel blocks][n]
+    double *B;              // [blocks up to the panel's end][b_stride]
+    int64_t b_stride, b0;   // columns of B: bodies b0 ...
+};
+
+template <int R, int W>
+__global__ __launch_bounds__(kWave * W) void potential_pairs_kernel(PotPairs a)
+{
+    constexpr int BL = kWave * R * W;
+    constexpr int JC = BL < 256 ? BL : 256;   // bodies of q staged at a time
+    __shared__ PBody tile[JC];
+    __shared__ double jsum[W][JC];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+    // item k of the triangle: q(q+1)/2 + p
+    const int64_t k = (int64_t)blockIdx.x + (int64_t)a.s0 * (a.s0 + 1) / 2;
+    int64_t q = (int64_t)((__builtin_sqrt(8.0 * (double)k + 1.0) - 1.0) * 0.5);
+    while (q * (q + 1) / 2 > k) --q;
+    while ((q + 1) * (q + 2) / 2 <= k) ++q;
+    const int64_t p = k - q * (q + 1) / 2;
+    const bool diag = p == q;
+
+    double xi[R], yi[R], zi[R], mi[R], phi[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = p * BL + (w * R + r) * kWave + lane;
+        const bool live = i < a.n;
+        xi[r] = live ? a.x[i] : kFar * 0.5;
+        yi[r] = live ? a.x[a.n + i] : kFar * 0.5;
+        zi[r] = live ? a.x[2 * a.n + i] : kFar * 0.5;
+        mi[r] = live ? -0.5 * a.m[i] : 0.0;
+        phi[r] = 0.0;
+    }
+    for (int c = 0; c < BL / JC; ++c) {
+        const int64_t jc = q * BL + c * JC;
+        if (c > 0) __syncthreads();   // the last chunk's sums are read
+        for (int e = tid; e < JC; e += kWave * W) {
+            const int64_t j = jc + e;
+            const bool live = j < a.n;
+            PBody b;
+            b.x = live ? a.x[j] : kFar;
+            b.y = live ? a.x[a.n + j] : kFar;
+            b.z = live ? a.x[2 * a.n + j] : kFar;
+            b.m = live ? -0.5 * a.m[j] : 0.0;
+            tile[e] = b;
+        }
+        for (int e = lane; e < JC; e += kWave) jsum[w][e] = 0.0;
+        __syncthreads();
+        for (int t = 0; t < JC; t += kWave) {
+            // r^-1 by one Newton step, as rsqrt_newton_f64, with its factor
+            // one half in the masses: 2 / |r| = y (3 - r^2 y^2)
+            if (!diag) {
+#pragma unroll 2
+                for (int s = 0; s < kWave; ++s) {
+                    const int e = t + (lane ^ s);
+                    const PBody J = tile[e];
+                    double sj = 0.0;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const double dx = J.x - xi[r], dy = J.y - yi[r], dz = J.z - zi[r];
+                        const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+                        const double y = __builtin_amdgcn_rsq(r2);
+                        const double u = y * __builtin_fma(-(r2 * y), y, 3.0);
+                        phi[r] = __builtin_fma(J.m, u, phi[r]);
+                        sj = __builtin_fma(mi[r], u, sj);
+                    }
+                    __hip_atomic_fetch_add(&jsum[w][e], sj, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            } else {
+                for (int s = 0; s < kWave; ++s) {
+                    const int e = t + (lane ^ s);
+                    const PBody J = tile[e];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const double dx = J.x - xi[r], dy = J.y - yi[r], dz = J.z - zi[r];
+                        const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+                        const double y = __builtin_amdgcn_rsq(r2);
+                        double u = y * __builtin_fma(-(r2 * y), y, 3.0);
+                        u = c * JC + e == (w * R + r) * kWave + lane ? 0.0 : u;   // the body itself
+                        phi[r] = __builtin_fma(J.m, u, phi[r]);
+                    }
+                }
+            }
+        }
+        if (!diag) {
+            __syncthreads();
+            for (int e = tid; e < JC; e += kWave * W) {
+                const int64_t j = jc + e;
+                double v = 0.0;
+#pragma unroll
+                for (int u = 0; u < W; ++u) v += jsum[u][e];
+                if (j < a.n) a.B[p * a.b_stride + j - a.b0] = v;
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = p * BL + (w * R + r) * kWave + lane;
+        if (i < a.n) a.A[(q - a.s0) * a.n + i] = phi[r];
+    }
+}
+
+// One value per work-group: a fixed-shape tree over its 256 lanes.
+__device__ __forceinline__ void block_tree_sum(double e, double *wg_sum)
+{
+    __shared__ double red[256];
+    red[threadIdx.x] = e;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) wg_sum[blockIdx.x] = red[0];
+}
+
+// Adds a panel's entries of every body to phi, in block order: q = s0 .. s1-1
+// not below the body's own block, then, for bodies of the panel, the blocks
+// below their own.  The last panel (wg_sum not null) completes every phi and
+// forms m_i phi_i / 2, reduced to one value per work-group.
+__global__ __launch_bounds__(256) void potential_pairs_reduce(PotPairs a, int32_t s1, int32_t block,
+                                                              double *phi, double *wg_sum)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t own = i / block;
+    double e = 0.0;
+    if (i < a.n && own < s1) {
+        double v = own < a.s0 ? phi[i] : 0.0;
+        for (int64_t q = own > a.s0 ? own : a.s0; q < s1; ++q) v += a.A[(q - a.s0) * a.n + i];
+        if (own >= a.s0)
+            for (int64_t p = 0; p < own; ++p) v += a.B[p * a.b_stride + i - a.b0];
+        phi[i] = v;
+        e = 0.5 * a.m[i] * v;
+    }
+    if (wg_sum) block_tree_sum(e, wg_sum);
+}
+
 // Sums split partials (fixed order) into phi and forms m_i phi_i / 2 per
 // body; then a fixed-shape tree reduction of those into one value per
 // work-group, and a final single-work-group pass.
@@ -243,7 +399,6 @@ __global__ __launch_bounds__(256) void potential_reduce(int64_t n, const double 
                                                         int32_t splits, const double *part,
                                                         double *phi, double *wg_sum)
 {
-    __shared__ double red[256];
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     double e = 0.0;
     if (i < n) {
@@ -252,13 +407,7 @@ __global__ __launch_bounds__(256) void potential_reduce(int64_t n, const double 
         phi[i] = p;
         e = 0.5 * m[i] * p;
     }
-    red[threadIdx.x] = e;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) wg_sum[blockIdx.x] = red[0];
+    block_tree_sum(e, wg_sum);
 }
 
 __global__ __launch_bounds__(256) void sum_kernel(int64_t count, const double *v, double *out)
@@ -279,6 +428,44 @@ __global__ __launch_bounds__(256) void sum_kernel(int64_t count, const double *v
 }  // namespace nb
 
 using namespace nbrt;
+
+namespace {
+
+// Block size of the pair-wise potential and its launch, by the number of
+// bodies: large blocks share a body of q among more pairs, small ones make
+// enough items for the chip.  Whole calls in us, rows per lane x waves:
+//   n       1x1     2x1     2x4     4x4     plain kernel
+//   1024    15.6    21.7    56.7    172     75
+//   4096    32.4    29.0    60.0    174     145
+//   8192    68      52      62      176     146
+//   16384   167     119     121     178     176
+//   65536   1856    1214    1101    1109    1862
+//   131072  9121    5198    4179    3936    7311
+struct PotShape {
+    int64_t block;
+    void (*launch)(const nb::PotPairs &, int64_t, hipStream_t);
+};
+
+template <int R, int W>
+PotShape pot_shape_of()
+{
+    return {nb::kWave * R * W, [](const nb::PotPairs &a, int64_t items, hipStream_t s) {
+                hipLaunchKernelGGL((nb::potential_pairs_kernel<R, W>), dim3((unsigned)items),
+                                   dim3(nb::kWave * W), 0, s, a);
+            }};
+}
+
+PotShape pot_shape(int64_t n)
+{
+    if (n >= 65536) return pot_shape_of<4, 4>();
+    if (n >= 16384) return pot_shape_of<2, 4>();
+    if (n >= 4096) return pot_shape_of<2, 1>();
+    return pot_shape_of<1, 1>();
+}
+
+constexpr size_t kPotBytes = size_t(1) << 30;
+
+}  // namespace
 
 extern "C" {
 
@@ -349,6 +536,58 @@ int nb_potential(nb_ctx *ctx, int64_t n, const double *x, const double *m, doubl
 {
     if (!ctx || n <= 0 || n > INT32_MAX || !x || !m || !phi) return NB_ERR_INVALID_ARG;
     if (!ctx->usable) return NB_ERR_UNSUPPORTED;
+    hipEvent_t ev[2];
+    hipError_t e;
+    const int64_t red_wgs = (n + 255) / 256;
+    // one evaluation per pair of bodies, in panels of blocks whose entries take
+    // at most kPotBytes (one panel up to about 370000 bodies); under a scratch
+    // limit smaller panels, or, without room for one block, the plain kernel
+    const PotShape sh = pot_shape(n);
+    const int64_t blocks = (n + sh.block - 1) / sh.block;
+    int64_t panel = blocks;
+    auto pot_bytes = [&](int64_t pb) {
+        const int64_t cells = pb == blocks ? blocks * n : pb * n + blocks * pb * sh.block;
+        return (size_t)(cells + red_wgs + 1) * sizeof(double);
+    };
+    const size_t most = ctx->scratch_limit ? std::min(ctx->scratch_limit, kPotBytes) : kPotBytes;
+    while (panel > 1 && pot_bytes(panel) > most) panel = (panel + 1) / 2;
+    if (!ctx->scratch_limit || pot_bytes(panel) <= ctx->scratch_limit) {
+        int rc = ensure_scratch(ctx, pot_bytes(panel));
+        if (rc != NB_OK) return rc;
+        double *wg = (double *)ctx->scratch;
+        double *cells = wg + red_wgs + 1;
+        e = timed_begin(ctx, NB_CLASS_STEP, ev);
+        for (int64_t s0 = 0; e == hipSuccess && s0 < blocks; s0 += panel) {
+            const int64_t s1 = std::min(blocks, s0 + panel);
+            nb::PotPairs a{};
+            a.n = n;
+            a.x = x;
+            a.m = m;
+            a.s0 = (int32_t)s0;
+            a.A = cells;
+            if (panel == blocks) {   // (p, q) and (q, p) share one square of entries
+                a.B = cells;
+                a.b_stride = n;
+            } else {
+                a.B = cells + panel * n;
+                a.b_stride = panel * sh.block;
+                a.b0 = s0 * sh.block;
+            }
+            const int64_t items = (s1 * (s1 + 1) - s0 * (s0 + 1)) / 2;
+            sh.launch(a, items, ctx->stream);
+            hipLaunchKernelGGL(nb::potential_pairs_reduce, dim3((unsigned)red_wgs), dim3(256), 0,
+                               ctx->stream, a, (int32_t)s1, (int32_t)sh.block, phi,
+                               s1 == blocks ? wg : nullptr);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(nb::sum_kernel, dim3(1), dim3(256), 0, ctx->stream, red_wgs, wg,
+                               energy ? energy : wg + red_wgs);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess) e = timed_end(ctx, NB_CLASS_STEP, ev);
+        return e == hipSuccess ? NB_OK : hip_fail(ctx, e);
+    }
     const int cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
     const int64_t wgs = (n + nb::kBlock - 1) / nb::kBlock;
     int64_t splits = std::max<int64_t>(1, std::min<int64_t>((cus * 64 + wgs - 1) / wgs,
@@ -356,15 +595,13 @@ int nb_potential(nb_ctx *ctx, int64_t n, const double *x, const double *m, doubl
     const int64_t tiles = (n + nb::kTile - 1) / nb::kTile;
     const int64_t split_len = (tiles + splits - 1) / splits * nb::kTile;
     splits = (n + split_len - 1) / split_len;
-    const int64_t red_wgs = (n + 255) / 256;
     const size_t bytes = (size_t)(splits * n + red_wgs + 1) * sizeof(double) + 512;
     int rc = ensure_scratch(ctx, bytes);
     if (rc != NB_OK) return rc;
     double *part = (double *)ctx->scratch;
     double *wg = part + splits * n;
     double *tot = wg + red_wgs;
-    hipEvent_t ev[2];
-    hipError_t e = timed_begin(ctx, NB_CLASS_STEP, ev);
+    e = timed_begin(ctx, NB_CLASS_STEP, ev);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(nb::potential_kernel, dim3((unsigned)wgs, (unsigned)splits),
                            dim3(nb::kBlock), 0, ctx->stream, n, x, m, (int32_t)splits, split_len,
