@@ -12,64 +12,36 @@
 //   g_u      = m_j [ B R3 - 3 (B.r) R5 r ]
 //   dL/dx_j += g_r,  dL/dx_i -= g_r,  dL/dv_j += g_u,  dL/dv_i -= g_u.
 //
-// Two recompute passes, FP64, no per-pair storage and no atomics:
-//  * row pass: one row per lane, j-tiles through LDS; sums g_r and g_u over j
-//    (the per-row "-" terms).  The row-constant factors A and B are applied
-//    once at the end: sum_j g_r = A sum(m R3) - 3 B sum(m R5 s) + ...
-//  * body pass: one body j per lane, row tiles through LDS; sums the "+"
-//    terms and dL/dm_j over all rows, and subtracts the row pass result of
-//    every row whose body is j, in row order.
-// Both passes may split their loop range; partials are reduced in a fixed
-// order, so results are bitwise deterministic.
+// One recompute pass, FP64, no per-pair storage and no global atomics on
+// values.  Every pair is evaluated once for its row and its body (a row pass
+// and a body pass used to recompute the same geometry, about half of the 111
+// FP64 instructions that the two spent on a pair): each lane holds R rows in
+// registers, bodies pass through LDS in tiles of 64, and at step s lane l
+// meets body l ^ s, so the lanes of a wave work on 64 different bodies.  The
+// row's sums stay in registers; the body's seven shares of the lane's R rows
+// are added in registers and then to the wave's own LDS sums, without conflict
+// and in a fixed order.  Row sums per block of bodies and body sums per block
+// of rows go to scratch and are added in block order, so results are bitwise
+// deterministic; the "-" terms reach a body in row order.
+#include <algorithm>
+
 #include "nb_internal.h"
 #include "nb_pair.h"
 
 namespace nb {
 namespace {
 
-constexpr int kRowTile = 128;   // rows staged per LDS tile in the body pass
-
-struct alignas(16) JB {
-    double x, y, z, m;
-    double vx, vy, vz, pad;
-};
-
-struct alignas(16) RB {
-    double x, y, z, vx, vy, vz;
-    double ax, ay, az, bx, by, bz;
-    double hi;
-    float rs2f;
-    int32_t i;
-    int32_t b;
-    int32_t pad;
-};
-
 struct AdjPlan {
-    int32_t row_splits;
-    int64_t row_split_len;   // j per split in the row pass
-    int32_t body_splits;
-    int64_t body_split_len;  // rows per split in the body pass
-    double *row_partial;     // [row_splits][6][n_i]
-    double *body_partial;    // [body_splits][7][n]
+    int32_t row_block;       // rows per row block (64 R W)
+    int32_t panel_row0;      // first row of this panel
+    int32_t panel_rows;      // rows of this panel (its row blocks' rows below n_i)
+    int32_t body_blocks;     // blocks of body_len bodies
+    int64_t body_len;
+    int32_t add;             // body sums of an earlier panel are added to
+    double *row_partial;     // [body_blocks][6][panel_rows]
+    double *body_partial;    // [row blocks of a panel][7][n]
+    int2 *index;             // per body: its first row (n_i: none), its number of rows
 };
-
-__device__ __forceinline__ void load_jb(JB &J, const AdjointArgs &a, int64_t j, int64_t j1)
-{
-    if (j < j1) {
-        J.x = a.xp[j];
-        J.y = a.xp[a.n + j];
-        J.z = a.xp[2 * a.n + j];
-        J.vx = a.vp[j];
-        J.vy = a.vp[a.n + j];
-        J.vz = a.vp[2 * a.n + j];
-        J.m = a.m[j];
-    } else {
-        J.x = J.y = J.z = kFar;
-        J.vx = J.vy = J.vz = 0.0;
-        J.m = 0.0;
-    }
-    J.pad = 0.0;
-}
 
 // Exclusion (self pair or neighbour) by the canonical test, run only for
 // candidates below the FP64 bound hi: an excluded pair gets the squared
@@ -87,263 +59,248 @@ __device__ __forceinline__ void exclude(double dx, double dy, double dz, double 
     }
 }
 
-// ---------------------------------------------------------------------------
-// Row pass.  grid = (ceil(n_i / kBlock), row_splits).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void adj_rows_kernel(AdjointArgs a, AdjPlan p)
-{
-    __shared__ JB tile[2][kTile];
-    const int tid = threadIdx.x;
-    const int32_t split = blockIdx.y;
-    const int64_t j0 = (int64_t)split * p.row_split_len;
-    const int64_t j1 = j0 + p.row_split_len < a.n ? j0 + p.row_split_len : a.n;
-    const int64_t b = (int64_t)blockIdx.x * kBlock + tid;
-
-    double xi = kFar * 0.5, yi = kFar * 0.5, zi = kFar * 0.5, vxi = 0, vyi = 0, vzi = 0;
-    double Ax = 0, Ay = 0, Az = 0, Bx = 0, By = 0, Bz = 0, hi = -1.0;
-    float rs2f = -1.0f;
-    int32_t i = -1;
-    if (b < a.n_i) {
-        const int64_t ii = a.i_block[b];
-        if (ii >= 0 && ii < a.n) {
-            i = (int32_t)ii;
-            xi = a.xp[ii];
-            yi = a.xp[a.n + ii];
-            zi = a.xp[2 * a.n + ii];
-            vxi = a.vp[ii];
-            vyi = a.vp[a.n + ii];
-            vzi = a.vp[2 * a.n + ii];
-            Ax = a.w_a[b];
-            Ay = a.w_a[a.n_i + b];
-            Az = a.w_a[2 * (int64_t)a.n_i + b];
-            Bx = a.w_j[b];
-            By = a.w_j[a.n_i + b];
-            Bz = a.w_j[2 * (int64_t)a.n_i + b];
-            rs2f = (float)a.rs2[b];
-            hi = cand_bound_f64(rs2f);
-        }
+// One row in registers with its sums over bodies: with k = -3 R5,
+//   sum_j g_r = A C1 + B C2 + H,  sum_j g_u = B C1 + U,
+//   C1 = sum m R3,  C2 = sum m k s,  U = sum m k (B.r) r,
+//   H = sum m [k (B.r) u + k ((A.r + B.u) - 5 s (B.r) |r|^-2) r].
+struct AdjRow {
+    double x, y, z, vx, vy, vz, ax, ay, az, bx, by, bz, hi;
+    float rs2f;
+    int32_t i;
+    double C1, C2, Hx, Hy, Hz, Ux, Uy, Uz;
+    __device__ __forceinline__ void load(const AdjointArgs &a, int64_t b, int64_t end)
+    {
+        x = y = z = kFar * 0.5;
+        vx = vy = vz = ax = ay = az = bx = by = bz = 0.0;
+        hi = -1.0;
+        rs2f = -1.0f;
+        i = -1;
+        C1 = C2 = Hx = Hy = Hz = Ux = Uy = Uz = 0.0;
+        if (b >= end) return;
+        const int64_t k = a.i_block[b];
+        if (k < 0 || k >= a.n) return;
+        i = (int32_t)k;
+        x = a.xp[k];
+        y = a.xp[a.n + k];
+        z = a.xp[2 * a.n + k];
+        vx = a.vp[k];
+        vy = a.vp[a.n + k];
+        vz = a.vp[2 * a.n + k];
+        ax = a.w_a[b];
+        ay = a.w_a[a.n_i + b];
+        az = a.w_a[2 * (int64_t)a.n_i + b];
+        bx = a.w_j[b];
+        by = a.w_j[a.n_i + b];
+        bz = a.w_j[2 * (int64_t)a.n_i + b];
+        rs2f = (float)a.rs2[b];
+        hi = cand_bound_f64(rs2f);
     }
-    // With k5 = m R5 and t = k5 (B.r):
-    //   sum_j g_r = A C1 - 3 (B C2 + H),  sum_j g_u = B C1 - 3 U,
-    //   C1 = sum m R3,  C2 = sum k5 s,  U = sum t r,
-    //   H = sum [t u + k5 ((A.r + B.u) - 5 s (B.r) |r|^-2) r];
-    // the factor -3 is applied once per row.
-    double C1 = 0, C2 = 0, Hx = 0, Hy = 0, Hz = 0, Ux = 0, Uy = 0, Uz = 0;
+};
 
-    // Each tile is loaded when the work-group reaches it, into the buffer
-    // last read for tile t-2 (every wave has passed tile t-1's barrier since):
-    // one barrier per tile and no registers held across the pair loop.
-    const int64_t ntiles = j1 > j0 ? (j1 - j0 + kTile - 1) / kTile : 0;
-    for (int64_t t = 0; t < ntiles; ++t) {
-        const int cur = (int)(t & 1);
-        const int64_t tbase = j0 + t * kTile;
-        {
-            JB J;
-            load_jb(J, a, tbase + tid, j1);
-            tile[cur][tid] = J;
+// grid = row blocks of the panel x body blocks (row blocks fastest: running
+// work-groups share bodies); T bodies staged at a time.  FP64 VALU bound at R
+// = 2 (about 75 instructions per pair; the LDS is busy for half of that), LDS
+// bound at R = 1.  Held to three waves per SIMD at R = 2 (168 VGPRs, no spill;
+// at the compiler's 180 two fit): 65536 rows of 65536 11.15 ms against 11.53.
+// The two passes before took 16.2 ms there, 1823 us on 20011 of 20011 (now
+// 1150), 545 on 4096 of 4096 (75), 364 on 1024 of 1024 (35).
+template <int R, int W, int T>
+__global__ __launch_bounds__(kWave * W) __attribute__((amdgpu_waves_per_eu(R == 2 ? 3 : 4))) void adj_pairs_kernel(AdjointArgs a, AdjPlan p)
+{
+    constexpr int BR = kWave * R * W;
+    // planes of 16 bytes: consecutive lanes read consecutive banks
+    __shared__ double2 t_xy[T], t_zm[T], t_vxy[T];
+    __shared__ double t_vz[T];
+    __shared__ double sums[W][7][T];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int32_t row_blocks = (p.panel_rows + BR - 1) / BR;
+    const int32_t rb = (int32_t)(blockIdx.x % row_blocks), qb = (int32_t)(blockIdx.x / row_blocks);
+    const int64_t j0 = (int64_t)qb * p.body_len;
+    const int64_t j1 = j0 + p.body_len < a.n ? j0 + p.body_len : a.n;
+    const int64_t row0 = (int64_t)p.panel_row0 + (int64_t)rb * BR;
+    const int64_t row_end = (int64_t)p.panel_row0 + p.panel_rows;
+
+    // the bodies' row index starts empty (written by a later launch)
+    if (!p.add)
+        for (int64_t j = (int64_t)blockIdx.x * (kWave * W) + tid; j < a.n;
+             j += (int64_t)gridDim.x * (kWave * W))
+            p.index[j] = make_int2(a.n_i, 0);
+
+    AdjRow Q[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) Q[r].load(a, row0 + (w * R + r) * kWave + lane, row_end);
+    bool mine = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) mine = mine || Q[r].i >= 0;
+    const bool busy = __ballot(mine) != 0;   // a wave without rows only stages and stores
+
+    for (int64_t c0 = j0; c0 < j1; c0 += T) {
+        if (c0 > j0) __syncthreads();   // the last tile's sums are read
+        for (int e = tid; e < T; e += kWave * W) {
+            const int64_t j = c0 + e;
+            const bool live = j < j1;
+            t_xy[e] = live ? make_double2(a.xp[j], a.xp[a.n + j]) : make_double2(kFar, kFar);
+            t_zm[e] = live ? make_double2(a.xp[2 * a.n + j], a.m[j]) : make_double2(kFar, 0.0);
+            t_vxy[e] = live ? make_double2(a.vp[j], a.vp[a.n + j]) : make_double2(0.0, 0.0);
+            t_vz[e] = live ? a.vp[2 * a.n + j] : 0.0;
         }
+#pragma unroll
+        for (int k = 0; k < 7; ++k)
+            for (int e = lane; e < T; e += kWave) sums[w][k][e] = 0.0;
         __syncthreads();
-        const JB *buf = tile[cur];
-#pragma unroll 2
-        for (int jj = 0; jj < kTile; ++jj) {
-            const JB &J = buf[jj];
-            const double dx = J.x - xi, dy = J.y - yi, dz = J.z - zi;
-            double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-            exclude(dx, dy, dz, r2, hi, rs2f, (int32_t)(tbase + jj), i);
-            const double ux = J.vx - vxi, uy = J.vy - vyi, uz = J.vz - vzi;
-            const double y = rsqrt_f64(r2);
-            const double y2 = y * y;
-            const double R3 = y * y2, R5 = R3 * y2;
-            const double s = __builtin_fma(dz, uz, __builtin_fma(dy, uy, dx * ux));
-            const double Ar = __builtin_fma(Az, dz, __builtin_fma(Ay, dy, Ax * dx));
-            const double Br = __builtin_fma(Bz, dz, __builtin_fma(By, dy, Bx * dx));
-            const double Bu = __builtin_fma(Bz, uz, __builtin_fma(By, uy, Bx * ux));
-            const double m = J.m;
-            const double k5 = m * R5;
-            const double tb = k5 * Br;
-            const double c = k5 * __builtin_fma(-5.0 * (s * Br), y2, Ar + Bu);
-            C1 = __builtin_fma(m, R3, C1);
-            C2 = __builtin_fma(k5, s, C2);
-            Hx = __builtin_fma(tb, ux, __builtin_fma(c, dx, Hx));
-            Hy = __builtin_fma(tb, uy, __builtin_fma(c, dy, Hy));
-            Hz = __builtin_fma(tb, uz, __builtin_fma(c, dz, Hz));
-            Ux = __builtin_fma(tb, dx, Ux);
-            Uy = __builtin_fma(tb, dy, Uy);
-            Uz = __builtin_fma(tb, dz, Uz);
-        }
-    }
-    if (b < a.n_i) {
-        double *o = p.row_partial + (int64_t)split * 6 * a.n_i + b;
-        o[0] = __builtin_fma(Ax, C1, -3.0 * __builtin_fma(Bx, C2, Hx));
-        o[a.n_i] = __builtin_fma(Ay, C1, -3.0 * __builtin_fma(By, C2, Hy));
-        o[2 * (int64_t)a.n_i] = __builtin_fma(Az, C1, -3.0 * __builtin_fma(Bz, C2, Hz));
-        o[3 * (int64_t)a.n_i] = __builtin_fma(Bx, C1, -3.0 * Ux);
-        o[4 * (int64_t)a.n_i] = __builtin_fma(By, C1, -3.0 * Uy);
-        o[5 * (int64_t)a.n_i] = __builtin_fma(Bz, C1, -3.0 * Uz);
-    }
-}
-
-// Sums the row-pass partials over splits (fixed order) into row_part[6][n_i].
-__global__ void adj_rows_reduce(AdjointArgs a, AdjPlan p)
-{
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t total = 6 * (int64_t)a.n_i;
-    if (k >= total) return;
-    double s = 0.0;
-    for (int32_t q = 0; q < p.row_splits; ++q) s += p.row_partial[(int64_t)q * total + k];
-    a.row_part[k] = s;
-}
-
-// ---------------------------------------------------------------------------
-// Body pass.  grid = (ceil(n / kBlock), body_splits); split q covers rows
-// [q * body_split_len, ...).
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void load_rb(RB &R, const AdjointArgs &a, int64_t b, int64_t b1)
-{
-    R.x = R.y = R.z = kFar * 0.5;
-    R.vx = R.vy = R.vz = 0.0;
-    R.ax = R.ay = R.az = R.bx = R.by = R.bz = 0.0;
-    R.hi = -1.0;
-    R.rs2f = -1.0f;
-    R.i = -1;
-    R.b = (int32_t)b;
-    R.pad = 0;
-    if (b >= b1) return;
-    const int64_t i = a.i_block[b];
-    if (i < 0 || i >= a.n) return;
-    R.i = (int32_t)i;
-    R.x = a.xp[i];
-    R.y = a.xp[a.n + i];
-    R.z = a.xp[2 * a.n + i];
-    R.vx = a.vp[i];
-    R.vy = a.vp[a.n + i];
-    R.vz = a.vp[2 * a.n + i];
-    R.ax = a.w_a[b];
-    R.ay = a.w_a[a.n_i + b];
-    R.az = a.w_a[2 * (int64_t)a.n_i + b];
-    R.bx = a.w_j[b];
-    R.by = a.w_j[a.n_i + b];
-    R.bz = a.w_j[2 * (int64_t)a.n_i + b];
-    R.rs2f = (float)a.rs2[b];
-    R.hi = cand_bound_f64(R.rs2f);
-}
-
-__global__ __launch_bounds__(kBlock) void adj_bodies_kernel(AdjointArgs a, AdjPlan p)
-{
-    __shared__ RB tile[2][kRowTile];
-    const int tid = threadIdx.x;
-    const int32_t split = blockIdx.y;
-    const int64_t b0 = (int64_t)split * p.body_split_len;
-    const int64_t b1 = b0 + p.body_split_len < a.n_i ? b0 + p.body_split_len : a.n_i;
-    const int64_t j = (int64_t)blockIdx.x * kBlock + tid;
-    const bool live = j < a.n;
-
-    double xj = kFar, yj = kFar, zj = kFar, vxj = 0, vyj = 0, vzj = 0, mj = 0;
-    if (live) {
-        xj = a.xp[j];
-        yj = a.xp[a.n + j];
-        zj = a.xp[2 * a.n + j];
-        vxj = a.vp[j];
-        vyj = a.vp[a.n + j];
-        vzj = a.vp[2 * a.n + j];
-        mj = a.m[j];
-    }
-    const int32_t jidx = live ? (int32_t)j : -2;
-    // The body's own mass and the factor -3 are applied once per body:
-    //   dL/dx_j = m_j (GA - 3 GB) - D_x,  dL/dv_j = m_j (UA - 3 UB) - D_v,
-    //   dL/dm_j = MA - 3 MB,
-    // GA = sum R3 A, GB = sum [R5 s B + R5 (B.r) u + R5 ((A.r + B.u) - 5 s (B.r) |r|^-2) r],
-    // UA = sum R3 B, UB = sum R5 (B.r) r, MA = sum (A.r + B.u) R3, MB = sum s (B.r) R5,
-    // and D the row-pass sums of the rows whose body is j (in row order).
-    double GAx = 0, GAy = 0, GAz = 0, GBx = 0, GBy = 0, GBz = 0;
-    double UAx = 0, UAy = 0, UAz = 0, UBx = 0, UBy = 0, UBz = 0, MA = 0, MB = 0;
-    double Dx = 0, Dy = 0, Dz = 0, Dux = 0, Duy = 0, Duz = 0;
-
-    // row tiles are loaded as in the row pass: when reached, into the buffer
-    // last read two tiles ago, one barrier per tile
-    const int64_t ntiles = b1 > b0 ? (b1 - b0 + kRowTile - 1) / kRowTile : 0;
-    for (int64_t t = 0; t < ntiles; ++t) {
-        const int cur = (int)(t & 1);
-        const int64_t tbase = b0 + t * kRowTile;
-        if (tid < kRowTile) {
-            RB R;
-            load_rb(R, a, tbase + tid, b1);
-            tile[cur][tid] = R;
-        }
-        __syncthreads();
-        const RB *buf = tile[cur];
+        const int live = (int)(j1 - c0 < T ? j1 - c0 : T);
+        for (int t = 0; busy && t < live; t += kWave) {
 #pragma unroll 1
-        for (int q = 0; q < kRowTile; ++q) {
-            const RB &R = buf[q];
-            const double dx = xj - R.x, dy = yj - R.y, dz = zj - R.z;
-            double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-            exclude(dx, dy, dz, r2, R.hi, R.rs2f, jidx, R.i);
-            const double ux = vxj - R.vx, uy = vyj - R.vy, uz = vzj - R.vz;
-            const double y = rsqrt_f64(r2);
-            const double y2 = y * y;
-            const double R3 = y * y2, R5 = R3 * y2;
-            const double s = __builtin_fma(dz, uz, __builtin_fma(dy, uy, dx * ux));
-            const double Ar = __builtin_fma(R.az, dz, __builtin_fma(R.ay, dy, R.ax * dx));
-            const double Br = __builtin_fma(R.bz, dz, __builtin_fma(R.by, dy, R.bx * dx));
-            const double Bu = __builtin_fma(R.bz, uz, __builtin_fma(R.by, uy, R.bx * ux));
-            const double AB = Ar + Bu;
-            const double sBr = s * Br;
-            MA = __builtin_fma(AB, R3, MA);
-            MB = __builtin_fma(sBr, R5, MB);
-            const double R5s = R5 * s;
-            const double R5Br = R5 * Br;
-            const double cr = R5 * __builtin_fma(-5.0 * sBr, y2, AB);
-            GAx = __builtin_fma(R3, R.ax, GAx);
-            GAy = __builtin_fma(R3, R.ay, GAy);
-            GAz = __builtin_fma(R3, R.az, GAz);
-            GBx = __builtin_fma(R5s, R.bx, __builtin_fma(R5Br, ux, __builtin_fma(cr, dx, GBx)));
-            GBy = __builtin_fma(R5s, R.by, __builtin_fma(R5Br, uy, __builtin_fma(cr, dy, GBy)));
-            GBz = __builtin_fma(R5s, R.bz, __builtin_fma(R5Br, uz, __builtin_fma(cr, dz, GBz)));
-            UAx = __builtin_fma(R3, R.bx, UAx);
-            UAy = __builtin_fma(R3, R.by, UAy);
-            UAz = __builtin_fma(R3, R.bz, UAz);
-            UBx = __builtin_fma(R5Br, dx, UBx);
-            UBy = __builtin_fma(R5Br, dy, UBy);
-            UBz = __builtin_fma(R5Br, dz, UBz);
-            // this body is the row's own body: subtract the row pass sum
-            int32_t ri = R.i;
-            if (ri == jidx) {
-                opaque(ri);
-                const double *rp = a.row_part + R.b;
-                Dx += rp[0];
-                Dy += rp[a.n_i];
-                Dz += rp[2 * (int64_t)a.n_i];
-                Dux += rp[3 * (int64_t)a.n_i];
-                Duy += rp[4 * (int64_t)a.n_i];
-                Duz += rp[5 * (int64_t)a.n_i];
+            for (int s = 0; s < kWave; ++s) {
+                const int e = t + (lane ^ s);
+                const double2 xy = t_xy[e], zm = t_zm[e], vxy = t_vxy[e];
+                const double vz = t_vz[e];
+                double g[7] = {0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    AdjRow &b = Q[r];
+                    const double dx = xy.x - b.x, dy = xy.y - b.y, dz = zm.x - b.z;
+                    double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+                    exclude(dx, dy, dz, r2, b.hi, b.rs2f, (int32_t)(c0 + e), b.i);
+                    const double ux = vxy.x - b.vx, uy = vxy.y - b.vy, uz = vz - b.vz;
+                    const double y = rsqrt_f64(r2);
+                    const double y2 = y * y;
+                    const double R3 = y * y2, k5 = -3.0 * (R3 * y2);
+                    const double sv = __builtin_fma(dz, uz, __builtin_fma(dy, uy, dx * ux));
+                    const double Ar = __builtin_fma(b.az, dz, __builtin_fma(b.ay, dy, b.ax * dx));
+                    const double Br = __builtin_fma(b.bz, dz, __builtin_fma(b.by, dy, b.bx * dx));
+                    const double Bu = __builtin_fma(b.bz, uz, __builtin_fma(b.by, uy, b.bx * ux));
+                    const double AB = Ar + Bu, sBr = sv * Br;
+                    const double es = k5 * sv, tb = k5 * Br;
+                    const double c = k5 * __builtin_fma(-5.0 * sBr, y2, AB);
+                    // the body's shares (without its mass)
+                    g[0] = __builtin_fma(c, dx, __builtin_fma(tb, ux, __builtin_fma(es, b.bx, __builtin_fma(R3, b.ax, g[0]))));
+                    g[1] = __builtin_fma(c, dy, __builtin_fma(tb, uy, __builtin_fma(es, b.by, __builtin_fma(R3, b.ay, g[1]))));
+                    g[2] = __builtin_fma(c, dz, __builtin_fma(tb, uz, __builtin_fma(es, b.bz, __builtin_fma(R3, b.az, g[2]))));
+                    g[3] = __builtin_fma(tb, dx, __builtin_fma(R3, b.bx, g[3]));
+                    g[4] = __builtin_fma(tb, dy, __builtin_fma(R3, b.by, g[4]));
+                    g[5] = __builtin_fma(tb, dz, __builtin_fma(R3, b.bz, g[5]));
+                    g[6] = __builtin_fma(sBr, k5, __builtin_fma(AB, R3, g[6]));
+                    // the row's sums
+                    const double m = zm.y, mt = m * tb, mc = m * c;
+                    b.C1 = __builtin_fma(m, R3, b.C1);
+                    b.C2 = __builtin_fma(m, es, b.C2);
+                    b.Hx = __builtin_fma(mt, ux, __builtin_fma(mc, dx, b.Hx));
+                    b.Hy = __builtin_fma(mt, uy, __builtin_fma(mc, dy, b.Hy));
+                    b.Hz = __builtin_fma(mt, uz, __builtin_fma(mc, dz, b.Hz));
+                    b.Ux = __builtin_fma(mt, dx, b.Ux);
+                    b.Uy = __builtin_fma(mt, dy, b.Uy);
+                    b.Uz = __builtin_fma(mt, dz, b.Uz);
+                }
+#pragma unroll
+                for (int k = 0; k < 7; ++k)
+                    __hip_atomic_fetch_add(&sums[w][k][e], g[k], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+        __syncthreads();
+        double *o = p.body_partial + (int64_t)rb * 7 * a.n + c0;
+        for (int e = tid; e < live * 7; e += kWave * W) {
+            const int k = e / live, q = e - k * live;
+            double v = 0.0;
+#pragma unroll
+            for (int u = 0; u < W; ++u) v += sums[u][k][q];
+            double *d = o + (int64_t)k * a.n + q;
+            *d = p.add ? *d + v : v;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const AdjRow &b = Q[r];
+        const int64_t k = row0 + (w * R + r) * kWave + lane;
+        if (k >= row_end) continue;
+        const int64_t st = p.panel_rows;
+        double *o = p.row_partial + (int64_t)qb * 6 * st + (k - p.panel_row0);
+        o[0] = __builtin_fma(b.ax, b.C1, __builtin_fma(b.bx, b.C2, b.Hx));
+        o[st] = __builtin_fma(b.ay, b.C1, __builtin_fma(b.by, b.C2, b.Hy));
+        o[2 * st] = __builtin_fma(b.az, b.C1, __builtin_fma(b.bz, b.C2, b.Hz));
+        o[3 * st] = __builtin_fma(b.bx, b.C1, b.Ux);
+        o[4 * st] = __builtin_fma(b.by, b.C1, b.Uy);
+        o[5 * st] = __builtin_fma(b.bz, b.C1, b.Uz);
+    }
+}
+
+// Sums the row partials of a panel over the body blocks (fixed order) into
+// row_part[6][n_i], enters the rows in their bodies' index and flags bad
+// indices.  One lane per component of a row.
+__global__ __launch_bounds__(256) void adj_rows_reduce(AdjointArgs a, AdjPlan p)
+{
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t total = 6 * (int64_t)p.panel_rows;
+    bool bad = false;
+    if (k < total) {
+        double s = 0.0;
+        for (int32_t q = 0; q < p.body_blocks; ++q) s += p.row_partial[(int64_t)q * total + k];
+        const int64_t comp = k / p.panel_rows, row = k - comp * p.panel_rows + p.panel_row0;
+        a.row_part[comp * a.n_i + row] = s;
+        if (comp == 0) {
+            const int64_t i = a.i_block[row];
+            bad = i < 0 || i >= a.n;
+            if (!bad) {
+                atomicMin(&p.index[i].x, (int32_t)row);
+                atomicAdd(&p.index[i].y, 1);
             }
         }
     }
-    if (live) {
-        double *o = p.body_partial + (int64_t)split * 7 * a.n + j;
-        o[0] = mj * __builtin_fma(-3.0, GBx, GAx) - Dx;
-        o[a.n] = mj * __builtin_fma(-3.0, GBy, GAy) - Dy;
-        o[2 * a.n] = mj * __builtin_fma(-3.0, GBz, GAz) - Dz;
-        o[3 * a.n] = mj * __builtin_fma(-3.0, UBx, UAx) - Dux;
-        o[4 * a.n] = mj * __builtin_fma(-3.0, UBy, UAy) - Duy;
-        o[5 * a.n] = mj * __builtin_fma(-3.0, UBz, UAz) - Duz;
-        o[6 * a.n] = __builtin_fma(-3.0, MB, MA);
-    }
+    const uint64_t bb = __ballot(bad);
+    if ((threadIdx.x & (kWave - 1)) == 0 && bb && a.status) atomicOr(a.status, kStBadIndex);
 }
 
-// Sums the body-pass partials (fixed order) into gx, gv, gm; flags bad
-// indices and non-finite results.
-__global__ void adj_bodies_reduce(AdjointArgs a, AdjPlan p)
+// A body's gradient: its partials over the row blocks (fixed order) times its
+// mass, less the row sums of the rows whose body it is, in row order.  A body
+// of one row finds it in the index; for the others (duplicate rows) the wave
+// looks through the block's rows from the first one on.
+__global__ __launch_bounds__(256) void adj_bodies_reduce(AdjointArgs a, AdjPlan p,
+                                                         int32_t row_blocks)
 {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool nonfin = false;
-    if (j < a.n) {
-        double v[7] = {0, 0, 0, 0, 0, 0, 0};
-        for (int32_t q = 0; q < p.body_splits; ++q) {
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const bool live = j < a.n;
+    const int lane = threadIdx.x & (kWave - 1);
+    double v[7] = {0, 0, 0, 0, 0, 0, 0}, D[6] = {0, 0, 0, 0, 0, 0};
+    int32_t first = 0, count = 0;
+    if (live) {
+        for (int32_t q = 0; q < row_blocks; ++q) {
             const double *src = p.body_partial + (int64_t)q * 7 * a.n + j;
 #pragma unroll
             for (int k = 0; k < 7; ++k) v[k] += src[(int64_t)k * a.n];
         }
+        const int2 t = p.index[j];
+        first = t.x;
+        count = t.y;
+        if (count == 1)
+#pragma unroll
+            for (int k = 0; k < 6; ++k) D[k] = a.row_part[(int64_t)k * a.n_i + first];
+    }
+    uint64_t dup = __ballot(count > 1);
+    while (dup) {   // uniform over the wave
+        const int l = __builtin_ctzll(dup);
+        dup &= dup - 1;
+        const int32_t body = __shfl((int32_t)j, l, kWave);
+        int32_t left = __shfl(count, l, kWave);
+        for (int64_t b0 = __shfl(first, l, kWave); b0 < a.n_i && left > 0; b0 += kWave) {
+            const int64_t b = b0 + lane;
+            uint64_t hit = __ballot(b < a.n_i && a.i_block[b < a.n_i ? b : 0] == body);
+            left -= __popcll(hit);
+            while (hit) {
+                const int64_t row = b0 + __builtin_ctzll(hit);
+                hit &= hit - 1;
+                if (lane == l)
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) D[k] += a.row_part[(int64_t)k * a.n_i + row];
+            }
+        }
+    }
+    bool nonfin = false;
+    if (live) {
+        const double m = a.m[j];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) v[k] = m * v[k] - D[k];
         a.gx[j] = v[0];
         a.gx[a.n + j] = v[1];
         a.gx[2 * a.n + j] = v[2];
@@ -353,61 +310,114 @@ __global__ void adj_bodies_reduce(AdjointArgs a, AdjPlan p)
         a.gm[j] = v[6];
         nonfin = !finite6(v[0], v[1], v[2], v[3], v[4], v[5]) || !__builtin_isfinite(v[6]);
     }
-    bool bad = false;
-    for (int64_t b = j; b < a.n_i; b += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = a.i_block[b];
-        bad |= i < 0 || i >= a.n;
-    }
-    const uint64_t f = __ballot(nonfin), bb = __ballot(bad);
-    if ((threadIdx.x & (kWave - 1)) == 0 && (f | bb) && a.status)
-        atomicOr(a.status, (f ? kStNonFinite : 0u) | (bb ? kStBadIndex : 0u));
+    const uint64_t f = __ballot(nonfin);
+    if (lane == 0 && f && a.status) atomicOr(a.status, kStNonFinite);
+}
+
+__global__ __launch_bounds__(256) void adj_clear_kernel(AdjointArgs a)
+{
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (j >= a.n) return;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) a.gx[(int64_t)k * a.n + j] = a.gv[(int64_t)k * a.n + j] = 0.0;
+    a.gm[j] = 0.0;
+}
+
+size_t round256(size_t b) { return (b + 255) / 256 * 256; }
+
+template <int R, int W, int T>
+void launch_pairs(const AdjointArgs &a, const AdjPlan &p, int64_t items, hipStream_t s)
+{
+    hipLaunchKernelGGL((adj_pairs_kernel<R, W, T>), dim3((unsigned)items), dim3(kWave * W), 0, s, a,
+                       p);
 }
 
 }  // namespace
 
-size_t adjoint_scratch_bytes(int64_t n, int32_t n_i, int row_splits, int body_splits)
+// Rows per block, LDS tile, bodies per block and row blocks per panel.  Two
+// rows per lane (512 a block) where there are enough rows for it, one (256)
+// else, and tiles of 64 bodies where few bodies make the serial chain of a tile
+// the whole call: 1024 rows of 1024 35 us with 64, 57 with 128; 1024 of 16384
+// 111 against 92; 4096 of 16384 234 with two rows per lane, 252 with one.
+// Body blocks for about 24 items per CU (48 give the same time and twice the
+// row partials), entries of at most kAdjointBytes by smaller panels, then by
+// longer body blocks; a call under a scratch limit needs no more than
+// 7 n + 12 n_i values at the least.
+AdjointShape adjoint_shape(int64_t n, int32_t n_i, int cus, size_t limit)
 {
-    return (size_t)row_splits * 6 * n_i * sizeof(double) + 6 * (size_t)n_i * sizeof(double) +
-           (size_t)body_splits * 7 * n * sizeof(double) + 3 * 256;
+    AdjointShape sh{};
+    sh.row_block = n_i >= 2048 && n > 8192 ? 512 : 256;
+    sh.tile = n > 8192 ? 128 : 64;
+    const int64_t blocks = std::max<int64_t>(1, ((int64_t)n_i + sh.row_block - 1) / sh.row_block);
+    const int64_t want = ((int64_t)cus * 24 + blocks - 1) / blocks;
+    const int64_t tiles = (n + sh.tile - 1) / sh.tile;
+    sh.body_len = (tiles + want - 1) / want * sh.tile;
+    sh.panel_blocks = blocks;
+    const size_t most = limit ? std::min(limit, kAdjointBytes) : kAdjointBytes;
+    while (sh.panel_blocks > 1 && adjoint_scratch_bytes(n, n_i, sh) > most)
+        sh.panel_blocks = (sh.panel_blocks + 1) / 2;
+    while (sh.body_len < n && adjoint_scratch_bytes(n, n_i, sh) > most) sh.body_len *= 2;
+    sh.index_in_gm = limit && adjoint_scratch_bytes(n, n_i, sh) > limit;
+    return sh;
 }
 
-hipError_t launch_adjoint_plan(const AdjointArgs &a0, int row_splits, int body_splits,
-                               void *scratch, hipStream_t s)
+size_t adjoint_scratch_bytes(int64_t n, int32_t n_i, const AdjointShape &sh)
+{
+    const int64_t q = (n + sh.body_len - 1) / sh.body_len;
+    const int64_t rows = std::min<int64_t>(n_i, sh.panel_blocks * sh.row_block);
+    return round256((size_t)q * 6 * rows * sizeof(double)) +
+           round256(6 * (size_t)n_i * sizeof(double)) +
+           round256((size_t)sh.panel_blocks * 7 * n * sizeof(double)) +
+           (sh.index_in_gm ? 0 : round256((size_t)n * sizeof(int2)));
+}
+
+hipError_t launch_adjoint(const AdjointArgs &a0, const AdjointShape &sh, void *scratch,
+                          hipStream_t s)
 {
     AdjointArgs a = a0;
+    if (a.n_i == 0) {
+        hipLaunchKernelGGL(adj_clear_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s,
+                           a);
+        return hipGetLastError();
+    }
     AdjPlan p{};
-    // row pass: split j
-    const int64_t tiles = (a.n + kTile - 1) / kTile;
-    const int64_t per_t = (tiles + row_splits - 1) / row_splits;
-    p.row_split_len = per_t * kTile;
-    p.row_splits = (int32_t)((a.n + p.row_split_len - 1) / p.row_split_len);
-    // body pass: split rows
-    const int64_t rt = (a.n_i + kRowTile - 1) / kRowTile;
-    const int64_t per_r = (rt + body_splits - 1) / body_splits;
-    p.body_split_len = (per_r > 0 ? per_r : 1) * kRowTile;
-    p.body_splits = (int32_t)((a.n_i + p.body_split_len - 1) / p.body_split_len);
-    if (p.body_splits < 1) p.body_splits = 1;
+    p.row_block = sh.row_block;
+    p.body_len = sh.body_len;
+    p.body_blocks = (int32_t)((a.n + sh.body_len - 1) / sh.body_len);
+    const int64_t panel = (int64_t)sh.panel_blocks * sh.row_block;
+    const int64_t rows = std::min<int64_t>(a.n_i, panel);
     char *c = (char *)scratch;
     auto take = [&c](size_t bytes) {
         char *r = c;
-        c += (bytes + 255) / 256 * 256;
+        c += round256(bytes);
         return r;
     };
-    p.row_partial = (double *)take((size_t)p.row_splits * 6 * a.n_i * sizeof(double));
+    p.row_partial = (double *)take((size_t)p.body_blocks * 6 * rows * sizeof(double));
     a.row_part = (double *)take(6 * (size_t)a.n_i * sizeof(double));
-    p.body_partial = (double *)take((size_t)p.body_splits * 7 * a.n * sizeof(double));
-
-    if (a.n_i > 0) {
-        dim3 g1((unsigned)((a.n_i + kBlock - 1) / kBlock), (unsigned)p.row_splits);
-        hipLaunchKernelGGL(adj_rows_kernel, g1, dim3(kBlock), 0, s, a, p);
-        const int64_t tot = 6 * (int64_t)a.n_i;
+    p.body_partial = (double *)take((size_t)sh.panel_blocks * 7 * a.n * sizeof(double));
+    p.index = sh.index_in_gm ? (int2 *)a.gm : (int2 *)take((size_t)a.n * sizeof(int2));
+    int32_t used = 0;   // row-block slots that hold sums
+    for (int64_t r0 = 0; r0 < a.n_i; r0 += panel) {
+        p.panel_row0 = (int32_t)r0;
+        p.panel_rows = (int32_t)std::min<int64_t>(panel, a.n_i - r0);
+        p.add = r0 > 0;
+        const int32_t blocks = (p.panel_rows + sh.row_block - 1) / sh.row_block;
+        used = std::max(used, blocks);
+        const int64_t items = (int64_t)blocks * p.body_blocks;
+        if (sh.row_block == 512)
+            launch_pairs<2, 4, 128>(a, p, items, s);
+        else if (sh.tile == 128)
+            launch_pairs<1, 4, 128>(a, p, items, s);
+        else
+            launch_pairs<1, 4, 64>(a, p, items, s);
+        const int64_t tot = 6 * (int64_t)p.panel_rows;
         hipLaunchKernelGGL(adj_rows_reduce, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s,
                            a, p);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    dim3 g2((unsigned)((a.n + kBlock - 1) / kBlock), (unsigned)p.body_splits);
-    hipLaunchKernelGGL(adj_bodies_kernel, g2, dim3(kBlock), 0, s, a, p);
-    hipLaunchKernelGGL(adj_bodies_reduce, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s,
-                       a, p);
+    hipLaunchKernelGGL(adj_bodies_reduce, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a,
+                       p, used);
     return hipGetLastError();
 }
 

@@ -140,7 +140,7 @@ hipError_t launch_fill_i32(int32_t *p, int32_t value, int64_t count, hipStream_t
 // Zeroes *a and, if b is not null, *b in one launch.
 hipError_t launch_clear_words(int32_t *a, int32_t *b, hipStream_t s);
 
-// Adjoint: two recompute passes.
+// Adjoint: one recompute pass over (row block, body block) items.
 struct AdjointArgs {
     int64_t n;
     const double *xp, *vp, *m;
@@ -152,9 +152,19 @@ struct AdjointArgs {
     uint32_t *status;
     double *row_part;         // scratch [6][n_i]: per-row "-" terms (set by the launcher)
 };
-size_t adjoint_scratch_bytes(int64_t n, int32_t n_i, int row_splits, int body_splits);
-hipError_t launch_adjoint_plan(const AdjointArgs &a, int row_splits, int body_splits,
-                               void *scratch, hipStream_t s);
+struct AdjointShape {
+    int32_t row_block;       // rows per row block: 256 or 512
+    int32_t tile;            // bodies per LDS tile: 64 or 128
+    int64_t body_len;        // bodies per body block
+    int64_t panel_blocks;    // row blocks per launch (their body sums are kept apart)
+    bool index_in_gm;        // the bodies' row index lives in the gm output
+};
+// Most scratch an adjoint call asks for by itself.
+constexpr size_t kAdjointBytes = size_t(1) << 30;
+AdjointShape adjoint_shape(int64_t n, int32_t n_i, int cus, size_t limit);
+size_t adjoint_scratch_bytes(int64_t n, int32_t n_i, const AdjointShape &sh);
+hipError_t launch_adjoint(const AdjointArgs &a, const AdjointShape &sh, void *scratch,
+                          hipStream_t s);
 
 // Batched ensemble: clusters of the concatenated arrays.
 struct BCluster {

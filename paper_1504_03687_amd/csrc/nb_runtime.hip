@@ -547,17 +547,8 @@ int nb_regular_force_adjoint(nb_ctx *ctx, int64_t n, const double *xp, const dou
     if (n_i > 0 && (!i_block || !rs2 || !w_a || !w_j)) return NB_ERR_INVALID_ARG;
     if (!ctx->usable) return NB_ERR_UNSUPPORTED;
     const int cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
-    // as for the forward pass: many short work-groups (~64 per CU in total),
-    // with at least 2048 bodies (row pass) or 512 rows (body pass) per split
-    const int64_t target = (int64_t)cus * 64;
-    const int64_t row_wgs = std::max<int64_t>(1, (n_i + nb::kBlock - 1) / nb::kBlock);
-    const int64_t body_wgs = (n + nb::kBlock - 1) / nb::kBlock;
-    int row_splits = (int)std::max<int64_t>(
-        1, std::min<int64_t>((target + row_wgs - 1) / row_wgs, std::max<int64_t>(1, n / 2048)));
-    int body_splits = (int)std::max<int64_t>(
-        1, std::min<int64_t>((target + body_wgs - 1) / body_wgs,
-                             std::max<int64_t>(1, (n_i + 511) / 512)));
-    int rc = ensure_scratch(ctx, nb::adjoint_scratch_bytes(n, n_i, row_splits, body_splits));
+    const nb::AdjointShape sh = nb::adjoint_shape(n, n_i, cus, ctx->scratch_limit);
+    int rc = n_i > 0 ? ensure_scratch(ctx, nb::adjoint_scratch_bytes(n, n_i, sh)) : NB_OK;
     if (rc != NB_OK) return rc;
     nb::AdjointArgs aa{};
     aa.n = n;
@@ -576,7 +567,7 @@ int nb_regular_force_adjoint(nb_ctx *ctx, int64_t n, const double *xp, const dou
     hipEvent_t ev[2];
     hipError_t e = timed_begin(ctx, NB_CLASS_ADJOINT, ev);
     if (e == hipSuccess)
-        e = nb::launch_adjoint_plan(aa, row_splits, body_splits, ctx->scratch, ctx->stream);
+        e = nb::launch_adjoint(aa, sh, ctx->scratch, ctx->stream);
     if (e == hipSuccess) e = timed_end(ctx, NB_CLASS_ADJOINT, ev);
     return e == hipSuccess ? NB_OK : hip_fail(ctx, e);
 }
