@@ -59,8 +59,10 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(IR == 1 && T
 // leaves at most kWave - 1 lanes idle.  Bound by VALU issue, as the
 // single-block kernel: 96 clusters of 1024 to 32768 bodies (5.8e9 pairs,
 // mixed) took 6113 us a call through LDS and take 5825.
+// The mixed kernel is held to five waves per SIMD (96 VGPRs, as the
+// single-block one has by itself): at 98 four fit.
 template <bool MIXED>
-__global__ __launch_bounds__(kBlock) void batched_packed_kernel(BatchArgs A)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MIXED ? 5 : 4))) void batched_packed_kernel(BatchArgs A)
 {
     for (;;) {
         // The whole wave comes back here together before lane 0 pulls.  The
@@ -82,8 +84,9 @@ __global__ __launch_bounds__(kBlock) void batched_packed_kernel(BatchArgs A)
         const int64_t j1 = j0 + C.split_len < C.j_end ? j0 + C.split_len : C.j_end;
         const Dest d{C.splits == 1, C.slot_base + (int64_t)I.split, (int64_t)C.row_begin,
                      (int64_t)C.splits};
-        rows_pass_packed<MIXED>(A.f, (JRecPtr)(A.f.packed + C.rec_base + (j0 - C.j_begin)),
-                                I.row0, (int64_t)C.row_begin + C.n_rows, j0, j1, d, C.near);
+        rows_pass_packed<MIXED>(A.f, A.f.packed + C.rec_base + (j0 - C.j_begin), I.row0,
+                                (int64_t)C.row_begin + C.n_rows, j0, j1, d, C.near,
+                                near_queue<MIXED>());
     }
 }
 

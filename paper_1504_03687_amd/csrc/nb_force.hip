@@ -81,8 +81,8 @@ __global__ __launch_bounds__(kBlock) void force_packed_kernel(ForceArgs a)
     const int64_t j0 = (int64_t)split * a.split_len;
     const int64_t j1 = j0 + a.split_len < a.n ? j0 + a.split_len : a.n;
     const Dest d{a.splits == 1, (int64_t)split, 0, (int64_t)a.splits};
-    rows_pass_packed<MIXED>(a, (JRecPtr)(a.packed + j0), tile * kWave, a.n_i, j0, j1, d,
-                            a.near_factor);
+    rows_pass_packed<MIXED>(a, a.packed + j0, tile * kWave, a.n_i, j0, j1, d, a.near_factor,
+                            near_queue<MIXED>());
 }
 
 // One-wave work-groups of the row-per-lane pass (64 rows, a 64-body LDS tile):

@@ -234,6 +234,11 @@ __device__ __forceinline__ void opaque(int32_t &a)
     __asm__ volatile("" : "+v"(a));
 }
 
+__device__ __forceinline__ void opaque_uniform(int32_t &a)
+{
+    __asm__ volatile("" : "+s"(a));
+}
+
 __device__ __forceinline__ bool finite6(double a, double b, double c, double d, double e,
                                         double f)
 {

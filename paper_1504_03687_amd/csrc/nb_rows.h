@@ -19,6 +19,7 @@
 namespace nb {
 
 struct alignas(16) JBody {
+    static constexpr bool kPacked = false;
     double x, y, z, m;
     double vx, vy, vz;
     float m32;
@@ -32,6 +33,7 @@ struct alignas(16) JBody {
 typedef const __attribute__((address_space(4))) JRec *JRecPtr;
 template <bool MIXED>
 struct SBody {
+    static constexpr bool kPacked = true;
     double x, y, z, vx, vy, vz;
     double m;      // FP64 plan
     float m32;     // mixed plan
@@ -137,48 +139,110 @@ __device__ __forceinline__ void row_init(Row<MIXED> &R, const ForceArgs &a, int6
 }
 
 // Row-per-lane mapping: each lane appends to its own row's list (in j order).
-// Rare branch of a mixed pair (neighbour, self or near pair): appends a
-// neighbour, or adds a near pair's term in FP64.
-template <bool MIXED, class Body>
-__device__ __forceinline__ void rare_mixed(Row<MIXED> &R, const Body &J, int32_t jidx, float r2f,
-                                           double dx, double dy, double dz)
+template <bool MIXED>
+__device__ __forceinline__ void append(Row<MIXED> &R, int32_t jidx)
 {
-    double ex = dx, ey = dy, ez = dz;
-    int32_t jj = jidx;
-    opaque(ex, ey, ez);
-    opaque(jj);
-    // padding past the j-range (far away, mass 0) passes the test only for a
-    // huge or infinite radius; it is never a neighbour and adds nothing
-    if (jj >= R.jend) return;
-    const bool self = jj == R.i;
-    const bool nbr = (r2f < R.rs2f) && !self;
-    if (nbr) {
-        if (R.cnt < R.lcap) R.lst[R.cnt] = jidx;
-        ++R.cnt;
-    } else if (!self) {
-        add_term_f64(R.S.ax, R.S.ay, R.S.az, R.S.jx, R.S.jy, R.S.jz, ex, ey, ez,
-                     J.vx - R.vx, J.vy - R.vy, J.vz - R.vz, J.mass());
+    if (R.cnt < R.lcap) R.lst[R.cnt] = jidx;
+    ++R.cnt;
+}
+
+// What the mixed pass does with a near pair (outside the radius, inside the
+// near bound), whose term is evaluated in FP64: at once ...
+struct NearNow {
+    template <class Body>
+    __device__ __forceinline__ void take(Row<true> &R, int32_t, const Body &J, double dx, double dy,
+                                         double dz)
+    {
+        add_term_f64(R.S.ax, R.S.ay, R.S.az, R.S.jx, R.S.jy, R.S.jz, dx, dy, dz, J.vx - R.vx,
+                     J.vy - R.vy, J.vz - R.vz, J.mass());
+    }
+};
+
+// ... or later: the lane notes the body in its own LDS queue, and every
+// kNearSpan bodies the wave evaluates all that its lanes hold.  At once, the
+// 30 FP64 instructions of a term run for one or two lanes of 64, in 28% of the
+// steps at n = 2^18 and 7% at 2^20 (512 near pairs per row).  A lane whose
+// queue is full takes further pairs at once: a halo row may have most of the
+// j-set inside its near bound, and emptying the queue for one lane costs more
+// than the term.  Both orders depend on the row alone, so its result does not
+// depend on the other lanes.
+constexpr int kNearSlots = 16;
+constexpr int64_t kNearSpan = 4096;
+
+struct NearLater {
+    int32_t (*queue)[kBlock];   // LDS [kNearSlots][kBlock]
+    int32_t n;                  // bodies queued
+    template <class Body>
+    __device__ __forceinline__ void take(Row<true> &R, int32_t jidx, const Body &J, double dx,
+                                         double dy, double dz)
+    {
+        if (n < kNearSlots) {
+            queue[n][threadIdx.x] = jidx;
+            ++n;
+        } else {
+            NearNow().take(R, jidx, J, dx, dy, dz);
+        }
+    }
+    // by the whole wave; rec0: the record of body j0
+    __device__ __forceinline__ void evaluate(Row<true> &R, const JRec *rec0, int32_t j0)
+    {
+        for (int q = 0; __ballot(q < n) != 0; ++q)
+            if (q < n) {
+                const double2 *p =
+                    reinterpret_cast<const double2 *>(rec0 + (queue[q][threadIdx.x] - j0));
+                const double2 xy = p[0], zvx = p[1], vyz = p[2], m = p[3];
+                add_term_f64(R.S.ax, R.S.ay, R.S.az, R.S.jx, R.S.jy, R.S.jz, xy.x - R.x,
+                             xy.y - R.y, zvx.x - R.z, zvx.y - R.vx, vyz.x - R.vy, vyz.y - R.vz,
+                             m.x);
+            }
+        n = 0;
+    }
+};
+
+// Rare branch of a mixed pair (neighbour, self or near pair): appends a
+// neighbour or takes a near pair; the pair then gets an excluding squared
+// distance.
+template <class Body, class Near>
+__device__ __forceinline__ void rare_mixed(Row<true> &R, const Body &J, int32_t jidx, float &r2f,
+                                           double dx, double dy, double dz, Near &N)
+{
+    if (r2f < R.candf) {
+        double ex = dx, ey = dy, ez = dz;
+        int32_t jj = jidx;
+        opaque(ex, ey, ez);
+        opaque_uniform(jj);
+        // padding past the j-range (far away, mass 0) passes the test only for a
+        // huge or infinite radius; it is never a neighbour and adds nothing
+        if (jj < R.jend && jj != R.i) {
+            if (r2f < R.rs2f)
+                append(R, jj);
+            else
+                N.take(R, jj, J, ex, ey, ez);
+        }
+        r2f = kExclR2F;
     }
 }
 
-// Exact canonical test of an FP64 candidate pair; appends a neighbour.
-// Returns true if the pair is excluded (neighbour or self).
-template <bool MIXED>
-__device__ __forceinline__ bool rare_f64(Row<MIXED> &R, int32_t jidx, double dx, double dy,
-                                         double dz)
+// Exact canonical test of an FP64 candidate pair; appends a neighbour, and
+// excludes it or the self pair (padding has mass 0: its term is exactly zero).
+// LATE: the test of the j-range stands after the canonical one (the packed
+// pass: 65536 rows of 2^20 71.4 ms against 73.5) or before it (the LDS passes:
+// 1024 of 1024 rows 23.7 us against 25.3).
+template <bool LATE>
+__device__ __forceinline__ void rare_f64(Row<false> &R, int32_t jidx, double &r2, double dx,
+                                         double dy, double dz)
 {
-    double ex = dx, ey = dy, ez = dz;
-    int32_t jj = jidx;
-    opaque(ex, ey, ez);
-    opaque(jj);
-    if (jj >= R.jend) return false;   // padding: mass 0, its term is exactly zero
-    const bool self = jj == R.i;
-    const bool nbr = (canon_r2f(ex, ey, ez) < R.rs2f) && !self;
-    if (nbr) {
-        if (R.cnt < R.lcap) R.lst[R.cnt] = jidx;
-        ++R.cnt;
+    if (r2 < R.hi && (LATE || jidx < R.jend)) {
+        double ex = dx, ey = dy, ez = dz;
+        int32_t jj = jidx;
+        opaque(ex, ey, ez);
+        opaque_uniform(jj);
+        const bool self = jj == R.i;
+        const bool nbr =
+            (canon_r2f(ex, ey, ez) < R.rs2f) && !self && (!LATE || jj < R.jend);
+        if (nbr) append(R, jj);
+        if (nbr || self) r2 = kExclR2;
     }
-    return nbr || self;
 }
 
 // One row against two consecutive j, with a single branch for the rare cases
@@ -191,9 +255,9 @@ __device__ __forceinline__ bool rare_f64(Row<MIXED> &R, int32_t jidx, double dx,
 // in the minimum), and a pair handled there gets an excluding squared
 // distance, so the common path holds no select.  Every accumulator receives
 // the terms of j and then j+1, as a loop over single j would give them.
-template <bool MIXED, class Body>
+template <bool MIXED, class Body, class Near>
 __device__ __forceinline__ void pair_rows2(Row<MIXED> &R, const Body &J0, const Body &J1,
-                                           int32_t jidx0)
+                                           int32_t jidx0, Near &N)
 {
     if constexpr (MIXED) {
         const double dx0 = J0.x - R.x, dy0 = J0.y - R.y, dz0 = J0.z - R.z;
@@ -203,14 +267,8 @@ __device__ __forceinline__ void pair_rows2(Row<MIXED> &R, const Body &J0, const 
         float r0 = __builtin_fmaf(fz0, fz0, __builtin_fmaf(fy0, fy0, fx0 * fx0));
         float r1 = __builtin_fmaf(fz1, fz1, __builtin_fmaf(fy1, fy1, fx1 * fx1));
         if (__builtin_fminf(r0, r1) < R.candf) {
-            if (r0 < R.candf) {
-                rare_mixed(R, J0, jidx0, r0, dx0, dy0, dz0);
-                r0 = kExclR2F;
-            }
-            if (r1 < R.candf) {
-                rare_mixed(R, J1, jidx0 + 1, r1, dx1, dy1, dz1);
-                r1 = kExclR2F;
-            }
+            rare_mixed(R, J0, jidx0, r0, dx0, dy0, dz0, N);
+            rare_mixed(R, J1, jidx0 + 1, r1, dx1, dy1, dz1, N);
         }
         accum_mixed(R.S, fx0, fy0, fz0, r0, J0.vx - R.vx, J0.vy - R.vy, J0.vz - R.vz, J0.m32);
         accum_mixed(R.S, fx1, fy1, fz1, r1, J1.vx - R.vx, J1.vy - R.vy, J1.vz - R.vz, J1.m32);
@@ -220,8 +278,8 @@ __device__ __forceinline__ void pair_rows2(Row<MIXED> &R, const Body &J0, const 
         double r0 = __builtin_fma(dz0, dz0, __builtin_fma(dy0, dy0, dx0 * dx0));
         double r1 = __builtin_fma(dz1, dz1, __builtin_fma(dy1, dy1, dx1 * dx1));
         if (__builtin_fmin(r0, r1) < R.hi) {
-            if (r0 < R.hi && rare_f64<MIXED>(R, jidx0, dx0, dy0, dz0)) r0 = kExclR2;
-            if (r1 < R.hi && rare_f64<MIXED>(R, jidx0 + 1, dx1, dy1, dz1)) r1 = kExclR2;
+            rare_f64<Body::kPacked>(R, jidx0, r0, dx0, dy0, dz0);
+            rare_f64<Body::kPacked>(R, jidx0 + 1, r1, dx1, dy1, dz1);
         }
         accum_f64(R.S, dx0, dy0, dz0, r0, J0.vx - R.vx, J0.vy - R.vy, J0.vz - R.vz, J0.m);
         accum_f64(R.S, dx1, dy1, dz1, r1, J1.vx - R.vx, J1.vy - R.vy, J1.vz - R.vz, J1.m);
@@ -357,6 +415,7 @@ __device__ __forceinline__ void rows_pass(const ForceArgs &a, JBody (*tile)[T], 
     static_assert(T % kFold == 0 && NB % kWave == 0, "tile and work-group shape");
     constexpr bool kPrefetch = T == NB;
     const int tid = threadIdx.x;
+    NearNow N;
     Row<MIXED> R[IR];
 #pragma unroll
     for (int r = 0; r < IR; ++r) {
@@ -406,7 +465,7 @@ __device__ __forceinline__ void rows_pass(const ForceArgs &a, JBody (*tile)[T], 
                 const int32_t jidx = (int32_t)(tbase + jj + q);
 #pragma unroll
                 for (int r = 0; r < IR; ++r)
-                    pair_rows2<MIXED>(R[r], buf[jj + q], buf[jj + q + 1], jidx);
+                    pair_rows2<MIXED>(R[r], buf[jj + q], buf[jj + q + 1], jidx, N);
             }
             if constexpr (MIXED) {
 #pragma unroll
@@ -439,6 +498,18 @@ __device__ __forceinline__ void rows_pass(const ForceArgs &a, JBody (*tile)[T], 
     flush_flags(a, ovf, bad, nonfin);
 }
 
+// LDS of the near-pair queues (the mixed pass of kBlock-lane work-groups).
+template <bool MIXED>
+__device__ __forceinline__ int32_t (*near_queue())[kBlock]
+{
+    if constexpr (MIXED) {
+        __shared__ int32_t q[kNearSlots][kBlock];
+        return q;
+    } else {
+        return nullptr;
+    }
+}
+
 // One wave's kWave rows [row0, row0 + kWave) against bodies [j0, j1) of the
 // packed j-set, whose records start at rec: the bodies are wave-uniform
 // operands in scalar registers, loaded two bodies ahead, so the pair loop has
@@ -450,19 +521,24 @@ __device__ __forceinline__ void rows_pass(const ForceArgs &a, JBody (*tile)[T], 
 // and 0.93e12 pairs/s).  What bounds it now is VALU issue: the loop's
 // instructions, timed one by one at four waves per SIMD, add up to 53 ns
 // (mixed) and 67 ns (FP64) per 64 pairs and SIMD; it takes 49 and 70.
-// Order, fold points and results are those of rows_pass.  Records past j1 up
+// Order and fold points are those of rows_pass, and so are the results but for
+// the order of a mixed row's near terms (queue: their queues, mixed pass only).
+// Records past j1 up
 // to the next multiple of kFold from j0, and two more, must be readable, and
 // at the end of the j-set they are padding.
 template <bool MIXED>
-__device__ __forceinline__ void rows_pass_packed(const ForceArgs &a, JRecPtr rec, int64_t row0,
-                                                 int64_t row_end, int64_t j0, int64_t j1,
-                                                 const Dest &d, float near)
+__device__ __forceinline__ void rows_pass_packed(const ForceArgs &a, const JRec *rec0,
+                                                 int64_t row0, int64_t row_end, int64_t j0,
+                                                 int64_t j1, const Dest &d, float near,
+                                                 int32_t (*queue)[kBlock])
 {
+    JRecPtr rec = (JRecPtr)rec0;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t b = row0 + lane;
     Row<MIXED> R;
     row_init(R, a, b, row_end, d, near);
     R.jend = (int32_t)j1;
+    NearLater N{queue, 0};
     if (__ballot(R.i >= 0) != 0) {
         SBody<MIXED> A0, A1, B0, B1;
         A0.load(rec);
@@ -476,16 +552,19 @@ __device__ __forceinline__ void rows_pass_packed(const ForceArgs &a, JRecPtr rec
                 B0.load(rec + 2);
                 B1.load(rec + 3);
                 __builtin_amdgcn_sched_barrier(0);
-                pair_rows2<MIXED>(R, A0, A1, jidx);
+                pair_rows2<MIXED>(R, A0, A1, jidx, N);
                 B0.arrive();
                 B1.arrive();
                 rec += 4;
                 A0.load(rec);
                 A1.load(rec + 1);
                 __builtin_amdgcn_sched_barrier(0);
-                pair_rows2<MIXED>(R, B0, B1, jidx + 2);
+                pair_rows2<MIXED>(R, B0, B1, jidx + 2, N);
             }
             if (MIXED || ((jb - j0 + kFold) & (kFoldF64 - 1)) == 0) R.S.fold();
+            if constexpr (MIXED)
+                if (((jb - j0 + kFold) & (kNearSpan - 1)) == 0 || jb + kFold >= j1)
+                    N.evaluate(R, rec0, (int32_t)j0);
         }
     }
     bool ovf = false, bad = false, nonfin = false;

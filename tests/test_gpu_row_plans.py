@@ -98,3 +98,39 @@ def test_short_splits(n, n_i, mapping, prec):
         compare_force(auto, s["x"], s["v"], s["m"], ib, rs2, cap, TOL[prec])
     finally:
         ctx.close()
+
+
+def test_near_queue_rows_do_not_depend_on_their_wave():
+    """Mixed packed pass at n >= 2^18, where near pairs wait in queues: rows
+    with no, few and far more near pairs than a queue holds, against the
+    oracle, and the same bits for a row whatever rows share its wave."""
+    n, n_i, cap = (1 << 18) + 77, 640, 16
+    say(f"near queue n={n}")
+    rng = np.random.default_rng(18)
+    x = rng.uniform(-1, 1, (3, n))
+    v = rng.standard_normal((3, n))
+    m = rng.uniform(0.5, 1.5, n) / n
+    ib = rng.choice(n, n_i, replace=False).astype(np.int32)
+    r = 2.0 * (8.0 / n) ** (1 / 3) * np.ones(n_i)     # about 4 neighbours, 30 near pairs
+    r[::7] = 0.2                                      # about 1000 near pairs
+    r[::31] = 1.0                                     # most of the bodies
+    r[::13] = 0.0
+    rs2 = (0.25 * r) ** 2 * np.where(r == 1.0, 16, 1)
+    X, V, M = dev(x), dev(v), dev(m)
+    ctx = nb.Context(0)
+    try:
+        ctx.set_plan(1, 1, 3)
+        one = nb.regular_force(X, V, M, dev(ib), dev(rs2), cap, "mixed", ctx=ctx)
+        assert "bodies=packed" in ctx.last_plan(), ctx.last_plan()
+        p = rng.permutation(n_i)
+        two = nb.regular_force(X, V, M, dev(ib[p]), dev(rs2[p]), cap, "mixed", ctx=ctx)
+        torch.cuda.synchronize()
+    finally:
+        ctx.close()
+    a, b = _defined(one, cap), _defined(two, cap)
+    for k in (0, 1):
+        assert np.array_equal(a[k][:, p], b[k])
+    for k in (2, 3):
+        assert np.array_equal(a[k][p], b[k])
+    rows = np.concatenate([np.arange(0, 64), rng.choice(n_i, 32, replace=False)])
+    compare_force(one, x, v, m, ib, rs2, cap, TOL_MIXED, rows=rows)
