@@ -18,13 +18,13 @@
 //
 // GPU shape: a counting sort by level, deterministic.  Each wave owns a
 // contiguous run of items and walks it in rounds of 64: per round, one ballot
-// per distinct level gives every item its rank among the wave's earlier items
+// per bit of the level gives every item its rank among the wave's earlier items
 // of that level (a running per-wave count in LDS); the per-level wave counts
 // are then scanned across waves (and work-groups) in item order, so the
 // build is stable.  All rounds' gathers are issued before any is used.
-//   <= 16384 items: one work-group of 1024 threads does the whole sort in one
-//            launch, in place (every read of the list precedes the first
-//            write);
+//   <= 8192 items, or <= 16384 while the context holds no scratch: one
+//            work-group of 1024 threads does the whole sort in one launch, in
+//            place (every read of the list precedes the first write);
 //   larger:  two launches: count (4096 items per work-group: per-level
 //            counts stored level-major [K][blocks], a per-block range flag,
 //            and for an update a copy of the prefix), then scatter (each
@@ -41,13 +41,19 @@ namespace nb {
 namespace {
 
 constexpr int kMaxLevels = 64;
-constexpr int kRounds = 16;   // rounds of 64 items per wave
-// multi-work-group path
-constexpr int kMwThreads = 256;
-constexpr int kMwItems = kMwThreads * kRounds;
+constexpr int kRounds = 16;   // rounds of 64 items per wave, single-work-group path
+// multi-work-group path: 16 waves of 4 rounds (with 4 waves of 16 rounds a SIMD
+// had one wave, and nothing hid its serial ranking: count and scatter of 2^20
+// items 15.9 and 18.4 us)
+constexpr int kMwThreads = 1024;
+constexpr int kMwRounds = 4;
+constexpr int kMwItems = kMwThreads * kMwRounds;
 // single-work-group path
 constexpr int kSwThreads = 1024;
 constexpr int kSwItems = kSwThreads * kRounds;
+// above this many items the two launches are faster (16384 items: 16 us in one
+// work-group, 10 in two launches), and are taken if their scratch is there
+constexpr int kSwFewItems = 8192;
 
 __device__ __forceinline__ uint32_t lane_rank(uint64_t mask)
 {
@@ -107,30 +113,42 @@ __device__ __forceinline__ bool load_items(int64_t n, const int32_t *src, int32_
     return bad;
 }
 
-// Ranks within the wave: rk[r] = number of the wave's earlier items with the
-// same level.  Returns the wave's count of level L in lane L (the running
-// counts live in that VGPR and are read back with readlane, so the loop has no
-// memory round trip).
-template <int R>
-__device__ __forceinline__ int32_t wave_rank(const int32_t (&lv)[R], int32_t (&rk)[R])
+// Lanes of the wave whose item has this lane's level (levels below 64, six
+// ballots; lanes without an item match nobody).  A ballot per distinct level,
+// the way before, took a dozen serial turns per round on a spread of levels.
+__device__ __forceinline__ uint64_t same_level(int32_t lv)
 {
-    const int lane = threadIdx.x & (kWave - 1);
-    int32_t runv = 0;
+    uint64_t m = __ballot(lv >= 0);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const uint64_t b = __ballot((lv >> k) & 1);
+        m &= ((lv >> k) & 1) ? b : ~b;
+    }
+    return lv >= 0 ? m : 0;
+}
+
+// Ranks within the wave: rk[r] (r < reff) = number of the wave's earlier items
+// with the same level.  run: the wave's level counts so far in LDS (zero at the start,
+// complete at the end); the first lane of a level's lanes advances it.
+template <int R>
+__device__ __forceinline__ void wave_rank(const int32_t (&lv)[R], int reff, int32_t (&rk)[R],
+                                          int32_t *run)
+{
+    run[threadIdx.x & (kWave - 1)] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         rk[r] = 0;
-        uint64_t todo = __ballot(lv[r] >= 0);
-        while (todo) {
-            const int first = __builtin_ctzll(todo);
-            const int32_t val = __builtin_amdgcn_readlane(lv[r], first);
-            const uint64_t m = __ballot(lv[r] == val);
-            const int32_t before = __builtin_amdgcn_readlane(runv, val);
-            if (lv[r] == val) rk[r] = before + (int32_t)lane_rank(m);
-            if (lane == val) runv += (int32_t)__popcll(m);
-            todo &= ~m;
+        if (r < reff) {   // uniform
+            const uint64_t m = same_level(lv[r]);
+            const uint32_t rank = lane_rank(m);
+            const int32_t before = lv[r] >= 0 ? run[lv[r]] : 0;
+            rk[r] = before + (int32_t)rank;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // every lane has read
+            if (lv[r] >= 0 && rank == 0) run[lv[r]] = before + (int32_t)__popcll(m);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     }
-    return runv;
 }
 
 // Exclusive scan of the per-wave level counts across the W waves, in wave
@@ -195,7 +213,7 @@ __global__ __launch_bounds__(kSwThreads) void sched_single_kernel(
     // an update's prefix must be exactly the bodies of level >= lmin
     if (level_end_old && threadIdx.x == 0 && level_end_old[lmin] != n_items) bad = true;
     if (bad) atomicOr(&bad_any, 1);
-    run[w][threadIdx.x & (kWave - 1)] = wave_rank<kRounds>(lv, rk);
+    wave_rank<kRounds>(lv, reff, rk, run[w]);
     __syncthreads();
     if (bad_any) {
         if (threadIdx.x == 0 && status) atomicOr(status, (uint32_t)NB_STATUS_BAD_LEVEL);
@@ -227,20 +245,13 @@ __global__ __launch_bounds__(kMwThreads) void sched_count_kernel(
     if (threadIdx.x < kMaxLevels) h[threadIdx.x] = 0;
     if (threadIdx.x == 0) bad_any = 0;
     __syncthreads();
-    const int lane = threadIdx.x & (kWave - 1);
-    int32_t body[kRounds], lv[kRounds];
-    bool bad = load_items<kRounds>(n, src, n_items, level, lmin, K,
-                                   (int64_t)blockIdx.x * kMwItems, kRounds, body, lv, copy);
+    int32_t body[kMwRounds], lv[kMwRounds];
+    bool bad = load_items<kMwRounds>(n, src, n_items, level, lmin, K,
+                                     (int64_t)blockIdx.x * kMwItems, kMwRounds, body, lv, copy);
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-        uint64_t todo = __ballot(lv[r] >= 0);
-        while (todo) {
-            const int first = __builtin_ctzll(todo);
-            const int32_t val = __builtin_amdgcn_readlane(lv[r], first);
-            const uint64_t m = __ballot(lv[r] == val);
-            if (lane == first) atomicAdd(&h[val], (int32_t)__popcll(m));
-            todo &= ~m;
-        }
+    for (int r = 0; r < kMwRounds; ++r) {
+        const uint64_t m = same_level(lv[r]);
+        if (lv[r] >= 0 && lane_rank(m) == 0) atomicAdd(&h[lv[r]], (int32_t)__popcll(m));
     }
     if (level_end_old && blockIdx.x == 0 && threadIdx.x == 0 && level_end_old[lmin] != n_items)
         bad = true;
@@ -257,9 +268,13 @@ __global__ __launch_bounds__(kMwThreads) void sched_scatter_kernel(
     int32_t K, int32_t nblk, const int32_t *hist, const int32_t *bad_blk, int32_t *dst,
     int32_t *level_end, uint32_t *status)
 {
-    constexpr int W = kMwThreads / kWave;   // 4 threads per level slot below
+    constexpr int W = kMwThreads / kWave;   // W threads per level slot below
     __shared__ int32_t run[W][kMaxLevels];
     __shared__ int32_t tot[kMaxLevels], above[kMaxLevels], before[kMaxLevels];
+    // the items' loads go out with those of the count rows
+    int32_t body[kMwRounds], lv[kMwRounds];
+    (void)load_items<kMwRounds>(n, src, n_items, level, lmin, K, (int64_t)blockIdx.x * kMwItems,
+                                kMwRounds, body, lv, nullptr);
     int bad = 0;
     for (int32_t b = threadIdx.x; b < nblk; b += kMwThreads) bad |= bad_blk[b];
     if (__syncthreads_or(bad)) {
@@ -270,7 +285,7 @@ __global__ __launch_bounds__(kMwThreads) void sched_scatter_kernel(
     const int w = threadIdx.x / kWave;
     {
         // level totals and the counts of blocks before this one: thread
-        // (L = tid / W, part = tid % W) sums a quarter of row L
+        // (L = tid / W, part = tid % W) sums its share of row L
         const int L = threadIdx.x / W, part = threadIdx.x % W;
         int32_t all = 0, bef = 0;
         if (L < K) {
@@ -292,10 +307,8 @@ __global__ __launch_bounds__(kMwThreads) void sched_scatter_kernel(
     }
     __syncthreads();
     level_offsets(tot, K, lmin, above, blockIdx.x == 0 ? level_end : nullptr);
-    int32_t body[kRounds], lv[kRounds], rk[kRounds];
-    (void)load_items<kRounds>(n, src, n_items, level, lmin, K, (int64_t)blockIdx.x * kMwItems,
-                              kRounds, body, lv, nullptr);
-    run[w][threadIdx.x & (kWave - 1)] = wave_rank<kRounds>(lv, rk);
+    int32_t rk[kMwRounds];
+    wave_rank<kMwRounds>(lv, kMwRounds, rk, run[w]);
     __syncthreads();
     int32_t excl;
     (void)wave_scan_first<W>(run, K, &excl);
@@ -304,7 +317,7 @@ __global__ __launch_bounds__(kMwThreads) void sched_scatter_kernel(
     if (Ls < K) run[ws][Ls] = above[Ls] + before[Ls] + excl;
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r)
+    for (int r = 0; r < kMwRounds; ++r)
         if (lv[r] >= 0) dst[run[w][lv[r]] + rk[r]] = body[r];
 }
 
@@ -313,16 +326,18 @@ struct SchedScratch {
 };
 
 // Scratch of the multi-work-group path: hist [K][nblk], bad_blk [nblk] and
-// (update) a copy of the prefix.
+// (update) a copy of the prefix; null for the single-work-group path, which
+// sorts up to kSwItems items without scratch.
 int sched_prepare(nb_ctx *ctx, int32_t n_items, int32_t K, bool in_place, SchedScratch &s)
 {
     s = SchedScratch{};
-    if (n_items <= kSwItems) return NB_OK;
+    if (n_items <= kSwFewItems) return NB_OK;
     const int32_t nblk = (n_items + kMwItems - 1) / kMwItems;
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t h = up(sizeof(int32_t) * (size_t)nblk * K);
     const size_t f = up(sizeof(int32_t) * (size_t)nblk);
     const size_t c = in_place ? up(sizeof(int32_t) * (size_t)n_items) : 0;
+    if (n_items <= kSwItems && ctx->scratch_bytes < h + f + c) return NB_OK;
     const int rc = nbrt::ensure_scratch(ctx, h + f + c);
     if (rc != NB_OK) return rc;
     char *p = (char *)ctx->scratch;
@@ -338,7 +353,7 @@ hipError_t sched_sort(nb_ctx *ctx, int64_t n, const int32_t *src, int32_t n_item
                       const int32_t *level, int32_t lmin, int32_t K, const int32_t *check_le,
                       const SchedScratch &s, int32_t *dst, int32_t *level_end, uint32_t *status)
 {
-    if (n_items <= kSwItems) {
+    if (!s.hist) {
         hipLaunchKernelGGL(sched_single_kernel, dim3(1), dim3(kSwThreads), 0, ctx->stream, n,
                            src, n_items, level, lmin, K, check_le, dst, level_end, status);
         return hipGetLastError();
