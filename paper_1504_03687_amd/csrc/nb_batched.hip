@@ -620,6 +620,7 @@ extern "C" int nb_regular_force_batched(nb_ctx *ctx, int32_t n_clusters, const i
     hit->last_use = ++g_use_clock;
     ctx->last_redo_counter = hit->redo_k > 0.0 ? hit->args.f.redo_count : nullptr;
     const nb::BShape &sh = nb::kBatchedShape[hit->shape];
+    ctx->plan_note.set = false;
     std::snprintf(ctx->last_plan, sizeof ctx->last_plan,
                   "batched clusters=%d items=%d grid=%d tile=%d lanes=%d rows_per_lane=%d "
                   "items_per_cu=%d merge_rows=%d shape=%s prec=%s%s",

@@ -36,6 +36,14 @@ struct PendingTiming {
     int cls;
     hipEvent_t start, stop;
 };
+// What nb_ctx_last_plan describes of a single-block call (the text is made
+// when it is asked for, not on every call).
+struct PlanNote {
+    bool set;
+    nb::Plan p;
+    int64_t split_len;
+    bool asked_mixed, mixed, fixed, packed;
+};
 struct BatchedCache;   // defined in nb_batched.hip
 void batched_release(nb_ctx *ctx);
 }  // namespace nbrt
@@ -58,6 +66,7 @@ struct nb_ctx {
     nb::Plan forced{};
     bool has_forced = false;
     char last_plan[256] = "none";
+    nbrt::PlanNote plan_note{};
     std::map<std::tuple<int, int64_t, int64_t>, nb::Plan> tuned;
     // mixed precision: target relative error per row and safety factor of
     // the rounding-error estimate that triggers an FP64 recompute (tol 0: off)

@@ -252,6 +252,15 @@ int nb_ctx_set_plan(nb_ctx *ctx, int mapping, int rows_per_lane, int splits)
 int nb_ctx_last_plan(nb_ctx *ctx, char *buf, int len)
 {
     if (!ctx || !buf || len <= 0) return NB_ERR_INVALID_ARG;
+    if (ctx->plan_note.set) {
+        const nbrt::PlanNote &k = ctx->plan_note;
+        std::snprintf(ctx->last_plan, sizeof ctx->last_plan,
+                      "mapping=%d rows_per_lane=%d splits=%d split_len=%lld prec=%s%s%s%s",
+                      k.p.mapping, k.p.rows_per_lane, k.p.splits, (long long)k.split_len,
+                      k.mixed ? "mixed" : "fp64",
+                      k.p.f64 && k.asked_mixed ? " requested=mixed" : "",
+                      k.fixed ? " workspace=fixed" : "", k.packed ? " bodies=packed" : "");
+    }
     std::snprintf(buf, (size_t)len, "%s", ctx->last_plan);
     return NB_OK;
 }
@@ -351,6 +360,7 @@ static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const do
     if (n_i == 0) {
         e = nb::launch_clear_words(overflow, nullptr, ctx->stream);
         if (e != hipSuccess) return hip_fail(ctx, e);
+        ctx->plan_note.set = false;
         std::snprintf(ctx->last_plan, sizeof ctx->last_plan, "empty");
         return NB_OK;
     }
@@ -446,11 +456,8 @@ static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const do
         if (e != hipSuccess) return hip_fail(ctx, e);
     }
     nb::force_bind_scratch(fa, (char *)base + redo_bytes);
-    std::snprintf(ctx->last_plan, sizeof ctx->last_plan,
-                  "mapping=%d rows_per_lane=%d splits=%d split_len=%lld prec=%s%s%s%s", p.mapping,
-                  p.rows_per_lane, p.splits, (long long)split_len, mixed ? "mixed" : "fp64",
-                  p.f64 && prec == NB_MIXED ? " requested=mixed" : "",
-                  fixed ? " workspace=fixed" : "", pack_bytes ? " bodies=packed" : "");
+    ctx->plan_note = nbrt::PlanNote{true, p, split_len, prec == NB_MIXED, mixed, fixed != nullptr,
+                                    pack_bytes != 0};
 
     // timing events are created on demand, so the allocation-free path is
     // never timed
