@@ -163,10 +163,9 @@ extern "C" int nb_autotune(nb_ctx *ctx, int64_t n, const char *cache_path, int f
                     // the automatic split count of this mapping, halved and doubled
                     const int64_t base = default_splits(ctx, n, ni, mapping, rows);
                     for (int64_t sc : {base / 2, base, base * 2}) {
-                        const int64_t maxs =
-                            max_splits(n, mapping, pack_pays(mapping, rows, n, ni));
+                        const int64_t maxs = max_splits(ctx, n, ni, mapping, rows);
                         const int s = (int)std::max<int64_t>(1, std::min<int64_t>(sc, maxs));
-                        nb::Plan p{mapping, rows, s, 0, fine_splits(mapping, s, n)};
+                        nb::Plan p{mapping, rows, s, 0, split_step(mapping, s, n)};
                         bool dup = false;
                         for (auto &q : cands)
                             dup |= q.mapping == p.mapping && q.rows_per_lane == p.rows_per_lane &&

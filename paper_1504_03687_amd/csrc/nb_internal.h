@@ -113,7 +113,8 @@ struct Plan {
     int rows_per_lane;  // mapping 1: 1, 2, 4;  mapping 2: rows per wave 1, 2, 4
     int splits;         // j-ranges (mapping 1: per work-group; mapping 2: per wave)
     int f64;            // 1: a mixed-precision request runs the FP64 kernels
-    int fine;           // 1 (mapping 1): splits in steps of kWave bodies, not kTile
+    int step;           // row-per-lane mappings: splits in steps of this many bodies
+                        // (0: kTile in mapping 1, kWave in mapping 3)
 };
 
 // Scratch bytes needed for a plan (0 when splits == 1).

@@ -37,13 +37,38 @@ bool pack_pays(int mapping, int rows_per_lane, int64_t n, int32_t n_i)
            n * (int64_t)n_i > (int64_t(1) << 27);
 }
 
-// Largest useful split count: splits of about 4 waves' worth of bodies in the
-// wave mapping, 64 bodies in the row-per-lane mappings through LDS (a lane is
-// a serial chain of its split's pairs, so small blocks want short splits) and
-// 512 in the packed launches, whose blocks have enough row tiles.
-int64_t max_splits(int64_t n, int mapping, bool packed)
+// Row groups of a launch: waves in mappings 2 and 3, work-groups of four
+// waves in mapping 1.
+static int64_t row_groups(int32_t n_i, int mapping, int rows)
 {
-    const int64_t unit = mapping == 2 ? 4 * nb::kWave : packed ? 2 * nb::kTile : nb::kWave;
+    const int64_t per = mapping == 2 ? rows : mapping == 3 ? nb::kWave : (int64_t)rows * nb::kBlock;
+    return std::max<int64_t>(1, (n_i + per - 1) / per);
+}
+
+// Bodies of the shortest useful split: 256 in the wave mapping, 512 in the
+// packed launches, whose blocks have enough row tiles, and 64 in the
+// row-per-lane mappings through LDS: a lane is a serial chain of its split's
+// pairs, so small blocks want short splits, at the price of a record per
+// split and row in the merge.  32 (the run of the folds) where splits of 64
+// come to at most one wave per SIMD: whole calls, splits of 64 against 32,
+// FP64 / mixed, 1024 rows of 1024 24.0 / 36.0 against 17.4 / 29.8 us, 256 of
+// 4096 22.7 / 32.3 against 18.3 / 28.1, 1024 of 4096 (one wave per SIMD) 26.4
+// / 38.6 against 24.7 / 37.6; past that it loses, 4096 of 4096 (four waves)
+// 46.6 / 51.2 against 50.3 / 58.3.
+static int64_t min_split(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, int rows)
+{
+    if (mapping == 2) return 4 * nb::kWave;
+    if (pack_pays(mapping, rows, n, n_i)) return 2 * nb::kTile;
+    const int64_t simds = 4 * (int64_t)(ctx->cu_count > 0 ? ctx->cu_count : 256);
+    const int64_t waves = row_groups(n_i, mapping, rows) * (mapping == 1 ? nb::kBlock / nb::kWave : 1) *
+                          ((n + nb::kWave - 1) / nb::kWave);
+    return waves <= simds ? nb::kFold : nb::kWave;
+}
+
+// Largest useful split count.
+int64_t max_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, int rows)
+{
+    const int64_t unit = min_split(ctx, n, n_i, mapping, rows);
     return std::max<int64_t>(1, (n + unit - 1) / unit);
 }
 
@@ -53,7 +78,7 @@ int64_t max_splits(int64_t n, int mapping, bool packed)
 //    total, and at most kWaveMaxSplits splits per row; more splits only add
 //    merge work (measured at N = 2^20, n_i = 1 .. 255).
 //  * row per lane through LDS (mapping 3 with 64 rows a work-group, mapping 1
-//    with 256): about 8 waves per SIMD in total, down to 64 bodies per split,
+//    with 256): about 8 waves per SIMD in total, down to min_split bodies,
 //    at most kRowWaveMaxSplits splits.
 //    A lane that is alone on its SIMD takes 150 to 200 ns per pair, so long
 //    splits leave the chip waiting for few waves.  Whole calls, FP64, with
@@ -73,25 +98,18 @@ int64_t default_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, i
 {
     const int64_t cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
     const bool packed = pack_pays(mapping, rows, n, n_i);
-    int64_t units, target;
-    if (mapping == 2) {
-        units = (n_i + rows - 1) / rows;                       // row groups, one wave each
-        target = cus * 8;
-    } else if (mapping == 3) {
-        units = (n_i + nb::kWave - 1) / nb::kWave;             // one-wave work-groups
-        target = cus * 32;
-    } else {
-        units = (n_i + (int64_t)rows * nb::kBlock - 1) / ((int64_t)rows * nb::kBlock);
-        // work-groups of four waves
-        target = cus * (!packed ? 8 : n * (int64_t)n_i > (int64_t(1) << 32) ? 64 : 32);
-    }
+    const int64_t u = row_groups(n_i, mapping, rows);
+    // in row groups
+    const int64_t target = cus * (mapping == 2   ? 8
+                                  : mapping == 3 ? 32
+                                  : !packed      ? 8
+                                  : n * (int64_t)n_i > (int64_t(1) << 32) ? 64 : 32);
     // mapping 2 rounds down: with only ~2 work-groups per CU, one wave group
     // past the target puts a third work-group on some CU and stretches the
     // whole launch by half (72 rows at N = 2^20: 2052 waves took 257 us,
     // against 152 us for 64 rows in 2048 waves).  finish_plan can only lower
     // the count further.  The others round up: at many waves per CU one extra
     // costs little.
-    const int64_t u = std::max<int64_t>(units, 1);
     int64_t s = mapping == 2 ? std::max<int64_t>(1, target / u) : (target + u - 1) / u;
     // mapping 2 with few row groups: at most kWaveMaxSplits splits.  Each
     // split adds a partial to every row's merge, which one work-group reads;
@@ -101,14 +119,16 @@ int64_t default_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, i
     // mapping 3, 64 rows of 2^20: 107 us at 4096 splits, 114 at 8192.
     if (mapping == 2) s = std::min(s, kWaveMaxSplits);
     if (mapping != 2) s = std::min(s, kRowWaveMaxSplits);
-    return std::max<int64_t>(1, std::min(s, max_splits(n, mapping, packed)));
+    return std::max<int64_t>(1, std::min(s, max_splits(ctx, n, n_i, mapping, rows)));
 }
 
-// Whether a tuned split count asks for splits finer than mapping 1's steps of
-// kTile bodies (see Plan::fine).
-int fine_splits(int mapping, int64_t splits, int64_t n)
+// Plan::step of a split count chosen for a launch: the coarsest that can give
+// that many splits.
+int split_step(int mapping, int64_t splits, int64_t n)
 {
-    return mapping == 1 && splits * nb::kTile > n;
+    if (mapping == 2) return 0;
+    if (splits > (n + nb::kWave - 1) / nb::kWave) return nb::kFold;
+    return mapping == 1 && splits * nb::kTile > n ? nb::kWave : 0;
 }
 
 // Mappings of the automatic plan by block size, from steady-state whole calls:
@@ -141,7 +161,7 @@ Plan auto_plan(const nb_ctx *ctx, int64_t n, int32_t n_i, bool mixed)
     auto it = ctx->tuned.find(std::make_tuple((int)mixed, bucket_log2(n), bucket_log2(n_i)));
     if (it != ctx->tuned.end()) {
         Plan p = it->second;
-        p.fine = fine_splits(p.mapping, p.splits, n);
+        p.step = split_step(p.mapping, p.splits, n);
         return p;
     }
     if (mixed && n_i <= kMixedAsF64MaxRows) {
@@ -159,7 +179,7 @@ Plan auto_plan(const nb_ctx *ctx, int64_t n, int32_t n_i, bool mixed)
         const int64_t pad3 = ((int64_t)n_i + nb::kWave - 1) / nb::kWave * nb::kWave;
         const bool packed = pack_pays(1, 1, n, n_i);
         p.mapping = !packed && pad1 * 5 > pad3 * 6 ? 3 : 1;
-        p.fine = p.mapping == 1 && !packed;
+        if (!packed) p.step = (int)min_split(ctx, n, n_i, p.mapping, p.rows_per_lane);
     }
     p.splits = (int)default_splits(ctx, n, n_i, p.mapping, p.rows_per_lane);
     return p;
@@ -169,7 +189,7 @@ Plan auto_plan(const nb_ctx *ctx, int64_t n, int32_t n_i, bool mixed)
 void finish_plan(Plan &p, int64_t n, int32_t n_i, int64_t *split_len)
 {
     if (p.splits < 1) p.splits = 1;
-    const int64_t unit = p.mapping == 1 && !p.fine ? nb::kTile : nb::kWave;
+    const int64_t unit = p.step ? p.step : p.mapping == 1 ? nb::kTile : nb::kWave;
     const int64_t units = (n + unit - 1) / unit;
     int64_t per = (units + p.splits - 1) / p.splits;
     if (per < 1) per = 1;

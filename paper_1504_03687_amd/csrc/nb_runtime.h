@@ -103,9 +103,9 @@ hipError_t timed_end(nb_ctx *ctx, int cls, hipEvent_t *ev);
 int64_t bucket_log2(int64_t v);
 double redo_k(const nb_ctx *ctx);
 nb::Plan auto_plan(const nb_ctx *ctx, int64_t n, int32_t n_i, bool mixed);
-int64_t max_splits(int64_t n, int mapping, bool packed);
+int64_t max_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, int rows);
 int64_t default_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, int rows);
 bool pack_pays(int mapping, int rows_per_lane, int64_t n, int32_t n_i);
-int fine_splits(int mapping, int64_t splits, int64_t n);
+int split_step(int mapping, int64_t splits, int64_t n);
 void finish_plan(nb::Plan &p, int64_t n, int32_t n_i, int64_t *split_len);
 }  // namespace nbrt

@@ -366,10 +366,12 @@ static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const do
     }
     Plan p = auto_plan(ctx, n, n_i, prec == NB_MIXED);
     if (ctx->has_forced) {
+        // the automatic step belongs to the automatic splits and mapping
+        if (ctx->forced.splits || (ctx->forced.mapping && ctx->forced.mapping != p.mapping))
+            p.step = ctx->forced.step;
         if (ctx->forced.mapping) p.mapping = ctx->forced.mapping;
         if (ctx->forced.rows_per_lane) p.rows_per_lane = ctx->forced.rows_per_lane;
         if (ctx->forced.splits) p.splits = ctx->forced.splits;
-        if (ctx->forced.splits || p.mapping != 1) p.fine = ctx->forced.fine;
         p.f64 = ctx->forced.f64;   // a forced plan runs the requested kernels
     }
     const bool mixed = prec == NB_MIXED && !p.f64;

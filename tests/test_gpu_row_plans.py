@@ -72,11 +72,13 @@ def test_packed_equals_lds_pass(n, n_i, splits, prec):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
-@pytest.mark.parametrize("n,n_i,mapping", [(65, 64, 3), (1000, 250, 1), (1024, 1024, 1),
-                                           (4033, 300, 3), (4097, 1000, 1)])
-def test_short_splits(n, n_i, mapping, prec):
-    """Automatic plans of small blocks cut the j-set into splits of 64 bodies:
-    a part of a 256-body tile in mapping 1, a ragged last split."""
+@pytest.mark.parametrize("n,n_i,mapping,step", [
+    (33, 33, 2, 0), (65, 64, 3, 32), (1000, 250, 1, 32), (1024, 1024, 1, 32), (4033, 300, 3, 32),
+    (4096, 1000, 1, 32), (4097, 1000, 1, 64), (9000, 700, 1, 64)])
+def test_short_splits(n, n_i, mapping, step, prec):
+    """Automatic plans of small blocks cut the j-set into splits of 32 bodies
+    up to one wave per SIMD (in splits of 64), and of 64 above: a part of a
+    256-body tile in mapping 1, a ragged last split."""
     say(f"short splits n={n} n_i={n_i} {prec}")
     rng = np.random.default_rng(n + 1)
     s = W.small_state(400 + n_i, n, k_nn=20)
@@ -88,8 +90,9 @@ def test_short_splits(n, n_i, mapping, prec):
     try:
         auto = nb.regular_force(*args, ctx=ctx)
         plan = ctx.last_plan()
-        assert f"mapping={mapping}" in plan and "split_len=64" in plan, plan
-        assert f"splits={(n + 63) // 64}" in plan, plan
+        assert f"mapping={mapping}" in plan, plan
+        if step:
+            assert f"split_len={step}" in plan and f"splits={-(-n // step)}" in plan, plan
         ctx.set_plan(1, 1, 1)
         one = nb.regular_force(*args, ctx=ctx)
         torch.cuda.synchronize()
