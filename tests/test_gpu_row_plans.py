@@ -137,3 +137,34 @@ def test_near_queue_rows_do_not_depend_on_their_wave():
         assert np.array_equal(a[k][p], b[k])
     rows = np.concatenate([np.arange(0, 64), rng.choice(n_i, 32, replace=False)])
     compare_force(one, x, v, m, ib, rs2, cap, TOL_MIXED, rows=rows)
+
+
+@pytest.mark.parametrize("n,rows", [(300, 300), (2048, 41), (2048, 2048), (2049, 200)])
+def test_refined_rows_of_one_chunk(n, rows):
+    """Refinement of every row: a row of one chunk (2048 bodies) goes straight
+    to the outputs, longer ones through chunk partials; single and batched
+    calls give the same bits, at FP64 accuracy, call after call."""
+    say(f"refinement n={n} rows={rows}")
+    rng = np.random.default_rng(n + rows)
+    s = W.small_state(800 + rows, n, k_nn=20)
+    ib = rng.choice(n, rows, replace=False).astype(np.int32)
+    rs2 = s["rs2"][ib]
+    cap = 24
+    args = (dev(s["x"]), dev(s["v"]), dev(s["m"]), dev(ib), dev(rs2))
+    ctx = nb.Context(0)
+    try:
+        ctx.set_plan(1, 1, 0)    # the mixed kernel at every block size
+        ctx.set_mixed_tolerance(1e-30, 32.0)
+        runs = []
+        for _ in range(2):
+            res = nb.regular_force(*args, cap, "mixed", ctx=ctx)
+            assert ctx.last_refined_rows() == rows
+            runs.append([host(t) for t in res])
+        compare_force(res, s["x"], s["v"], s["m"], ib, rs2, cap, TOL_FP64)
+        bat = nb.regular_force_batched([0, n], [0, rows], *args, cap, "mixed", ctx=ctx)
+        assert ctx.last_refined_rows() == rows
+        for k in (0, 1):
+            assert np.array_equal(runs[0][k], runs[1][k])
+            assert np.array_equal(host(bat[k]), runs[0][k])
+    finally:
+        ctx.close()
