@@ -36,12 +36,8 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(IR == 1 && T
 {
     __shared__ JBody tile[2][T];
     __shared__ int32_t s_item;
-    for (;;) {
-        if (threadIdx.x == 0) s_item = atomicAdd(A.queue, 1);
-        __syncthreads();
-        const int32_t it = __builtin_amdgcn_readfirstlane(s_item);
-        __syncthreads();   // every lane has read s_item before it is replaced
-        if (it >= A.n_items) break;
+    int32_t it = (int32_t)blockIdx.x;   // the first item; the queue hands out the others
+    while (it < A.n_items) {
         const BItem I = A.items[it];
         const BCluster C = A.clusters[I.cluster];
         const int64_t j0 = C.j_begin + (int64_t)I.split * C.split_len;
@@ -50,13 +46,22 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(IR == 1 && T
                      (int64_t)C.splits};
         rows_pass<MIXED, IR, T, NB>(A.f, tile, I.row0, (int64_t)C.row_begin + C.n_rows, j0, j1,
                                     d, C.near);
+        if (A.n_items <= (int32_t)gridDim.x) break;
+        if (threadIdx.x == 0) s_item = (int32_t)gridDim.x + atomicAdd(A.queue, 1);
+        __syncthreads();
+        it = __builtin_amdgcn_readfirstlane(s_item);
+        __syncthreads();   // every lane has read s_item before it is replaced
     }
 }
 
 // The scalar-operand pass (rows_pass_packed) over the packed ensemble: an item
 // is one wave's kWave rows over one j-range, and every wave pulls its own, so
 // no wave waits for another of its work-group and a cluster's last row tile
-// leaves at most kWave - 1 lanes idle.  Bound by VALU issue, as the
+// leaves at most kWave - 1 lanes idle.  A wave's first item is its own number
+// and an ensemble of no more items than waves never touches the queue: one
+// word that every wave adds to answers one pull in about 20 ns (32 clusters of
+// 1000 bodies in 8192 items took 208 us and take 153; the 96 clusters below
+// 5705 and 5583).  Bound by VALU issue, as the
 // single-block kernel: 96 clusters of 1024 to 32768 bodies (5.8e9 pairs,
 // mixed) took 6113 us a call through LDS and take 5825.
 // The mixed kernel is held to five waves per SIMD (96 VGPRs, as the
@@ -64,8 +69,22 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(IR == 1 && T
 template <bool MIXED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MIXED ? 5 : 4))) void batched_packed_kernel(BatchArgs A)
 {
-    for (;;) {
-        // The whole wave comes back here together before lane 0 pulls.  The
+    constexpr int32_t kWaves = kBlock / kWave;
+    const int32_t waves = (int32_t)gridDim.x * kWaves;
+    // the first item; the queue hands out the others
+    int32_t it = (int32_t)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    while (it < A.n_items) {
+        const BItem I = load_uniform(A.items + it);
+        const BCluster C = load_uniform(A.clusters + I.cluster);
+        const int64_t j0 = C.j_begin + (int64_t)I.split * C.split_len;
+        const int64_t j1 = j0 + C.split_len < C.j_end ? j0 + C.split_len : C.j_end;
+        const Dest d{C.splits == 1, C.slot_base + (int64_t)I.split, (int64_t)C.row_begin,
+                     (int64_t)C.splits};
+        rows_pass_packed<MIXED>(A.f, A.f.packed + C.rec_base + (j0 - C.j_begin), I.row0,
+                                (int64_t)C.row_begin + C.n_rows, j0, j1, d, C.near,
+                                near_queue<MIXED>());
+        if (A.n_items <= waves) break;
+        // The whole wave arrives here together before lane 0 pulls.  The
         // barrier emits nothing, but code around it is not duplicated per
         // lane, and the opaque lane number keeps the compiler from joining
         // this branch with an earlier one on the same condition: without
@@ -76,17 +95,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MIXED ? 
         opaque(lane);
         int32_t next = 0;
         if (lane == 0) next = atomicAdd(A.queue, 1);
-        const int32_t it = __builtin_amdgcn_readfirstlane(next);
-        if (it >= A.n_items) break;
-        const BItem I = load_uniform(A.items + it);
-        const BCluster C = load_uniform(A.clusters + I.cluster);
-        const int64_t j0 = C.j_begin + (int64_t)I.split * C.split_len;
-        const int64_t j1 = j0 + C.split_len < C.j_end ? j0 + C.split_len : C.j_end;
-        const Dest d{C.splits == 1, C.slot_base + (int64_t)I.split, (int64_t)C.row_begin,
-                     (int64_t)C.splits};
-        rows_pass_packed<MIXED>(A.f, A.f.packed + C.rec_base + (j0 - C.j_begin), I.row0,
-                                (int64_t)C.row_begin + C.n_rows, j0, j1, d, C.near,
-                                near_queue<MIXED>());
+        it = waves + __builtin_amdgcn_readfirstlane(next);
     }
 }
 
