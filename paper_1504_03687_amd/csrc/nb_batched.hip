@@ -245,6 +245,7 @@ struct BatchedCache {
     void *dmem = nullptr;
     nb::BatchArgs args{};
     bool packed = false;
+    bool coarse = false;      // splits of kSplitLen only (the finer ones found no memory)
     int grid = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -281,6 +282,27 @@ static bool batched_pack_pays(const BatchedCache *c)
     return c->shape == 0 && c->j_off.back() >= 256 * clusters;
 }
 
+// Split lengths of an ensemble, in bodies: kSplitLen where the chip is full,
+// half of it up to kTailWaves waves per CU (the longest items would end long
+// after the others), and halved further, down to kMinSplitLen, while there are
+// fewer than kFullWaves waves per CU: a lane is a serial chain of its split's
+// pairs, and few clusters leave the SIMDs to single waves.  Each split costs a
+// record per row in the merge, so longer ones are better wherever the waves
+// suffice.  Whole calls (mixed / FP64), splits of 2048 / this rule: 4 clusters
+// of 600 to 4000 bodies 577 / 60 us and 626 / 56, 12 of 1000 to 8000 718 / 154
+// and 758 / 186, 32 of 4000 701 / 544 and 720 / 643, 160 of 600 to 4000 798 /
+// 585 and 1052 / 817, 12 of 3000 to 32768 1614 / 1449 and 2087 / 1973; at 165
+// waves per CU (96 of 1024 to 32768) 5587 against 5818 us with 1024.
+constexpr int64_t kSplitLen = 2048, kMinSplitLen = 64;
+constexpr int64_t kTailWaves = 64, kFullWaves = 11;
+
+// Splits of at most len bodies of a cluster of nc bodies; less than 7/4 of
+// len stays whole (and needs no merge).
+static int64_t split_cap(int64_t nc, int64_t len)
+{
+    return 4 * nc < 7 * len ? 1 : (nc + len - 1) / len;
+}
+
 // Builds the work list, uploads metadata, and captures the launch graph.
 static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, bool mixed)
 {
@@ -289,18 +311,37 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     int64_t slots = 0;
     // automatic splits: items of at most ~1/(items_per_cu per CU) of the
     // total pair work, so the queue's tail is short (as for single blocks),
-    // with splits of at least 8 split units
+    // and not shorter than the ensemble's split length
     double total_work = 0.0;
     for (int32_t k = 0; k < C; ++k)
         total_work += (double)(c->i_off[k + 1] - c->i_off[k]) * (double)(c->j_off[k + 1] - c->j_off[k]);
-    const double item_work =
-        std::max(1.0, total_work / ((ctx->cu_count > 0 ? ctx->cu_count : 256) *
-                                    (double)c->items_per_cu));
+    const int64_t cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
+    const double item_work = std::max(1.0, total_work / (cus * (double)c->items_per_cu));
     const nb::BShape sh = nb::kBatchedShape[c->shape];
     const int64_t rows_per_item = (int64_t)sh.rows_per_lane * sh.lanes;
     const int64_t n_total = c->j_off[(size_t)C];
     const size_t b_rec = r256((size_t)(n_total + C * nb::kRecPad) * sizeof(nb::JRec));
-    constexpr int64_t U = nb::kSplitUnit;
+    const auto auto_splits = [&](int32_t k, int64_t len) {
+        const int64_t nc = c->j_off[k + 1] - c->j_off[k];
+        const int64_t rc = c->i_off[k + 1] - c->i_off[k];
+        const double rows = (double)std::min<int64_t>(rc, rows_per_item);
+        const int64_t S = (int64_t)std::ceil(rows * (double)nc / item_work);
+        return std::max<int64_t>(1, std::min<int64_t>(S, split_cap(nc, len)));
+    };
+    // waves of kWave rows at splits of len bodies
+    const auto waves = [&](int64_t len) {
+        int64_t w = 0;
+        for (int32_t k = 0; k < C; ++k)
+            w += (c->i_off[k + 1] - c->i_off[k] + nb::kWave - 1) / nb::kWave * auto_splits(k, len);
+        return w;
+    };
+    int64_t len = kSplitLen;
+    if (c->forced_splits <= 0 && !c->coarse) {
+        if (waves(len) < kTailWaves * cus) len /= 2;
+        while (len > kMinSplitLen && waves(len) < kFullWaves * cus) len /= 2;
+    }
+    const int64_t U = c->forced_splits > 0 ? nb::kSplitUnit
+                                           : std::min<int64_t>(len, nb::kSplitUnit);
     for (int32_t k = 0; k < C; ++k) {
         const int64_t nc = c->j_off[k + 1] - c->j_off[k];
         const int64_t rc = c->i_off[k + 1] - c->i_off[k];
@@ -310,9 +351,7 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
         } else if (c->forced_splits > 0) {
             S = std::min<int64_t>(c->forced_splits, (nc + U - 1) / U);
         } else {
-            const double rows = (double)std::min<int64_t>(rc, rows_per_item);
-            S = (int64_t)std::ceil(rows * (double)nc / item_work);
-            S = std::max<int64_t>(1, std::min<int64_t>(S, nc / (8 * U)));
+            S = auto_splits(k, len);
         }
         const int64_t tiles = std::max<int64_t>(1, (nc + U - 1) / U);
         const int64_t per = (tiles + S - 1) / S;
@@ -441,8 +480,7 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     A.n_merge_rows = (int32_t)merge_rows.size();
     A.max_splits = 1;
     for (int32_t k = 0; k < C; ++k) A.max_splits = std::max(A.max_splits, cl[(size_t)k].splits);
-    const int cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
-    c->grid = cus * nb::batched_max_blocks_per_cu(mixed, c->shape, c->packed);
+    c->grid = (int)cus * nb::batched_max_blocks_per_cu(mixed, c->shape, c->packed);
     // work-groups past the last item (a packed one pulls an item per wave) would do nothing
     const int pulls = c->packed ? nb::kBlock / nb::kWave : 1;
     c->grid = std::max(1, std::min(c->grid, (A.n_items + pulls - 1) / pulls));
@@ -615,6 +653,10 @@ extern "C" int nb_regular_force_batched(nb_ctx *ctx, int32_t n_clusters, const i
         f.status = status;
         c->packed = batched_pack_pays(c);
         rc = build_cache(ctx, c, f, mixed);
+        if (rc == NB_ERR_OOM && fsplits <= 0) {   // no room for the slots of short splits
+            c->coarse = true;
+            rc = build_cache(ctx, c, f, mixed);
+        }
         if (rc == NB_ERR_OOM && c->packed) {   // no room for the packed bodies
             c->packed = false;
             rc = build_cache(ctx, c, f, mixed);

@@ -206,9 +206,9 @@ struct BShape {
 constexpr int kBatchedShapes = 6;
 constexpr BShape kBatchedShape[kBatchedShapes] = {
     {256, 256, 1}, {256, 256, 2}, {128, 128, 1}, {64, 64, 1}, {512, 512, 1}, {256, 512, 1}};
-// j-splits of the batched ensemble are multiples of this many bodies, for
-// every shape, so a cluster's split boundaries (and so its sums) depend only
-// on its split count.
+// j-splits of the batched ensemble are multiples of this many bodies (or of
+// the ensemble's split length, where that is shorter), for every shape, so a
+// cluster's split boundaries (and so its sums) depend only on its split count.
 constexpr int kSplitUnit = 256;
 // Index of a shape in kBatchedShape, or -1.
 int batched_shape_index(int tile, int lanes, int rows_per_lane);
