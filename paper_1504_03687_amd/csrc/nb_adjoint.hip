@@ -228,15 +228,33 @@ __global__ __launch_bounds__(kWave * W) __attribute__((amdgpu_waves_per_eu(R == 
 
 // Sums the row partials of a panel over the body blocks (fixed order) into
 // row_part[6][n_i], enters the rows in their bodies' index and flags bad
-// indices.  One lane per component of a row.
-__global__ __launch_bounds__(256) void adj_rows_reduce(AdjointArgs a, AdjPlan p)
+// indices.  A work-group takes 64 components of rows; its waves share the body
+// blocks (a lane that adds them all is a chain of memory round trips, and few
+// rows are few lanes: 512 blocks of 1024 rows 123 us with one lane per
+// component, 8 so).
+constexpr int kReduceWaves = 16;
+
+__global__ __launch_bounds__(kWave * kReduceWaves) void adj_rows_reduce(AdjointArgs a, AdjPlan p)
 {
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    __shared__ double part[kReduceWaves][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t k = (int64_t)blockIdx.x * kWave + lane;
     const int64_t total = 6 * (int64_t)p.panel_rows;
+    const int32_t share = (p.body_blocks + kReduceWaves - 1) / kReduceWaves;
+    const int32_t q1 = p.body_blocks < (w + 1) * share ? p.body_blocks : (w + 1) * share;
+    double s = 0.0;
+    if (k < total)
+#pragma unroll 8
+        for (int32_t q = w * share; q < q1; ++q) s += p.row_partial[(int64_t)q * total + k];
+    part[w][lane] = s;
+    __syncthreads();
+    if (w > 0) return;
     bool bad = false;
     if (k < total) {
-        double s = 0.0;
-        for (int32_t q = 0; q < p.body_blocks; ++q) s += p.row_partial[(int64_t)q * total + k];
+        s = 0.0;
+#pragma unroll
+        for (int u = 0; u < kReduceWaves; ++u) s += part[u][lane];
         const int64_t comp = k / p.panel_rows, row = k - comp * p.panel_rows + p.panel_row0;
         a.row_part[comp * a.n_i + row] = s;
         if (comp == 0) {
@@ -336,9 +354,12 @@ void launch_pairs(const AdjointArgs &a, const AdjPlan &p, int64_t items, hipStre
 
 // Rows per block, LDS tile, bodies per block and row blocks per panel.  Two
 // rows per lane (512 a block) where there are enough rows for it, one (256)
-// else, and tiles of 64 bodies where few bodies make the serial chain of a tile
-// the whole call: 1024 rows of 1024 35 us with 64, 57 with 128; 1024 of 16384
-// 111 against 92; 4096 of 16384 234 with two rows per lane, 252 with one.
+// else: 4096 of 16384 234 us with two, 252 with one.  Tiles of 64 bodies where
+// there are few bodies, or fewer than two work-groups per CU with tiles of
+// 128, and the serial chain of a tile is much of the call: 1024 rows of 1024
+// 35 us with 64, 57 with 128; 256 of 16384 33 and 49; 1024 of 12000 (376
+// work-groups) 61 and 72; 1024 of 16384 (512) 75.5 both; 4096 of 16384 222 and
+// 217; 2500 of 65536 517 and 497.
 // Body blocks for about 24 items per CU (48 give the same time and twice the
 // row partials), entries of at most kAdjointBytes by smaller panels, then by
 // longer body blocks; a call under a scratch limit needs no more than
@@ -347,8 +368,8 @@ AdjointShape adjoint_shape(int64_t n, int32_t n_i, int cus, size_t limit)
 {
     AdjointShape sh{};
     sh.row_block = n_i >= 2048 && n > 8192 ? 512 : 256;
-    sh.tile = n > 8192 ? 128 : 64;
     const int64_t blocks = std::max<int64_t>(1, ((int64_t)n_i + sh.row_block - 1) / sh.row_block);
+    sh.tile = n > 8192 && blocks * ((n + 127) / 128) >= 2 * (int64_t)cus ? 128 : 64;
     const int64_t want = ((int64_t)cus * 24 + blocks - 1) / blocks;
     const int64_t tiles = (n + sh.tile - 1) / sh.tile;
     sh.body_len = (tiles + want - 1) / want * sh.tile;
@@ -411,8 +432,8 @@ hipError_t launch_adjoint(const AdjointArgs &a0, const AdjointShape &sh, void *s
         else
             launch_pairs<1, 4, 64>(a, p, items, s);
         const int64_t tot = 6 * (int64_t)p.panel_rows;
-        hipLaunchKernelGGL(adj_rows_reduce, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s,
-                           a, p);
+        hipLaunchKernelGGL(adj_rows_reduce, dim3((unsigned)((tot + kWave - 1) / kWave)),
+                           dim3(kWave * kReduceWaves), 0, s, a, p);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

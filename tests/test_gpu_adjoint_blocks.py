@@ -48,7 +48,8 @@ def _run(args, limit=0):
 
 @pytest.mark.parametrize("n,n_i,dup", [(63, 1, False), (64, 64, False), (65, 130, True),
                                        (257, 256, False), (1000, 257, True), (8192, 300, False),
-                                       (8193, 255, False), (8300, 2049, True)])
+                                       (8193, 255, False), (8300, 2049, True),
+                                       (9000, 70, True), (9500, 1700, False)])
 def test_adjoint_block_edges(n, n_i, dup):
     say(f"adjoint blocks n={n} n_i={n_i}")
     args = _case(n, n_i, n + n_i, dup)
