@@ -374,22 +374,49 @@ __device__ __forceinline__ void block_tree_sum(double e, double *wg_sum)
 // Adds a panel's entries of every body to phi, in block order: q = s0 .. s1-1
 // not below the body's own block, then, for bodies of the panel, the blocks
 // below their own.  The last panel (wg_sum not null) completes every phi and
-// forms m_i phi_i / 2, reduced to one value per work-group.
-__global__ __launch_bounds__(256) void potential_pairs_reduce(PotPairs a, int32_t s1, int32_t block,
-                                                              double *phi, double *wg_sum)
+// forms m_i phi_i / 2, reduced to one value per work-group.  A work-group
+// takes 64 bodies (of one block); its waves share their entries, since a lane
+// that adds them all is a chain of memory round trips on few waves: 64 blocks
+// of 8192 bodies 20 us with a lane per body, 5 so.
+constexpr int kPotReduceWaves = 16;
+
+__global__ __launch_bounds__(kWave * kPotReduceWaves) void potential_pairs_reduce(
+    PotPairs a, int32_t s1, int32_t block, double *phi, double *wg_sum)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t own = i / block;
-    double e = 0.0;
-    if (i < a.n && own < s1) {
-        double v = own < a.s0 ? phi[i] : 0.0;
-        for (int64_t q = own > a.s0 ? own : a.s0; q < s1; ++q) v += a.A[(q - a.s0) * a.n + i];
-        if (own >= a.s0)
-            for (int64_t p = 0; p < own; ++p) v += a.B[p * a.b_stride + i - a.b0];
-        phi[i] = v;
-        e = 0.5 * a.m[i] * v;
+    __shared__ double part[kPotReduceWaves][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t i0 = (int64_t)blockIdx.x * kWave, i = i0 + lane;
+    const int32_t own = (int32_t)(i0 / block);
+    if (own >= s1) return;   // the whole work-group: a block of a later panel
+    const int32_t q0 = own > a.s0 ? own : a.s0;
+    const int32_t above = s1 - q0, entries = above + (own >= a.s0 ? own : 0);
+    const int32_t share = (entries + kPotReduceWaves - 1) / kPotReduceWaves;
+    const int32_t e1 = entries < (w + 1) * share ? entries : (w + 1) * share;
+    double v = 0.0;
+    if (i < a.n) {
+        const int32_t m1 = e1 < above ? e1 : above;
+        int32_t e = w * share;
+#pragma unroll 8
+        for (; e < m1; ++e) v += a.A[(int64_t)(q0 - a.s0 + e) * a.n + i];
+#pragma unroll 8
+        for (; e < e1; ++e) v += a.B[(int64_t)(e - above) * a.b_stride + i - a.b0];
     }
-    if (wg_sum) block_tree_sum(e, wg_sum);
+    part[w][lane] = v;
+    __syncthreads();
+    if (w > 0) return;
+    double u = 0.0;
+    if (i < a.n) {
+        v = own < a.s0 ? phi[i] : 0.0;
+#pragma unroll
+        for (int k = 0; k < kPotReduceWaves; ++k) v += part[k][lane];
+        phi[i] = v;
+        u = 0.5 * a.m[i] * v;
+    }
+    if (!wg_sum) return;
+    double t[1] = {u};
+    group_sums<kWave, 1>(t);
+    if (lane == 0) wg_sum[blockIdx.x] = t[0];
 }
 
 // Sums split partials (fixed order) into phi and forms m_i phi_i / 2 per
@@ -432,15 +459,19 @@ using namespace nbrt;
 namespace {
 
 // Block size of the pair-wise potential and its launch, by the number of
-// bodies: large blocks share a body of q among more pairs, small ones make
-// enough items for the chip.  Whole calls in us, rows per lane x waves:
-//   n       1x1     2x1     2x4     4x4     plain kernel
-//   1024    15.6    21.7    56.7    172     75
-//   4096    32.4    29.0    60.0    174     145
-//   8192    68      52      62      176     146
-//   16384   167     119     121     178     176
-//   65536   1856    1214    1101    1109    1862
-//   131072  9121    5198    4179    3936    7311
+// bodies: large blocks share a body of q among more pairs (and leave fewer
+// entries to add), small ones make enough items for the chip.  Whole calls in
+// us, rows per lane x waves:
+//   n       1x1     2x1     4x1     4x2     2x4     4x4     plain
+//   1024    12.4    19.9    46.2    85.3    56.5    172     75
+//   6000    24.8    28.5    50.4    87.0    57.8    173
+//   8192    37.5    36.7    51.4    87.6    58.5    173     146
+//   16384   109     88      107     147     114     175     176
+//   24000   214     164     169     205     177     286
+//   32768   390     291     287     319     303     398
+//   48000   833     609     555     568     591     631
+//   65536   1563    1115    1025    1019    1082    1100    1862
+//   131072  6309    4547    4024    3984    4326    3958    7311
 struct PotShape {
     int64_t block;
     void (*launch)(const nb::PotPairs &, int64_t, hipStream_t);
@@ -457,9 +488,10 @@ PotShape pot_shape_of()
 
 PotShape pot_shape(int64_t n)
 {
-    if (n >= 65536) return pot_shape_of<4, 4>();
-    if (n >= 16384) return pot_shape_of<2, 4>();
-    if (n >= 4096) return pot_shape_of<2, 1>();
+    if (n >= 131072) return pot_shape_of<4, 4>();
+    if (n >= 65536) return pot_shape_of<4, 2>();
+    if (n >= 28672) return pot_shape_of<4, 1>();
+    if (n >= 8192) return pot_shape_of<2, 1>();
     return pot_shape_of<1, 1>();
 }
 
@@ -538,16 +570,16 @@ int nb_potential(nb_ctx *ctx, int64_t n, const double *x, const double *m, doubl
     if (!ctx->usable) return NB_ERR_UNSUPPORTED;
     hipEvent_t ev[2];
     hipError_t e;
-    const int64_t red_wgs = (n + 255) / 256;
     // one evaluation per pair of bodies, in panels of blocks whose entries take
     // at most kPotBytes (one panel up to about 370000 bodies); under a scratch
     // limit smaller panels, or, without room for one block, the plain kernel
     const PotShape sh = pot_shape(n);
     const int64_t blocks = (n + sh.block - 1) / sh.block;
+    const int64_t sum_wgs = (n + nb::kWave - 1) / nb::kWave;
     int64_t panel = blocks;
     auto pot_bytes = [&](int64_t pb) {
         const int64_t cells = pb == blocks ? blocks * n : pb * n + blocks * pb * sh.block;
-        return (size_t)(cells + red_wgs + 1) * sizeof(double);
+        return (size_t)(cells + sum_wgs + 1) * sizeof(double);
     };
     const size_t most = ctx->scratch_limit ? std::min(ctx->scratch_limit, kPotBytes) : kPotBytes;
     while (panel > 1 && pot_bytes(panel) > most) panel = (panel + 1) / 2;
@@ -555,7 +587,7 @@ int nb_potential(nb_ctx *ctx, int64_t n, const double *x, const double *m, doubl
         int rc = ensure_scratch(ctx, pot_bytes(panel));
         if (rc != NB_OK) return rc;
         double *wg = (double *)ctx->scratch;
-        double *cells = wg + red_wgs + 1;
+        double *cells = wg + sum_wgs + 1;
         e = timed_begin(ctx, NB_CLASS_STEP, ev);
         for (int64_t s0 = 0; e == hipSuccess && s0 < blocks; s0 += panel) {
             const int64_t s1 = std::min(blocks, s0 + panel);
@@ -575,21 +607,21 @@ int nb_potential(nb_ctx *ctx, int64_t n, const double *x, const double *m, doubl
             }
             const int64_t items = (s1 * (s1 + 1) - s0 * (s0 + 1)) / 2;
             sh.launch(a, items, ctx->stream);
-            hipLaunchKernelGGL(nb::potential_pairs_reduce, dim3((unsigned)red_wgs), dim3(256), 0,
-                               ctx->stream, a, (int32_t)s1, (int32_t)sh.block, phi,
-                               s1 == blocks ? wg : nullptr);
+            hipLaunchKernelGGL(nb::potential_pairs_reduce, dim3((unsigned)sum_wgs),
+                               dim3(nb::kWave * nb::kPotReduceWaves), 0, ctx->stream, a,
+                               (int32_t)s1, (int32_t)sh.block, phi, s1 == blocks ? wg : nullptr);
             e = hipGetLastError();
         }
         if (e == hipSuccess) {
-            hipLaunchKernelGGL(nb::sum_kernel, dim3(1), dim3(256), 0, ctx->stream, red_wgs, wg,
-                               energy ? energy : wg + red_wgs);
+            hipLaunchKernelGGL(nb::sum_kernel, dim3(1), dim3(256), 0, ctx->stream, sum_wgs, wg,
+                               energy ? energy : wg + sum_wgs);
             e = hipGetLastError();
         }
         if (e == hipSuccess) e = timed_end(ctx, NB_CLASS_STEP, ev);
         return e == hipSuccess ? NB_OK : hip_fail(ctx, e);
     }
     const int cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
-    const int64_t wgs = (n + nb::kBlock - 1) / nb::kBlock;
+    const int64_t wgs = (n + nb::kBlock - 1) / nb::kBlock, red_wgs = (n + 255) / 256;
     int64_t splits = std::max<int64_t>(1, std::min<int64_t>((cus * 64 + wgs - 1) / wgs,
                                                              std::max<int64_t>(1, n / 2048)));
     const int64_t tiles = (n + nb::kTile - 1) / nb::kTile;

@@ -40,15 +40,16 @@ def _check(x, m, limit=0, rows=None):
     assert (np.abs(p - ophi) <= TOL * np.abs(ophi)).all()
 
 
-# one wave per item up to 4096 bodies, two rows per lane, four waves, four rows
-@pytest.mark.parametrize("n", [2, 63, 64, 65, 128, 129, 1000, 4095, 4096, 4225, 16383, 16385])
+# one row per lane up to 8191 bodies, two above (four, and more waves: below)
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 128, 129, 1000, 4095, 4096, 4225, 8191, 8193,
+                               16385])
 def test_potential_block_edges(n):
     say(f"potential n={n}")
     x, _, m = W.plummer(np.random.default_rng(n), n, "kroupa")
     _check(x, m)
 
 
-@pytest.mark.parametrize("n", [65536, 66561])
+@pytest.mark.parametrize("n", [28671, 28672, 33025, 65536, 66561, 131073])
 def test_potential_large_blocks(n):
     say(f"potential n={n}")
     x, _, m = W.plummer(np.random.default_rng(n), n, "kroupa")
