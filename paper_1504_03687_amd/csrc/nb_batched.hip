@@ -44,8 +44,8 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(IR == 1 && T
         const int64_t j1 = j0 + C.split_len < C.j_end ? j0 + C.split_len : C.j_end;
         const Dest d{C.splits == 1, C.slot_base + (int64_t)I.split, (int64_t)C.row_begin,
                      (int64_t)C.splits};
-        rows_pass<MIXED, IR, T, NB>(A.f, tile, I.row0, (int64_t)C.row_begin + C.n_rows, j0, j1,
-                                    d, C.near);
+        rows_pass<MIXED, IR == 1, IR, T, NB>(A.f, tile, I.row0, (int64_t)C.row_begin + C.n_rows, j0,
+                                             j1, d, C.near);
         if (A.n_items <= (int32_t)gridDim.x) break;
         if (threadIdx.x == 0) s_item = (int32_t)gridDim.x + atomicAdd(A.queue, 1);
         __syncthreads();
@@ -66,8 +66,8 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(IR == 1 && T
 // mixed) took 6113 us a call through LDS and take 5825.
 // The mixed kernel is held to five waves per SIMD (96 VGPRs, as the
 // single-block one has by itself): at 98 four fit.
-template <bool MIXED>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MIXED ? 5 : 4))) void batched_packed_kernel(BatchArgs A)
+template <bool MIXED, bool RUN>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MIXED ? RUN ? 6 : 5 : 4))) void batched_packed_kernel(BatchArgs A)
 {
     constexpr int32_t kWaves = kBlock / kWave;
     const int32_t waves = (int32_t)gridDim.x * kWaves;
@@ -80,9 +80,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MIXED ? 
         const int64_t j1 = j0 + C.split_len < C.j_end ? j0 + C.split_len : C.j_end;
         const Dest d{C.splits == 1, C.slot_base + (int64_t)I.split, (int64_t)C.row_begin,
                      (int64_t)C.splits};
-        rows_pass_packed<MIXED>(A.f, A.f.packed + C.rec_base + (j0 - C.j_begin), I.row0,
+        rows_pass_packed<MIXED, RUN>(A.f, A.f.packed + C.rec_base + (j0 - C.j_begin), I.row0,
                                 (int64_t)C.row_begin + C.n_rows, j0, j1, d, C.near,
-                                near_queue<MIXED>());
+                                near_queue<MIXED, RUN>());
         if (A.n_items <= waves) break;
         // The whole wave arrives here together before lane 0 pulls.  The
         // barrier emits nothing, but code around it is not duplicated per
@@ -170,15 +170,18 @@ int batched_shape_index(int tile, int lanes, int rows_per_lane)
     return -1;
 }
 
-static const void *batched_packed_fn(bool mixed)
+static const void *batched_packed_fn(bool mixed, bool run)
 {
-    return mixed ? (const void *)&batched_packed_kernel<true>
-                 : (const void *)&batched_packed_kernel<false>;
+    if (run)
+        return mixed ? (const void *)&batched_packed_kernel<true, true>
+                     : (const void *)&batched_packed_kernel<false, true>;
+    return mixed ? (const void *)&batched_packed_kernel<true, false>
+                 : (const void *)&batched_packed_kernel<false, false>;
 }
 
-int batched_max_blocks_per_cu(bool mixed, int shape, bool packed)
+int batched_max_blocks_per_cu(bool mixed, int shape, bool packed, bool run)
 {
-    const void *fn = packed ? batched_packed_fn(mixed)
+    const void *fn = packed ? batched_packed_fn(mixed, run)
                             : (mixed ? batched_fn<true>(shape) : batched_fn<false>(shape));
     int blocks = 0;
     if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -189,10 +192,10 @@ int batched_max_blocks_per_cu(bool mixed, int shape, bool packed)
     return blocks > 0 ? blocks : 1;
 }
 
-hipError_t launch_batched(bool mixed, int shape, bool packed, int grid, const BatchArgs &a,
-                          hipStream_t s)
+hipError_t launch_batched(bool mixed, int shape, bool packed, bool run, int grid,
+                          const BatchArgs &a, hipStream_t s)
 {
-    const void *fn = packed ? batched_packed_fn(mixed)
+    const void *fn = packed ? batched_packed_fn(mixed, run)
                             : (mixed ? batched_fn<true>(shape) : batched_fn<false>(shape));
     if (!fn) return hipErrorInvalidValue;
     BatchArgs arg = a;
@@ -480,7 +483,8 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     A.n_merge_rows = (int32_t)merge_rows.size();
     A.max_splits = 1;
     for (int32_t k = 0; k < C; ++k) A.max_splits = std::max(A.max_splits, cl[(size_t)k].splits);
-    c->grid = (int)cus * nb::batched_max_blocks_per_cu(mixed, c->shape, c->packed);
+    const bool run = max_len < nb::kRunMaxBodies;
+    c->grid = (int)cus * nb::batched_max_blocks_per_cu(mixed, c->shape, c->packed, run);
     // work-groups past the last item (a packed one pulls an item per wave) would do nothing
     const int pulls = c->packed ? nb::kBlock / nb::kWave : 1;
     c->grid = std::max(1, std::min(c->grid, (A.n_items + pulls - 1) / pulls));
@@ -500,7 +504,7 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
             le = nb::launch_fill_i32(queue, 0, 64, cs);
             if (le == hipSuccess) le = nb::launch_fill_i32(f.overflow, 0, 1, cs);
         }
-        if (le == hipSuccess) le = nb::launch_batched(mixed, c->shape, c->packed, c->grid, A, cs);
+        if (le == hipSuccess) le = nb::launch_batched(mixed, c->shape, c->packed, run, c->grid, A, cs);
         if (le == hipSuccess) le = nb::launch_batched_merge(A, cs);
         if (le == hipSuccess && c->redo_k > 0.0)
             le = nb::launch_redo(A.f, false, cs);

@@ -44,8 +44,8 @@ __device__ __forceinline__ void clear_call_words(const ForceArgs &a)
     }
 }
 
-// grid = (ceil(n_i / (IR * kBlock)), splits)
-template <bool MIXED, int IR>
+// grid = (ceil(n_i / (IR * kBlock)), splits); RUN: see mark_mixed
+template <bool MIXED, bool RUN, int IR>
 __global__ __launch_bounds__(kBlock) void force_rows_kernel(ForceArgs a)
 {
     __shared__ JBody tile[2][kTile];
@@ -54,8 +54,8 @@ __global__ __launch_bounds__(kBlock) void force_rows_kernel(ForceArgs a)
     const int64_t j0 = (int64_t)split * a.split_len;
     const int64_t j1 = j0 + a.split_len < a.n ? j0 + a.split_len : a.n;
     const Dest d{a.splits == 1, (int64_t)split, 0, (int64_t)a.splits};
-    rows_pass<MIXED, IR, kTile, kBlock>(a, tile, (int64_t)blockIdx.x * IR * kBlock, a.n_i, j0, j1, d,
-                         a.near_factor);
+    rows_pass<MIXED, RUN, IR, kTile, kBlock>(a, tile, (int64_t)blockIdx.x * IR * kBlock, a.n_i, j0, j1,
+                                             d, a.near_factor);
 }
 
 __global__ __launch_bounds__(kBlock) void pack_kernel(ForceArgs a)
@@ -69,8 +69,10 @@ __global__ __launch_bounds__(kBlock) void pack_kernel(ForceArgs a)
 // (global) takes row tile w % tiles (kWave rows) over j-range w / tiles, so
 // the waves of a work-group mostly share one j-range (and its lines in the
 // scalar cache) and no lane is lost to row tiles larger than a wave.
-template <bool MIXED>
-__global__ __launch_bounds__(kBlock) void force_packed_kernel(ForceArgs a)
+// The mixed kernel that settles rare pairs by runs fits six waves per SIMD (75
+// registers; 16384 rows of 16384 270 us with five, 267 with six).
+template <bool MIXED, bool RUN>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MIXED ? RUN ? 6 : 5 : 4))) void force_packed_kernel(ForceArgs a)
 {
     const int64_t tiles = (a.n_i + kWave - 1) / kWave;
     const int64_t gw = (int64_t)blockIdx.x * (kBlock / kWave) +
@@ -81,8 +83,8 @@ __global__ __launch_bounds__(kBlock) void force_packed_kernel(ForceArgs a)
     const int64_t j0 = (int64_t)split * a.split_len;
     const int64_t j1 = j0 + a.split_len < a.n ? j0 + a.split_len : a.n;
     const Dest d{a.splits == 1, (int64_t)split, 0, (int64_t)a.splits};
-    rows_pass_packed<MIXED>(a, a.packed + j0, tile * kWave, a.n_i, j0, j1, d, a.near_factor,
-                            near_queue<MIXED>());
+    rows_pass_packed<MIXED, RUN>(a, a.packed + j0, tile * kWave, a.n_i, j0, j1, d, a.near_factor,
+                                 near_queue<MIXED, RUN>());
 }
 
 // One-wave work-groups of the row-per-lane pass (64 rows, a 64-body LDS tile):
@@ -91,7 +93,7 @@ __global__ __launch_bounds__(kBlock) void force_packed_kernel(ForceArgs a)
 // Held to four waves per SIMD (128 VGPRs, no spill): the plan puts about 16
 // work-groups on each CU, and at the compiler's 130 VGPRs only 12 fit at
 // once (64 rows took 95 us instead of 87).
-template <bool MIXED>
+template <bool MIXED, bool RUN>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void force_rows_wave_kernel(ForceArgs a)
 {
     __shared__ JBody tile[2][kWave];
@@ -100,8 +102,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
     const int64_t j0 = (int64_t)split * a.split_len;
     const int64_t j1 = j0 + a.split_len < a.n ? j0 + a.split_len : a.n;
     const Dest d{a.splits == 1, (int64_t)split, 0, (int64_t)a.splits};
-    rows_pass<MIXED, 1, kWave, kWave>(a, tile, (int64_t)blockIdx.x * kWave, a.n_i, j0, j1, d,
-                                      a.near_factor);
+    rows_pass<MIXED, RUN, 1, kWave, kWave>(a, tile, (int64_t)blockIdx.x * kWave, a.n_i, j0, j1, d,
+                                           a.near_factor);
 }
 
 // Wave w (global) handles row group w % ngroups (rows G*(w%ngroups) + g) over
@@ -627,26 +629,28 @@ hipError_t launch_pack(const ForceArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-template <bool MIXED>
+// RUN: for j-ranges of less than kRunMaxBodies bodies (see mark_mixed); plans of
+// several rows per lane, which only a caller or the tuner chooses, have it not.
+template <bool MIXED, bool RUN>
 static hipError_t launch_force_t(const Plan &p, const ForceArgs &a, hipStream_t s)
 {
     if (a.packed) {
         const int64_t waves = ((int64_t)a.n_i + kWave - 1) / kWave * p.splits;
         const int64_t per = kBlock / kWave;
-        hipLaunchKernelGGL((force_packed_kernel<MIXED>), dim3((unsigned)((waves + per - 1) / per)),
+        hipLaunchKernelGGL((force_packed_kernel<MIXED, RUN>), dim3((unsigned)((waves + per - 1) / per)),
                            dim3(kBlock), 0, s, a);
     } else if (p.mapping == 1) {
         const int per = p.rows_per_lane * kBlock;
         dim3 grid((unsigned)((a.n_i + per - 1) / per), (unsigned)p.splits);
         switch (p.rows_per_lane) {
-        case 1: hipLaunchKernelGGL((force_rows_kernel<MIXED, 1>), grid, dim3(kBlock), 0, s, a); break;
-        case 2: hipLaunchKernelGGL((force_rows_kernel<MIXED, 2>), grid, dim3(kBlock), 0, s, a); break;
-        case 4: hipLaunchKernelGGL((force_rows_kernel<MIXED, 4>), grid, dim3(kBlock), 0, s, a); break;
+        case 1: hipLaunchKernelGGL((force_rows_kernel<MIXED, RUN, 1>), grid, dim3(kBlock), 0, s, a); break;
+        case 2: hipLaunchKernelGGL((force_rows_kernel<MIXED, false, 2>), grid, dim3(kBlock), 0, s, a); break;
+        case 4: hipLaunchKernelGGL((force_rows_kernel<MIXED, false, 4>), grid, dim3(kBlock), 0, s, a); break;
         default: return hipErrorInvalidValue;
         }
     } else if (p.mapping == 3) {
         dim3 grid((unsigned)((a.n_i + kWave - 1) / kWave), (unsigned)p.splits);
-        hipLaunchKernelGGL((force_rows_wave_kernel<MIXED>), grid, dim3(kWave), 0, s, a);
+        hipLaunchKernelGGL((force_rows_wave_kernel<MIXED, RUN>), grid, dim3(kWave), 0, s, a);
     } else {
         const int G = p.rows_per_lane;
         const int64_t waves = ((a.n_i + G - 1) / G) * (int64_t)p.splits;
@@ -664,7 +668,9 @@ static hipError_t launch_force_t(const Plan &p, const ForceArgs &a, hipStream_t 
 
 hipError_t launch_force(const Plan &p, bool mixed, const ForceArgs &a, hipStream_t s)
 {
-    return mixed ? launch_force_t<true>(p, a, s) : launch_force_t<false>(p, a, s);
+    if (a.n < kRunMaxBodies)
+        return mixed ? launch_force_t<true, true>(p, a, s) : launch_force_t<false, true>(p, a, s);
+    return mixed ? launch_force_t<true, false>(p, a, s) : launch_force_t<false, false>(p, a, s);
 }
 
 hipError_t launch_merge(bool mixed, const ForceArgs &a, hipStream_t s)

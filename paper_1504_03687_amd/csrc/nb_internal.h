@@ -16,6 +16,9 @@ constexpr int kTile = 256;
 // Mixed precision: FP32 partial sums run over this many j before they are
 // folded into the FP64 running sums.
 constexpr int kFold = 32;
+// j-ranges of less than this many bodies run the passes that settle rare pairs
+// (neighbours) once per kFold bodies, larger ones those that do it at once.
+constexpr int64_t kRunMaxBodies = 65536;
 // Capacity of one split's neighbour segment in scratch.  A segment that
 // overflows is rebuilt by the merge kernel from its j-range.
 constexpr int kSegCap = 96;
@@ -213,11 +216,11 @@ constexpr int kSplitUnit = 256;
 // Index of a shape in kBatchedShape, or -1.
 int batched_shape_index(int tile, int lanes, int rows_per_lane);
 // packed: the scalar-operand kernel (items of one wave, kWave rows) instead of
-// the LDS kernel of the shape.
-hipError_t launch_batched(bool mixed, int shape, bool packed, int grid, const BatchArgs &a,
-                          hipStream_t s);
+// the LDS kernel of the shape; run: the one that settles rare pairs by runs.
+hipError_t launch_batched(bool mixed, int shape, bool packed, bool run, int grid,
+                          const BatchArgs &a, hipStream_t s);
 hipError_t launch_batched_pack(const BatchArgs &a, hipStream_t s);
 hipError_t launch_batched_merge(const BatchArgs &a, hipStream_t s);
-int batched_max_blocks_per_cu(bool mixed, int shape, bool packed);
+int batched_max_blocks_per_cu(bool mixed, int shape, bool packed, bool run);
 
 }  // namespace nb

@@ -229,6 +229,10 @@ __device__ __forceinline__ void opaque(double &a, double &b, double &c)
 {
     __asm__ volatile("" : "+v"(a), "+v"(b), "+v"(c));
 }
+__device__ __forceinline__ void opaque(uint32_t &a)
+{
+    __asm__ volatile("" : "+v"(a));
+}
 __device__ __forceinline__ void opaque(int32_t &a)
 {
     __asm__ volatile("" : "+v"(a));

@@ -83,7 +83,15 @@ struct Row {
     int32_t cnt;    // neighbours found so far (true count)
     int32_t *lst;   // where this row's neighbours go
     int32_t lcap;   // capacity of lst
+    // passes that settle rare pairs by runs: the current run of kFold bodies, a
+    // bit per body, the pairs that the common path left out, and (mixed, see
+    // classify()) those of them inside the radius
+    uint32_t hit, nbr;
     Sums<MIXED> S;
+    // whether a mixed pair that is left out may be something else than a
+    // neighbour or the row's body: with the near bound, or where the radius is
+    // below the least candidate bound
+    __device__ __forceinline__ bool classify() const { return candf != rs2f; }
 };
 
 // Where the rows of one pass write: straight to the caller's outputs, or to
@@ -122,6 +130,7 @@ __device__ __forceinline__ void row_init(Row<MIXED> &R, const ForceArgs &a, int6
     R.lst = nullptr;
     R.lcap = 0;
     R.jend = 0;
+    R.hit = R.nbr = 0;
     if (b >= row_end) return;
     const int64_t i = a.i_block[b];
     if (i < 0 || i >= a.n) return;   // bad index: handled in the epilogue / merge
@@ -175,6 +184,22 @@ struct NearNow {
 constexpr int kNearSlots = 16;
 constexpr int64_t kNearSpan = 4096;
 
+// The record of one body of the packed j-set, read lane by lane.
+__device__ __forceinline__ JBody rec_body(const JRec *r)
+{
+    const double2 *p = reinterpret_cast<const double2 *>(r);
+    const double2 xy = p[0], zvx = p[1], vyz = p[2], m = p[3];
+    JBody J;
+    J.x = xy.x;
+    J.y = xy.y;
+    J.z = zvx.x;
+    J.vx = zvx.y;
+    J.vy = vyz.x;
+    J.vz = vyz.y;
+    J.m = m.x;
+    return J;
+}
+
 struct NearLater {
     int32_t (*queue)[kBlock];   // LDS [kNearSlots][kBlock]
     int32_t n;                  // bodies queued
@@ -194,12 +219,9 @@ struct NearLater {
     {
         for (int q = 0; __ballot(q < n) != 0; ++q)
             if (q < n) {
-                const double2 *p =
-                    reinterpret_cast<const double2 *>(rec0 + (queue[q][threadIdx.x] - j0));
-                const double2 xy = p[0], zvx = p[1], vyz = p[2], m = p[3];
-                add_term_f64(R.S.ax, R.S.ay, R.S.az, R.S.jx, R.S.jy, R.S.jz, xy.x - R.x,
-                             xy.y - R.y, zvx.x - R.z, zvx.y - R.vx, vyz.x - R.vy, vyz.y - R.vz,
-                             m.x);
+                const JBody J = rec_body(rec0 + (queue[q][threadIdx.x] - j0));
+                add_term_f64(R.S.ax, R.S.ay, R.S.az, R.S.jx, R.S.jy, R.S.jz, J.x - R.x, J.y - R.y,
+                             J.z - R.z, J.vx - R.vx, J.vy - R.vy, J.vz - R.vz, J.m);
             }
         n = 0;
     }
@@ -251,6 +273,75 @@ __device__ __forceinline__ void rare_f64(Row<false> &R, int32_t jidx, double &r2
     }
 }
 
+// The rare branches of the passes that settle rare pairs by runs: they only
+// set the pair's bit in R.hit and give it an excluding squared distance; what
+// the pair is, take_hits settles once per run of kFold bodies.  Appending to
+// the list in the branch itself takes five nested exec-mask changes and a
+// store, and with 69 neighbours among 1024 bodies some lane of a wave has one
+// at nearly every body, among 25000 at every sixth.  Passes over
+// kRunMaxBodies bodies or more append at once: there the look at the bits of
+// every run costs more than it saves.  LDS and packed passes, at once against
+// by runs, mixed / FP64: 1024 rows of 1024 23.8 / 17.4 against 21.6 / 16.3 us,
+// 4096 of 4096 50.7 / 46.6 against 46.9 / 43.4, 16384 of 16384 275 / 352
+// against 268 / 348, 1500 of 65536 127 / 147 both, 300 of 131072 72.0 / 71.0
+// against 72.3 / 71.9, 65536 of 2^20 49.7 / 71.5 against 50.2 / 72.3 ms; 160
+// clusters of 1000 to 10000 1910 / 2573 against 1802 / 2407 us.
+__device__ __forceinline__ void mark_mixed(Row<true> &R, float &r0, float &r1, uint32_t bit,
+                                           bool classify)
+{
+    opaque(R.hit);
+    if (classify) R.nbr |= (r0 < R.rs2f ? bit : 0u) | (r1 < R.rs2f ? bit << 1 : 0u);
+    const bool c0 = r0 < R.candf, c1 = r1 < R.candf;
+    R.hit |= (c0 ? bit : 0u) | (c1 ? bit << 1 : 0u);
+    r0 = c0 ? kExclR2F : r0;
+    r1 = c1 ? kExclR2F : r1;
+}
+
+__device__ __forceinline__ void mark_f64(Row<false> &R, int32_t jidx, double &r2, double dx,
+                                         double dy, double dz, uint32_t bit)
+{
+    if (r2 < R.hi) {
+        double ex = dx, ey = dy, ez = dz;
+        opaque(ex, ey, ez);
+        // the self pair fails the canonical test where the radius is zero
+        const bool c = canon_r2f(ex, ey, ez) < R.rs2f || jidx == R.i;
+        R.hit |= c ? bit : 0u;
+        r2 = c ? kExclR2 : r2;
+    }
+}
+
+// Settles the pairs that the run of kFold bodies from jb on left out, in j
+// order: neighbours go to the list, near pairs (mixed) get their FP64 term; the
+// self pair and padding past the j-range (which passes the test for a huge or
+// infinite radius only) add nothing.  By the whole wave; at(q): body jb + q.
+template <bool MIXED, class At>
+__device__ __forceinline__ void take_hits(Row<MIXED> &R, int32_t jb, bool classify, const At &at)
+{
+    if (__ballot(R.hit != 0) == 0) return;
+    uint32_t h = R.hit;
+    R.hit = 0;
+    if (R.jend - jb < kFold) h &= (1u << (R.jend - jb)) - 1u;
+    const uint32_t self = (uint32_t)(R.i - jb);
+    if (self < kFold) h &= ~(1u << self);
+    if constexpr (MIXED) {
+        if (classify) {
+            uint32_t f = h & ~R.nbr;
+            h &= R.nbr;
+            R.nbr = 0;
+            while (f) {
+                const JBody J = at(__builtin_ctz(f));
+                f &= f - 1;
+                add_term_f64(R.S.ax, R.S.ay, R.S.az, R.S.jx, R.S.jy, R.S.jz, J.x - R.x, J.y - R.y,
+                             J.z - R.z, J.vx - R.vx, J.vy - R.vy, J.vz - R.vz, J.m);
+            }
+        }
+    }
+    while (h) {
+        append(R, jb + __builtin_ctz(h));
+        h &= h - 1;
+    }
+}
+
 // One row against two consecutive j, with a single branch for the rare cases
 // (one exec-mask change per two j).  Mixed: FP64 differences, canonical FP32
 // r2f (the neighbour test itself), FP32 terms; pairs with r2f below the
@@ -261,9 +352,10 @@ __device__ __forceinline__ void rare_f64(Row<false> &R, int32_t jidx, double &r2
 // in the minimum), and a pair handled there gets an excluding squared
 // distance, so the common path holds no select.  Every accumulator receives
 // the terms of j and then j+1, as a loop over single j would give them.
-template <bool MIXED, class Body, class Near>
+// RUN: rare pairs are marked, not handled (bit: the first pair's place in the run).
+template <bool MIXED, bool RUN, class Body, class Near>
 __device__ __forceinline__ void pair_rows2(Row<MIXED> &R, const Body &J0, const Body &J1,
-                                           int32_t jidx0, Near &N)
+                                           int32_t jidx0, Near &N, uint32_t bit, bool classify)
 {
     if constexpr (MIXED) {
         const double dx0 = J0.x - R.x, dy0 = J0.y - R.y, dz0 = J0.z - R.z;
@@ -273,8 +365,12 @@ __device__ __forceinline__ void pair_rows2(Row<MIXED> &R, const Body &J0, const 
         float r0 = __builtin_fmaf(fz0, fz0, __builtin_fmaf(fy0, fy0, fx0 * fx0));
         float r1 = __builtin_fmaf(fz1, fz1, __builtin_fmaf(fy1, fy1, fx1 * fx1));
         if (__builtin_fminf(r0, r1) < R.candf) {
-            rare_mixed(R, J0, jidx0, r0, dx0, dy0, dz0, N);
-            rare_mixed(R, J1, jidx0 + 1, r1, dx1, dy1, dz1, N);
+            if constexpr (RUN) {
+                mark_mixed(R, r0, r1, bit, classify);
+            } else {
+                rare_mixed(R, J0, jidx0, r0, dx0, dy0, dz0, N);
+                rare_mixed(R, J1, jidx0 + 1, r1, dx1, dy1, dz1, N);
+            }
         }
         accum_mixed(R.S, fx0, fy0, fz0, r0, J0.vx - R.vx, J0.vy - R.vy, J0.vz - R.vz, J0.m32);
         accum_mixed(R.S, fx1, fy1, fz1, r1, J1.vx - R.vx, J1.vy - R.vy, J1.vz - R.vz, J1.m32);
@@ -284,8 +380,14 @@ __device__ __forceinline__ void pair_rows2(Row<MIXED> &R, const Body &J0, const 
         double r0 = __builtin_fma(dz0, dz0, __builtin_fma(dy0, dy0, dx0 * dx0));
         double r1 = __builtin_fma(dz1, dz1, __builtin_fma(dy1, dy1, dx1 * dx1));
         if (__builtin_fmin(r0, r1) < R.hi) {
-            rare_f64<Body::kPacked>(R, jidx0, r0, dx0, dy0, dz0);
-            rare_f64<Body::kPacked>(R, jidx0 + 1, r1, dx1, dy1, dz1);
+            if constexpr (RUN) {
+                opaque(R.hit);
+                mark_f64(R, jidx0, r0, dx0, dy0, dz0, bit);
+                mark_f64(R, jidx0 + 1, r1, dx1, dy1, dz1, bit << 1);
+            } else {
+                rare_f64<Body::kPacked>(R, jidx0, r0, dx0, dy0, dz0);
+                rare_f64<Body::kPacked>(R, jidx0 + 1, r1, dx1, dy1, dz1);
+            }
         }
         accum_f64(R.S, dx0, dy0, dz0, r0, J0.vx - R.vx, J0.vy - R.vy, J0.vz - R.vz, J0.m);
         accum_f64(R.S, dx1, dy1, dz1, r1, J1.vx - R.vx, J1.vy - R.vy, J1.vz - R.vz, J1.m);
@@ -413,7 +515,7 @@ __device__ __forceinline__ void flush_flags(const ForceArgs &a, bool ovf, bool b
 // kFold bodies from j0) and all sums are the same for every T and NB, so
 // results do not depend on the tile or work-group shape.  Must be called by
 // the whole work-group (it contains barriers).
-template <bool MIXED, int IR, int T, int NB>
+template <bool MIXED, bool RUN, int IR, int T, int NB>
 __device__ __forceinline__ void rows_pass(const ForceArgs &a, JBody (*tile)[T], int64_t row0,
                                           int64_t row_end, int64_t j0, int64_t j1,
                                           const Dest &d, float near)
@@ -422,11 +524,13 @@ __device__ __forceinline__ void rows_pass(const ForceArgs &a, JBody (*tile)[T], 
     constexpr bool kPrefetch = T == NB;
     const int tid = threadIdx.x;
     NearNow N;
+    bool classify[IR];
     Row<MIXED> R[IR];
 #pragma unroll
     for (int r = 0; r < IR; ++r) {
         row_init(R[r], a, row0 + r * NB + tid, row_end, d, near);
         R[r].jend = (int32_t)j1;
+        classify[r] = RUN && MIXED && __ballot(R[r].classify()) != 0;
     }
 
     // a wave none of whose lanes holds a valid row (the tail of a cluster's
@@ -471,7 +575,14 @@ __device__ __forceinline__ void rows_pass(const ForceArgs &a, JBody (*tile)[T], 
                 const int32_t jidx = (int32_t)(tbase + jj + q);
 #pragma unroll
                 for (int r = 0; r < IR; ++r)
-                    pair_rows2<MIXED>(R[r], buf[jj + q], buf[jj + q + 1], jidx, N);
+                    pair_rows2<MIXED, RUN>(R[r], buf[jj + q], buf[jj + q + 1], jidx, N, 1u << q,
+                                           classify[r]);
+            }
+            if constexpr (RUN) {
+#pragma unroll
+                for (int r = 0; r < IR; ++r)
+                    take_hits(R[r], (int32_t)tbase + jj, classify[r],
+                              [buf, jj](int q) { return buf[jj + q]; });
             }
             if constexpr (MIXED) {
 #pragma unroll
@@ -504,11 +615,12 @@ __device__ __forceinline__ void rows_pass(const ForceArgs &a, JBody (*tile)[T], 
     flush_flags(a, ovf, bad, nonfin);
 }
 
-// LDS of the near-pair queues (the mixed pass of kBlock-lane work-groups).
-template <bool MIXED>
+// LDS of the near-pair queues (the mixed pass of kBlock-lane work-groups that
+// handles rare pairs at once).
+template <bool MIXED, bool RUN>
 __device__ __forceinline__ int32_t (*near_queue())[kBlock]
 {
-    if constexpr (MIXED) {
+    if constexpr (MIXED && !RUN) {
         __shared__ int32_t q[kNearSlots][kBlock];
         return q;
     } else {
@@ -532,7 +644,7 @@ __device__ __forceinline__ int32_t (*near_queue())[kBlock]
 // Records past j1 up
 // to the next multiple of kFold from j0, and two more, must be readable, and
 // at the end of the j-set they are padding.
-template <bool MIXED>
+template <bool MIXED, bool RUN>
 __device__ __forceinline__ void rows_pass_packed(const ForceArgs &a, const JRec *rec0,
                                                  int64_t row0, int64_t row_end, int64_t j0,
                                                  int64_t j1, const Dest &d, float near,
@@ -544,6 +656,7 @@ __device__ __forceinline__ void rows_pass_packed(const ForceArgs &a, const JRec 
     Row<MIXED> R;
     row_init(R, a, b, row_end, d, near);
     R.jend = (int32_t)j1;
+    const bool classify = RUN && MIXED && __ballot(R.classify()) != 0;
     NearLater N{queue, 0};
     if (__ballot(R.i >= 0) != 0) {
         SBody<MIXED> A0, A1, B0, B1;
@@ -558,17 +671,20 @@ __device__ __forceinline__ void rows_pass_packed(const ForceArgs &a, const JRec 
                 B0.load(rec + 2);
                 B1.load(rec + 3);
                 __builtin_amdgcn_sched_barrier(0);
-                pair_rows2<MIXED>(R, A0, A1, jidx, N);
+                pair_rows2<MIXED, RUN>(R, A0, A1, jidx, N, 1u << q, classify);
                 B0.arrive();
                 B1.arrive();
                 rec += 4;
                 A0.load(rec);
                 A1.load(rec + 1);
                 __builtin_amdgcn_sched_barrier(0);
-                pair_rows2<MIXED>(R, B0, B1, jidx + 2, N);
+                pair_rows2<MIXED, RUN>(R, B0, B1, jidx + 2, N, 4u << q, classify);
             }
+            if constexpr (RUN)
+                take_hits(R, (int32_t)jb, classify,
+                          [rec0, jb, j0](int q) { return rec_body(rec0 + (jb - j0 + q)); });
             if (MIXED || ((jb - j0 + kFold) & (kFoldF64 - 1)) == 0) R.S.fold();
-            if constexpr (MIXED)
+            if constexpr (MIXED && !RUN)
                 if (((jb - j0 + kFold) & (kNearSpan - 1)) == 0 || jb + kFold >= j1)
                     N.evaluate(R, rec0, (int32_t)j0);
         }

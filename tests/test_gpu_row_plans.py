@@ -22,7 +22,8 @@ def _defined(out, cap):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
-@pytest.mark.parametrize("n,n_i,splits", [(65537, 2049, 7), (65567, 4096, 1), (140001, 1000, 0)])
+@pytest.mark.parametrize("n,n_i,splits", [(65537, 2049, 7), (65567, 4096, 1), (140001, 1000, 0),
+                                          (30011, 4600, 3), (65535, 2100, 1)])
 def test_packed_equals_lds_pass(n, n_i, splits, prec):
     """n and n_i one past and one short of the runs and tiles; several splits,
     one (direct stores), and the automatic count; duplicate rows, a bad index
@@ -168,3 +169,52 @@ def test_refined_rows_of_one_chunk(n, rows):
             assert np.array_equal(host(bat[k]), runs[0][k])
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,n_i,mapping", [(1030, 70, 3), (1030, 1030, 1), (40961, 3300, 1)])
+def test_rare_pairs_by_runs(n, n_i, mapping, prec):
+    """Passes over less than 65536 bodies settle neighbours once per 32 bodies:
+    the same lists and bits as the passes that do it at once (two rows per
+    lane), with rows whose radius takes in everything (also the padding), a
+    few, or nothing, and two bodies so close that their squared distance is
+    below the smallest normal float (a near pair of a row without radius)."""
+    say(f"rare pairs by runs n={n} n_i={n_i} {prec}")
+    rng = np.random.default_rng(n + n_i)
+    s = W.small_state(900 + n_i, n, k_nn=20)
+    x = s["x"].copy()
+    ib = rng.permutation(n)[:n_i].astype(np.int32)
+    x[:, ib[0]] = 0.0
+    x[:, ib[1]] = [3e-20, 0.0, 0.0]
+    rs2 = s["rs2"][ib].copy()
+    rs2[:2] = 0.0
+    rs2[2::17] = np.inf
+    rs2[3::17] = (2.0 * np.abs(x).max()) ** 2
+    rs2[4::17] = 0.0
+    cap = 40
+    args = (dev(x), dev(s["v"]), dev(s["m"]), dev(ib), dev(rs2), cap, prec)
+    ctx = nb.Context(0)
+    try:
+        ctx.set_mixed_tolerance(0.0)   # no refinement: the sums of the pass itself
+        runs = nb.regular_force(*args, ctx=ctx)
+        plan = ctx.last_plan()
+        assert f"mapping={mapping}" in plan and "rows_per_lane=1" in plan, plan
+        assert ("packed" in plan) == (n * n_i > 1 << 27), plan
+        k = 3
+        ctx.set_plan(mapping, 1, k)
+        runs_k = nb.regular_force(*args, ctx=ctx)
+        ctx.set_plan(1, 2, k)
+        once = nb.regular_force(*args, ctx=ctx)
+        torch.cuda.synchronize()
+    finally:
+        ctx.close()
+    a, b, c = (_defined(o, cap) for o in (runs, runs_k, once))
+    for i in (2, 3, 4):
+        assert np.array_equal(a[i], c[i]) and np.array_equal(b[i], c[i])
+    if mapping == 1:     # the same splits: the same bits
+        assert np.array_equal(b[0], c[0], equal_nan=True)
+        assert np.array_equal(b[1], c[1], equal_nan=True)
+    assert (a[2][2::17] == n - 1).all() and (a[2][4::17] == 0).all()
+    fin = np.setdiff1d(np.arange(n_i), [0, 1])   # rows 0 and 1: a pair at 3e-20
+    compare_force(runs, x, s["v"], s["m"], ib, rs2, cap, TOL[prec],
+                  rows=rng.choice(fin, min(48, fin.size), replace=False))
