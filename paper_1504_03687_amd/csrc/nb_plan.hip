@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdint>
 
 #include "nbreg.h"
 #include "nb_internal.h"
@@ -94,6 +95,38 @@ int64_t max_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, int r
 constexpr int64_t kWaveMaxSplits = 1024;
 constexpr int64_t kRowWaveMaxSplits = 4096;
 
+// Split length of a packed launch, from the least one to twice that in steps of
+// 64 bodies: the one whose work-groups fill the CUs best.  Cost in pairs of the
+// whole chip: the work-groups of the fullest CU and one more for the end of the
+// launch, where few waves are left on each SIMD, each of kBlock rows by the
+// split's bodies; and 40 a record for the merge.  It orders whole calls as they
+// were measured: 4099 rows of 131072, splits of 512 (16.25 work-groups per CU)
+// 501 us mixed and 655 FP64, 768 (10.9) 491 and 633, 1024 (8.1) 535 and 685,
+// 1280 538 and 678, 2048 (4.06) 632 and 785.  Not below kMinPerCu work-groups
+// per CU: at little more than fit at once (10000 of 30000, 6.6 per CU instead of
+// 9.1) the last ones run alone, 312 us against 290.  Without and with this rule,
+// mixed / FP64: 4099 of 131072 501 / 646 and 487 / 627 us, 5500 634 / 843 and
+// 625 / 821, 7000 794 / 1065 and 771 / 1030, 8192 896 / 1207 and 884 / 1175.
+// Longer splits, whose number is the target's, gain nothing reliable by it (2222
+// of 2^20 1858 and 1896, 3333 2820 and 2775 us).
+static int64_t even_split_len(int64_t cus, int64_t n, int32_t n_i)
+{
+    constexpr int64_t kWaves = nb::kBlock / nb::kWave, kMinPerCu = 10, kLeast = 2 * nb::kTile;
+    const int64_t tiles = ((int64_t)n_i + nb::kWave - 1) / nb::kWave;
+    int64_t best = kLeast, least = INT64_MAX;
+    for (int64_t l = kLeast; l <= 2 * kLeast; l += nb::kWave) {
+        const int64_t s = (n + l - 1) / l;
+        const int64_t per_cu = ((tiles * s + kWaves - 1) / kWaves + cus - 1) / cus;
+        if (per_cu < kMinPerCu) break;
+        const int64_t cost = (per_cu + 1) * cus * nb::kBlock * l + n_i * s * 40;
+        if (cost < least) {
+            least = cost;
+            best = l;
+        }
+    }
+    return best;
+}
+
 int64_t default_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, int rows)
 {
     const int64_t cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
@@ -119,7 +152,8 @@ int64_t default_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, i
     // mapping 3, 64 rows of 2^20: 107 us at 4096 splits, 114 at 8192.
     if (mapping == 2) s = std::min(s, kWaveMaxSplits);
     if (mapping != 2) s = std::min(s, kRowWaveMaxSplits);
-    return std::max<int64_t>(1, std::min(s, max_splits(ctx, n, n_i, mapping, rows)));
+    s = std::max<int64_t>(1, std::min(s, max_splits(ctx, n, n_i, mapping, rows)));
+    return s;
 }
 
 // Plan::step of a split count chosen for a launch: the coarsest that can give
@@ -182,6 +216,14 @@ Plan auto_plan(const nb_ctx *ctx, int64_t n, int32_t n_i, bool mixed)
         if (!packed) p.step = (int)min_split(ctx, n, n_i, p.mapping, p.rows_per_lane);
     }
     p.splits = (int)default_splits(ctx, n, n_i, p.mapping, p.rows_per_lane);
+    // packed launches with splits of the least length: their number only falls
+    // out of it
+    if (pack_pays(p.mapping, p.rows_per_lane, n, n_i) &&
+        p.splits == max_splits(ctx, n, n_i, p.mapping, p.rows_per_lane)) {
+        const int64_t len = even_split_len(ctx->cu_count > 0 ? ctx->cu_count : 256, n, n_i);
+        p.splits = (int)((n + len - 1) / len);
+        p.step = nb::kWave;
+    }
     return p;
 }
 

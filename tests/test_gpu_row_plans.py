@@ -218,3 +218,32 @@ def test_rare_pairs_by_runs(n, n_i, mapping, prec):
     fin = np.setdiff1d(np.arange(n_i), [0, 1])   # rows 0 and 1: a pair at 3e-20
     compare_force(runs, x, s["v"], s["m"], ib, rs2, cap, TOL[prec],
                   rows=rng.choice(fin, min(48, fin.size), replace=False))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_even_splits_of_packed_launches(prec):
+    """Automatic plans of mid-size blocks take a split length that fills the CUs
+    evenly (a multiple of 64 bodies, 512 to 1024): lists as with other splits,
+    sums against the oracle."""
+    n, n_i, cap = 131075, 4100, 24
+    say(f"even splits n={n} n_i={n_i} {prec}")
+    rng = np.random.default_rng(n)
+    s = W.small_state(950, n, k_nn=20)
+    ib = rng.choice(n, n_i, replace=False).astype(np.int32)
+    rs2 = s["rs2"][ib]
+    args = (dev(s["x"]), dev(s["v"]), dev(s["m"]), dev(ib), dev(rs2), cap, prec)
+    ctx = nb.Context(0)
+    try:
+        auto = nb.regular_force(*args, ctx=ctx)
+        plan = ctx.last_plan()
+        length = int(plan.split("split_len=")[1].split()[0])
+        assert "bodies=packed" in plan and length % 64 == 0 and 512 < length <= 1024, plan
+        ctx.set_plan(1, 1, 5)
+        five = nb.regular_force(*args, ctx=ctx)
+        torch.cuda.synchronize()
+    finally:
+        ctx.close()
+    for x, y in zip(_defined(auto, cap)[2:], _defined(five, cap)[2:]):
+        assert np.array_equal(x, y)
+    compare_force(auto, s["x"], s["v"], s["m"], ib, rs2, cap, TOL[prec],
+                  rows=rng.choice(n_i, 64, replace=False))
