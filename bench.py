@@ -33,18 +33,19 @@ sys.path.insert(0, ROOT)
 # r.u (5), 1/sqrt (1), r^-2 (1), m r^-3 (2), 3 (r.u) r^-2 (2), acc += m r^-3 r
 # (6), jerk += m r^-3 (u - alpha r) (12).
 FLOPS_PER_PAIR = 40
-# Algorithmic floating-point operations per pair of the adjoint's two FP64
-# recompute passes (FMA = 2), counted from the gradient formulas with the
-# row-constant weights A = w_a, B = w_j factored out of the pair loops:
-#  row pass: r, u differences 6, |r|^2 5, 1/sqrt 1, |r|^-2, |r|^-3, |r|^-5 3,
-#    r.u, A.r, B.r, B.u 20, m |r|^-5 and its (B.r) product 2, the r
-#    coefficient 6, sum m |r|^-3 2, sum m |r|^-5 (r.u) 2, the u and r sums
-#    of H 12, sum (B.r) r 6 -> 65;
-#  body pass: the same geometry 35, A.r + B.u and s (B.r) 2, the two mass
-#    sums 4, |r|^-5 s and |r|^-5 (B.r) 2, the r coefficient 4, the A, B and
-#    u/r sums 36 -> 83.
-ADJ_FLOPS_ROWS = 65
-ADJ_FLOPS_BODIES = 83
+# Algorithmic floating-point operations per pair of the adjoint's FP64 pass
+# (FMA = 2), counted from the gradient formulas with the row-constant weights
+# A = w_a, B = w_j factored out of the row sums; every pair is evaluated once for
+# its row and its body:
+#  geometry: r, u differences 6, |r|^2 5, 1/sqrt 1, |r|^-2, |r|^-3, |r|^-5 3,
+#    r.u, A.r, B.r, B.u 20 -> 35;
+#  row: m |r|^-5 and its (B.r) product 2, the r coefficient 6, sum m |r|^-3 2,
+#    sum m |r|^-5 (r.u) 2, the u and r sums of H 12, sum (B.r) r 6 -> 30;
+#  body: A.r + B.u and s (B.r) 2, the two mass sums 4, |r|^-5 s and |r|^-5
+#    (B.r) 2, the r coefficient 4, the A, B and u/r sums 36 -> 48.
+ADJ_FLOPS_GEOMETRY = 35
+ADJ_FLOPS_ROW = 30
+ADJ_FLOPS_BODY = 48
 
 # MI355X published vector peaks (TFLOP/s): FP32 157.3, FP64 78.6.  Plain
 # (unpacked) FP32 instructions issue in 2 cycles per wave64 on gfx950 and
@@ -182,22 +183,22 @@ def small_blocks_leg(nb, ctx, dev, s, xp, vp, m, cap, precs):
 
 def adjoint_leg(nb, W, ctx, dev):
     """Adjoint of the regular force at N = 65536 Plummer + Kroupa, all bodies
-    active, FP64, in steady state; roofline by the algorithmic flops of both
-    passes over the whole call's time."""
+    active, FP64, in steady state; roofline by the algorithmic flops of its one
+    pass over the pairs and the whole call's time."""
     s5 = W.adjoint_plummer_n65536()
     n5 = s5["n"]
     a5 = [dev(s5[k]) for k in ("x", "v", "m", "i_block", "rs2", "w_a", "w_j")]
     ms = steady_ms(lambda: nb.regular_force_adjoint(*a5, ctx=ctx))
     pp = float(n5) * (n5 - 1)
-    ach = (ADJ_FLOPS_ROWS + ADJ_FLOPS_BODIES) * pp / ms * 1e-9
+    ach = (ADJ_FLOPS_GEOMETRY + ADJ_FLOPS_ROW + ADJ_FLOPS_BODY) * pp / ms * 1e-9
     log(f"adjoint: {ms:.2f} ms, {ach:.1f} TFLOP/s")
     return {"workload": f"N={n5} Plummer+Kroupa, all active, FP64",
             "ms": round(ms, 3), "gpairs_per_s_per_pass": round(pp / ms * 1e-6, 2),
             "roofline": {"bound": "alu", "achieved": round(ach, 2), "peak": PEAK_FP64,
                          "unit": "TFLOP/s", "frac": round(ach / PEAK_FP64, 4),
-                         "flops_per_pair": {"row_pass": ADJ_FLOPS_ROWS,
-                                            "body_pass": ADJ_FLOPS_BODIES},
-                         "time": "whole call (both passes and their reductions)"}}
+                         "flops_per_pair": {"geometry": ADJ_FLOPS_GEOMETRY, "row": ADJ_FLOPS_ROW,
+                                            "body": ADJ_FLOPS_BODY},
+                         "time": "whole call (the pass and its reductions)"}}
 
 
 def small_configs_leg(nb, W, ctx, dev, precs):
@@ -722,7 +723,7 @@ def main():
         "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": peak,
                      "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                      "traffic": profiled(dom, "hbm_bytes_per_launch"),
-                     "kernel": f"force_rows_kernel ({dom})",
+                     "kernel": f"force_packed_kernel ({dom})",
                      "flops_per_pair": FLOPS_PER_PAIR,
                      "issue_model_frac": profiled(dom, "issue_model_frac")},
         "cpu_baseline": cpu,

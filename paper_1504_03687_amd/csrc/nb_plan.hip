@@ -79,14 +79,13 @@ int64_t max_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, int r
 //    total, and at most kWaveMaxSplits splits per row; more splits only add
 //    merge work (measured at N = 2^20, n_i = 1 .. 255).
 //  * row per lane through LDS (mapping 3 with 64 rows a work-group, mapping 1
-//    with 256): about 8 waves per SIMD in total, down to min_split bodies,
+//    with 256): about 8 waves per SIMD in total, down to min_split bodies per split,
 //    at most kRowWaveMaxSplits splits.
 //    A lane that is alone on its SIMD takes 150 to 200 ns per pair, so long
 //    splits leave the chip waiting for few waves.  Whole calls, FP64, with
-//    splits of 512 bodies against this rule: 1024 rows of 1024 175 against 23
-//    us, 256 of 4096 136 against 23, 1024 of 16384 107 against 47 (128 splits
-//    44), 4096 of 16384 131 against 112, 256 of 131072 118 against 62 (1024
-//    splits 59).
+//    splits of 512 bodies against 64: 1024 rows of 1024 175 against 23 us, 256
+//    of 4096 136 against 23, 1024 of 16384 107 against 47 (128 splits 44), 4096
+//    of 16384 131 against 112, 256 of 131072 118 against 62 (1024 splits 59).
 //  * packed launches: many short waves even out their run-time differences, but
 //    every split adds a record per row to the merge: about 32 waves per SIMD,
 //    64 above 2^32 pairs.  FP64, per 32768 / 65536 waves: 16001 rows of 100003
