@@ -334,14 +334,15 @@ __global__ __launch_bounds__(kBlock) void merge_kernel(ForceArgs a)
     merge_row<W>(a, b, b < a.n_i, g);
 }
 
-// One work-group per row for plans with many splits.
+// One work-group per row for plans with many splits (B: see merge_row_wg).
+template <int B>
 __global__ __launch_bounds__(kBlock) void merge_wg_kernel(ForceArgs a)
 {
     __shared__ double lds[kSlotComp][kBlock / kWave];
     __shared__ int64_t scan[kBlock / kWave];
     const int64_t b = blockIdx.x;
     const MergeGeom g{a.splits, b * a.splits, 1, 0, a.n, a.split_len};
-    merge_row_wg(a, b, g, lds, scan);
+    merge_row_wg<B>(a, b, g, lds, scan);
 }
 
 __device__ __forceinline__ void write_forces(const ForceArgs &a, int64_t b, const double v[6])
@@ -677,7 +678,15 @@ hipError_t launch_merge(bool mixed, const ForceArgs &a, hipStream_t s)
 {
     (void)mixed;
     if (a.splits >= 256) {   // few rows, many splits: one work-group per row
-        hipLaunchKernelGGL(merge_wg_kernel, dim3((unsigned)a.n_i), dim3(kBlock), 0, s, a);
+        const dim3 grid((unsigned)a.n_i);
+        if (a.splits <= kBlock)
+            hipLaunchKernelGGL(merge_wg_kernel<1>, grid, dim3(kBlock), 0, s, a);
+        else if (a.splits <= 2 * kBlock)
+            hipLaunchKernelGGL(merge_wg_kernel<2>, grid, dim3(kBlock), 0, s, a);
+        else if (a.splits <= 4 * kBlock)
+            hipLaunchKernelGGL(merge_wg_kernel<4>, grid, dim3(kBlock), 0, s, a);
+        else
+            hipLaunchKernelGGL(merge_wg_kernel<8>, grid, dim3(kBlock), 0, s, a);
     } else {
         const int w = merge_width(a.splits);
         const int per = kBlock / w;

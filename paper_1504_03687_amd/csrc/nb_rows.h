@@ -1090,8 +1090,6 @@ __device__ __forceinline__ double redo_chunk_sum(const double (&w)[kBlock / kWav
     return t;
 }
 
-constexpr int kMergeBatch = 8;    // strides of split partials loaded per batch
-constexpr int kCountBatch = 8;    // segment counts loaded per batch
 
 // Copies entries [from, take) of the neighbour segment of split s (count c)
 // to dst: from its slot, or, for an overflowed segment, by rescanning the
@@ -1121,13 +1119,14 @@ __device__ __forceinline__ void copy_segment(const ForceArgs &a, const MergeGeom
     }
 }
 
-// Partial records of splits sb + u * kBlock (u < kMergeBatch) of one row;
+// Partial records of splits sb + u * kBlock (u < B) of one row;
 // past the last split, split 0's record is loaded (and not added).
+template <int B>
 __device__ __forceinline__ void merge_load_batch(const ForceArgs &a, const MergeGeom &g,
-                                                 int32_t sb, double (&t)[kMergeBatch][kSlotComp])
+                                                 int32_t sb, double (&t)[B][kSlotComp])
 {
 #pragma unroll
-    for (int u = 0; u < kMergeBatch; ++u) {
+    for (int u = 0; u < B; ++u) {
         const int32_t s = sb + u * kBlock;
         const double2 *p = slot_rec(a, g.slot0 + (int64_t)(s < g.splits ? s : 0) * g.slot_step);
 #pragma unroll
@@ -1139,12 +1138,13 @@ __device__ __forceinline__ void merge_load_batch(const ForceArgs &a, const Merge
     }
 }
 
+template <int B>
 __device__ __forceinline__ void merge_add_batch(int32_t S, int32_t sb,
-                                                const double (&t)[kMergeBatch][kSlotComp],
+                                                const double (&t)[B][kSlotComp],
                                                 double (&v)[kSlotComp])
 {
 #pragma unroll
-    for (int u = 0; u < kMergeBatch; ++u)
+    for (int u = 0; u < B; ++u)
         if (sb + u * kBlock < S) {
 #pragma unroll
             for (int k = 0; k < kSlotComp; ++k) v[k] += t[u][k];
@@ -1159,7 +1159,14 @@ __device__ __forceinline__ void merge_add_batch(int32_t S, int32_t sb,
 // segments, so the list stays in split order.  The work is laid out for few
 // memory round trips: a lane's counts are loaded with its partials, and the
 // first two entries of all its segments are loaded before any is stored.
+// B: strides of split partials, and segment counts, loaded per batch (the least
+// of 1, 2, 4, 8 that covers the splits in one; order and bits do not depend on
+// it).  Eight for every launch loaded split 0's record up to seven times more
+// for each lane and held 163 registers, one holds 100.  Whole calls: one row of
+// 2^20 (1024 splits) 18.3 us with eight, 17.3 so; 32 of 131072 (256) 18.2 and
+// 16.7, 1024 of 16384 (256) 44.7 and 41.3, 2048 of 131072 (256) 347 and 342.
 // Called once per work-group (its LDS arrays are not reused).
+template <int B>
 __device__ __forceinline__ void merge_row_wg(const ForceArgs &a, int64_t b, const MergeGeom &g,
                                              double (*lds)[kBlock / kWave], int64_t *scan)
 {
@@ -1172,37 +1179,37 @@ __device__ __forceinline__ void merge_row_wg(const ForceArgs &a, int64_t b, cons
     const int32_t s0 = tid * K;
     const int32_t nmine = s0 < S ? (S - s0 < K ? S - s0 : K) : 0;
 
-    // sums: the loads of kMergeBatch strides are issued before any is added,
+    // sums: the loads of B strides are issued before any is added,
     // so a lane waits on one memory latency per batch, not per split.  The
-    // first batch is issued ahead of the lane's first kCountBatch counts (the
+    // first batch is issued ahead of the lane's first B counts (the
     // memory counter waits in issue order), so both arrive in one round trip.
     double v[kSlotComp] = {0, 0, 0, 0, 0, 0, 0, 0};
-    double t[kMergeBatch][kSlotComp];
-    merge_load_batch(a, g, tid, t);
-    int32_t ck[kCountBatch];
+    double t[B][kSlotComp];
+    merge_load_batch<B>(a, g, tid, t);
+    int32_t ck[B];
 #pragma unroll
-    for (int u = 0; u < kCountBatch; ++u) {
+    for (int u = 0; u < B; ++u) {
         const int32_t s = s0 + u < S ? s0 + u : S - 1;   // in range; unused past nmine
         const int32_t c = a.seg_cnt[g.slot0 + (int64_t)s * g.slot_step];
         ck[u] = u < nmine ? c : 0;
     }
-    merge_add_batch(S, tid, t, v);
-    for (int32_t sb = tid + kBlock * kMergeBatch; sb < S; sb += kBlock * kMergeBatch) {
-        merge_load_batch(a, g, sb, t);
-        merge_add_batch(S, sb, t, v);
+    merge_add_batch<B>(S, tid, t, v);
+    for (int32_t sb = tid + kBlock * B; sb < S; sb += kBlock * B) {
+        merge_load_batch<B>(a, g, sb, t);
+        merge_add_batch<B>(S, sb, t, v);
     }
     int64_t mine = 0;
 #pragma unroll
-    for (int u = 0; u < kCountBatch; ++u) mine += ck[u];
-    for (int32_t sb = kCountBatch; sb < nmine; sb += kCountBatch) {   // K > kCountBatch
-        int32_t c[kCountBatch];
+    for (int u = 0; u < B; ++u) mine += ck[u];
+    for (int32_t sb = B; sb < nmine; sb += B) {   // K > B
+        int32_t c[B];
 #pragma unroll
-        for (int u = 0; u < kCountBatch; ++u) {
+        for (int u = 0; u < B; ++u) {
             const int32_t s = sb + u < nmine ? s0 + sb + u : s0;
             c[u] = a.seg_cnt[g.slot0 + (int64_t)s * g.slot_step];
         }
 #pragma unroll
-        for (int u = 0; u < kCountBatch; ++u) mine += sb + u < nmine ? c[u] : 0;
+        for (int u = 0; u < B; ++u) mine += sb + u < nmine ? c[u] : 0;
     }
 
     // one barrier for both reductions: wave butterflies of the sums and a
@@ -1237,23 +1244,23 @@ __device__ __forceinline__ void merge_row_wg(const ForceArgs &a, int64_t b, cons
 
     bool ovf = false, nonfin = false;
     if (!bad) {
-        // the lane's segments in batches of kCountBatch: the first two
+        // the lane's segments in batches of B: the first two
         // entries of every segment of a batch are loaded before any is stored
         int32_t *row = a.nb_list + b * (int64_t)a.cap;
         int64_t at = start;
-        for (int32_t sb = 0; sb < nmine && at < a.cap; sb += kCountBatch) {
+        for (int32_t sb = 0; sb < nmine && at < a.cap; sb += B) {
             if (sb > 0) {
 #pragma unroll
-                for (int u = 0; u < kCountBatch; ++u) {
+                for (int u = 0; u < B; ++u) {
                     const int32_t s = sb + u < nmine ? s0 + sb + u : s0;
                     const int32_t c = a.seg_cnt[g.slot0 + (int64_t)s * g.slot_step];
                     ck[u] = sb + u < nmine ? c : 0;
                 }
             }
-            int32_t e0[kCountBatch], e1[kCountBatch];
+            int32_t e0[B], e1[B];
             int64_t p = at;
 #pragma unroll
-            for (int u = 0; u < kCountBatch; ++u) {
+            for (int u = 0; u < B; ++u) {
                 const int32_t *src =
                     a.seg_list + (g.slot0 + (int64_t)(s0 + sb + u) * g.slot_step) * kSegCap;
                 const bool ok = ck[u] > 0 && ck[u] <= kSegCap && p < a.cap;
@@ -1262,7 +1269,7 @@ __device__ __forceinline__ void merge_row_wg(const ForceArgs &a, int64_t b, cons
                 p += ck[u];
             }
 #pragma unroll
-            for (int u = 0; u < kCountBatch; ++u) {
+            for (int u = 0; u < B; ++u) {
                 const int32_t c = ck[u];
                 if (c > 0 && at < a.cap) {
                     const int64_t take = (int64_t)c < a.cap - at ? c : a.cap - at;

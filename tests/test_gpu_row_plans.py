@@ -247,3 +247,34 @@ def test_even_splits_of_packed_launches(prec):
         assert np.array_equal(x, y)
     compare_force(auto, s["x"], s["v"], s["m"], ib, rs2, cap, TOL[prec],
                   rows=rng.choice(n_i, 64, replace=False))
+
+
+@pytest.mark.parametrize("splits", [256, 257, 512, 513, 1024, 1025, 2048, 2049])
+def test_merge_batches(splits):
+    """The work-group merge at the edges of its batches: short, long and
+    overflowed segments, a full list, rows without neighbours."""
+    n, n_i, cap = 64 * (2048 + splits % 2) - 5, 66, 700
+    say(f"merge of {splits} splits")
+    rng = np.random.default_rng(splits)
+    s = W.small_state(960, n, k_nn=40)
+    ib = rng.choice(n, n_i, replace=False).astype(np.int32)
+    rs2 = s["rs2"][ib].copy()
+    rs2[::5] *= 9.0
+    rs2[1::11] = 0.0
+    rs2[2::13] = (4.0 * np.abs(s["x"]).max()) ** 2
+    args = (dev(s["x"]), dev(s["v"]), dev(s["m"]), dev(ib), dev(rs2), cap, "fp64")
+    ctx = nb.Context(0)
+    try:
+        ctx.set_plan(3, 1, splits)
+        got = nb.regular_force(*args, ctx=ctx)
+        k = int(ctx.last_plan().split("splits=")[1].split()[0])
+        assert k == splits, ctx.last_plan()
+        ctx.set_plan(3, 1, 1)
+        one = nb.regular_force(*args, ctx=ctx)
+        torch.cuda.synchronize()
+    finally:
+        ctx.close()
+    for x, y in zip(_defined(got, cap)[2:], _defined(one, cap)[2:]):
+        assert np.array_equal(x, y)
+    some = np.setdiff1d(np.arange(n_i), np.arange(2, n_i, 13))   # rows with a regular force
+    compare_force(got, s["x"], s["v"], s["m"], ib, rs2, cap, TOL_FP64, rows=some[:32])
