@@ -94,27 +94,34 @@ int64_t max_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, int r
 constexpr int64_t kWaveMaxSplits = 1024;
 constexpr int64_t kRowWaveMaxSplits = 4096;
 
-// Split length of a packed launch, from the least one to twice that in steps of
-// 64 bodies: the one whose work-groups fill the CUs best.  Cost in pairs of the
-// whole chip: the work-groups of the fullest CU and one more for the end of the
-// launch, where few waves are left on each SIMD, each of kBlock rows by the
-// split's bodies; and 40 a record for the merge.  It orders whole calls as they
-// were measured: 4099 rows of 131072, splits of 512 (16.25 work-groups per CU)
-// 501 us mixed and 655 FP64, 768 (10.9) 491 and 633, 1024 (8.1) 535 and 685,
-// 1280 538 and 678, 2048 (4.06) 632 and 785.  Not below kMinPerCu work-groups
-// per CU: at little more than fit at once (10000 of 30000, 6.6 per CU instead of
-// 9.1) the last ones run alone, 312 us against 290.  Without and with this rule,
-// mixed / FP64: 4099 of 131072 501 / 646 and 487 / 627 us, 5500 634 / 843 and
-// 625 / 821, 7000 794 / 1065 and 771 / 1030, 8192 896 / 1207 and 884 / 1175.
+// Split length of a packed launch that its least length of 512 bounds, from 256
+// to 1024 in steps of 64 bodies: the one whose work-groups fill the CUs best.
+// Cost in pairs of the whole chip: the work-groups of the fullest CU and one more
+// for the end of the launch, where few waves are left on each SIMD, each of
+// kBlock rows by the split's bodies; and 40 a record for the merge.  It orders
+// whole calls as they were measured: 4099 rows of 131072, splits of 512 (16.25
+// work-groups per CU) 501 us mixed and 655 FP64, 768 (10.9) 491 and 633, 1024
+// (8.1) 535 and 685, 1280 538 and 678, 2048 (4.06) 632 and 785.  (100 a record:
+// 1500 of 131072 211 and 269, with 40 203 and 261.)  Not to less than kMinPerCu
+// work-groups per CU: at little more than fit at once (10000 of 30000, 6.6 per
+// CU instead of 9.1) the last ones run alone, 312 us against 290; blocks that
+// have fewer take 256.  Nor past kWave splits where 512 gives no more, which a
+// row's wave merges in one turn (10000 of 30000 291 and 402 us with 59, 300 and
+// 410 with 94).  Whole calls with 512 and with this rule, mixed / FP64: 9000 of
+// 16384 188 / 237 and 167 / 217 us, 3000 of 50000 185 / 228 and 164 / 210, 2049
+// of 65544 185 / 220 and 163 / 200, 1500 of 200000 321 / 412 and 302 / 393, 4099
+// of 131072 501 / 646 and 487 / 627, 7000 794 / 1065 and 771 / 1030; 4000 of
+// 65536 261 / 340 and 258 / 343.
 // Longer splits, whose number is the target's, gain nothing reliable by it (2222
 // of 2^20 1858 and 1896, 3333 2820 and 2775 us).
 static int64_t even_split_len(int64_t cus, int64_t n, int32_t n_i)
 {
-    constexpr int64_t kWaves = nb::kBlock / nb::kWave, kMinPerCu = 10, kLeast = 2 * nb::kTile;
+    constexpr int64_t kWaves = nb::kBlock / nb::kWave, kMinPerCu = 10, kLeast = nb::kTile;
     const int64_t tiles = ((int64_t)n_i + nb::kWave - 1) / nb::kWave;
     int64_t best = kLeast, least = INT64_MAX;
-    for (int64_t l = kLeast; l <= 2 * kLeast; l += nb::kWave) {
+    for (int64_t l = kLeast; l <= 4 * kLeast; l += nb::kWave) {
         const int64_t s = (n + l - 1) / l;
+        if (s > nb::kWave && n <= 2 * nb::kTile * (int64_t)nb::kWave) continue;
         const int64_t per_cu = ((tiles * s + kWaves - 1) / kWaves + cus - 1) / cus;
         if (per_cu < kMinPerCu) break;
         const int64_t cost = (per_cu + 1) * cus * nb::kBlock * l + n_i * s * 40;
