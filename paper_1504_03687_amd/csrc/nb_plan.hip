@@ -26,16 +26,18 @@ int64_t bucket_log2(int64_t v)
 // and runs the scalar-operand kernel.  The pack costs a launch and a copy of
 // the j-set (about 3 us at n = 131072, 25 us at 2^20), and a wave alone on its
 // SIMD waits longer for scalar loads than for LDS, so the block has to be
-// large enough to repay both.  Whole calls, LDS against packed, mixed / FP64:
-// 16384 rows of 131072 1959 / 2735 against 1812 / 2487 us, 4096 rows of
-// 131072 522 / 699 against 493 / 644, 16384 rows of 16384 306 / 390 against
-// 295 / 363, 1024 rows of 2^20 975 / 1325 against 948 / 1243; the two meet at
-// 1024 rows of 131072 (186 / 195 against 193 / 198) and 512 rows of 2^20 (483
-// / 673 against 486 / 659); 256 rows of 2^20 260 / 351 against 280 / 365.
+// large enough to repay both: above 2^26 pairs from 1024 rows on, above 2^27
+// from 512.  Whole calls, LDS against packed, mixed / FP64: 16384 rows of 131072
+// 1959 / 2735 against 1812 / 2487 us, 1024 of 131072 157 / 188 against 153 / 184,
+// 2048 of 65536 159 / 193 against 151 / 187, 8000 of 16384 158 / 197 against 152
+// / 195, 5000 of 16384 117 / 141 against 112 / 131, 9000 of 9000 117 / 142 against
+// 113 / 135, 1100 of 65536 109 / 125 against 109 / 122; with fewer rows 900 of
+// 131072 149 / 176 against 151 / 179, 550 of 131072 104 / 116 against 112 / 123;
+// 256 of 2^20 260 / 351 against 280 / 365.
 bool pack_pays(int mapping, int rows_per_lane, int64_t n, int32_t n_i)
 {
     return mapping == 1 && rows_per_lane == 1 && n_i >= 512 &&
-           n * (int64_t)n_i > (int64_t(1) << 27);
+           n * (int64_t)n_i > (int64_t(1) << (n_i >= 1024 ? 26 : 27));
 }
 
 // Row groups of a launch: waves in mappings 2 and 3, work-groups of four

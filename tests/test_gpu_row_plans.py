@@ -23,7 +23,8 @@ def _defined(out, cap):
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
 @pytest.mark.parametrize("n,n_i,splits", [(65537, 2049, 7), (65567, 4096, 1), (140001, 1000, 0),
-                                          (30011, 4600, 3), (65535, 2100, 1)])
+                                          (30011, 4600, 3), (65535, 2100, 1),
+                                          (16390, 4300, 5)])
 def test_packed_equals_lds_pass(n, n_i, splits, prec):
     """n and n_i one past and one short of the runs and tiles; several splits,
     one (direct stores), and the automatic count; duplicate rows, a bad index
