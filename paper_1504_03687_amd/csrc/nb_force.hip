@@ -567,14 +567,28 @@ void bind_redo_scratch(ForceArgs &a, void *base, int32_t *counter, int32_t group
     a.redo_rcap = redo_rcap_for(a.n_i, a.redo_chunks, rcap_limit);
 }
 
-template <int R>
-static hipError_t launch_redo_t(const ForceArgs &a, hipStream_t s)
+// Work-groups of the refinement launch: no more than the most items that a call
+// of n_i rows can list, in groups of R; half of redo_groups where few rows can
+// be listed.  Mostly none are, and after a launch of eight work-groups per CU
+// that all leave at once the next call's one-wave work-groups spread worse over
+// the SIMDs.  Force pass of 64 rows after 2048 idle work-groups, 1024 and none:
+// 524288 bodies in 2048 splits 61.6, 52.2 and 52.0 us, 262144 38.7, 34.0 and
+// 33.8; 1024 rows of 131072, some of which are refined, 156.1 us a call with
+// either.
+int32_t redo_grid(const ForceArgs &a, int R)
 {
-    // no more work-groups than the most items a call of n_i rows can list
     const int64_t rows = std::max<int64_t>(a.n_i, 1);
     const int64_t par = std::min<int64_t>(rows, a.redo_rcap);
     const int64_t items = std::max((par + R - 1) / R * a.redo_chunks, rows - par);
-    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(a.redo_groups, items));
+    const int64_t most = rows <= kFusedRedoRows ? (a.redo_groups + 1) / 2 : a.redo_groups;
+    return (int32_t)std::max<int64_t>(1, std::min(most, items));
+}
+
+template <int R>
+static hipError_t launch_redo_t(const ForceArgs &a, hipStream_t s)
+{
+    const int64_t par = std::min<int64_t>(std::max<int64_t>(a.n_i, 1), a.redo_rcap);
+    const int32_t grid = redo_grid(a, R);
     if (par <= kFusedRedoRows) {
         hipLaunchKernelGGL((redo_kernel<true, R>), dim3((unsigned)grid), dim3(kBlock), 0, s, a);
         return hipGetLastError();

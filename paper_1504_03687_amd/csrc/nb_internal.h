@@ -108,6 +108,7 @@ int32_t redo_groups_for(int cu_count);
 size_t redo_scratch_bytes(int32_t n_i, int64_t max_len, int32_t rcap_limit = 0);
 void bind_redo_scratch(ForceArgs &a, void *base, int32_t *counter, int32_t groups,
                        int64_t max_len, int32_t rcap_limit = 0);
+int32_t redo_grid(const ForceArgs &a, int rows_per_item);
 // one_range: every row of the launch has the same j-range (single-block calls).
 hipError_t launch_redo(const ForceArgs &a, bool one_range, hipStream_t s);
 

@@ -1,0 +1,37 @@
+// Prints what the library's host-side plan rules decide, for queries read from
+// stdin, one line each: a context of 256 CUs that launches nothing.
+#include <cstdio>
+#include <cstring>
+
+#include "nbreg.h"
+#include "nb_internal.h"
+#include "nb_runtime.h"
+
+int main()
+{
+    nb_ctx ctx;
+    ctx.cu_count = 256;
+    char what[32];
+    while (std::scanf("%31s", what) == 1) {
+        if (!std::strcmp(what, "plan")) {   // n n_i mixed
+            long long n, n_i, mixed;
+            if (std::scanf("%lld %lld %lld", &n, &n_i, &mixed) != 3) return 1;
+            nb::Plan p = nbrt::auto_plan(&ctx, n, (int32_t)n_i, mixed != 0);
+            int64_t len = 0;
+            nbrt::finish_plan(p, n, (int32_t)n_i, &len);
+            std::printf("%d %d %d %lld\n", p.mapping, p.rows_per_lane, p.splits, (long long)len);
+        } else if (!std::strcmp(what, "redo")) {   // n n_i rows_per_item
+            long long n, n_i, per;
+            if (std::scanf("%lld %lld %lld", &n, &n_i, &per) != 3) return 1;
+            nb::ForceArgs a{};
+            a.n = n;
+            a.n_i = (int32_t)n_i;
+            int32_t words[64] = {};
+            nb::bind_redo_scratch(a, nullptr, words, nb::redo_groups_for(ctx.cu_count), n);
+            std::printf("%d %d\n", nb::redo_grid(a, (int)per), nb::redo_groups_for(ctx.cu_count));
+        } else {
+            return 1;
+        }
+    }
+    return 0;
+}
