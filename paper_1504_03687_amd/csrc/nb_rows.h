@@ -350,7 +350,14 @@ __device__ __forceinline__ void take_hits(Row<MIXED> &R, int32_t jb, bool classi
 // candidates.  One minimum and one compare decide for both j whether any lane
 // has a rare case (NaN squared distances are never below the bound, alone or
 // in the minimum), and a pair handled there gets an excluding squared
-// distance, so the common path holds no select.  Every accumulator receives
+// distance, so the common path holds no select.  But the mixed LDS pass that
+// handles rare pairs at once does select, and handles them after the FP32 terms
+// (which touch other sums, so the bits are the same): there every LDS read of
+// the two bodies goes out before the first arithmetic, and the small blocks
+// that run it have one or two waves per SIMD, which wait for them.  Force pass
+// of 64 rows, rare pairs first against last: 524288 bodies in 512, 1024, 4096
+// splits 153.8 / 80.1 / 46.0 against 138.8 / 73.4 / 45.4 us, 262144 86.1 / 47.9
+// / 31.0 against 78.7 / 44.1 / 30.5.  Every accumulator receives
 // the terms of j and then j+1, as a loop over single j would give them.
 // RUN: rare pairs are marked, not handled (bit: the first pair's place in the run).
 template <bool MIXED, bool RUN, class Body, class Near>
@@ -364,16 +371,27 @@ __device__ __forceinline__ void pair_rows2(Row<MIXED> &R, const Body &J0, const 
         const float fx1 = (float)dx1, fy1 = (float)dy1, fz1 = (float)dz1;
         float r0 = __builtin_fmaf(fz0, fz0, __builtin_fmaf(fy0, fy0, fx0 * fx0));
         float r1 = __builtin_fmaf(fz1, fz1, __builtin_fmaf(fy1, fy1, fx1 * fx1));
-        if (__builtin_fminf(r0, r1) < R.candf) {
+        constexpr bool kTermsFirst = !RUN && !Body::kPacked;
+        const bool rare = __builtin_fminf(r0, r1) < R.candf;
+        float e0 = r0, e1 = r1;
+        if constexpr (kTermsFirst) {
+            e0 = r0 < R.candf ? kExclR2F : r0;
+            e1 = r1 < R.candf ? kExclR2F : r1;
+        } else if (rare) {
             if constexpr (RUN) {
-                mark_mixed(R, r0, r1, bit, classify);
+                mark_mixed(R, e0, e1, bit, classify);
             } else {
+                rare_mixed(R, J0, jidx0, e0, dx0, dy0, dz0, N);
+                rare_mixed(R, J1, jidx0 + 1, e1, dx1, dy1, dz1, N);
+            }
+        }
+        accum_mixed(R.S, fx0, fy0, fz0, e0, J0.vx - R.vx, J0.vy - R.vy, J0.vz - R.vz, J0.m32);
+        accum_mixed(R.S, fx1, fy1, fz1, e1, J1.vx - R.vx, J1.vy - R.vy, J1.vz - R.vz, J1.m32);
+        if constexpr (kTermsFirst)
+            if (rare) {
                 rare_mixed(R, J0, jidx0, r0, dx0, dy0, dz0, N);
                 rare_mixed(R, J1, jidx0 + 1, r1, dx1, dy1, dz1, N);
             }
-        }
-        accum_mixed(R.S, fx0, fy0, fz0, r0, J0.vx - R.vx, J0.vy - R.vy, J0.vz - R.vz, J0.m32);
-        accum_mixed(R.S, fx1, fy1, fz1, r1, J1.vx - R.vx, J1.vy - R.vy, J1.vz - R.vz, J1.m32);
     } else {
         const double dx0 = J0.x - R.x, dy0 = J0.y - R.y, dz0 = J0.z - R.z;
         const double dx1 = J1.x - R.x, dy1 = J1.y - R.y, dz1 = J1.z - R.z;
