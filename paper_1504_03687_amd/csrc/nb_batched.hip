@@ -296,8 +296,14 @@ static bool batched_pack_pays(const BatchedCache *c)
 // and 758 / 186, 32 of 4000 701 / 544 and 720 / 643, 160 of 600 to 4000 798 /
 // 585 and 1052 / 817, 12 of 3000 to 32768 1614 / 1449 and 2087 / 1973; at 165
 // waves per CU (96 of 1024 to 32768) 5587 against 5818 us with 1024.
+// In small clusters the chain is short and the merge much of the call: below
+// kFullWaves * kFullBodies bodies (the mean over the rows) proportionally fewer
+// waves are enough.  Split / whole at so many waves per CU, mixed: 1000 bodies
+// 230 / 239 us at 9.4 and 261 / 241 at 10.6, 600 108 / 130 at 5.9 and 211 / 166
+// at 9.8, 400 180 / 115 at 8.2, 300 82 / 85 at 5.9 and 181 / 109 at 9.8, 250 43
+// / 57 at 1.6, 63 / 63 at 3.9 and 93 / 76 at 7.8.
 constexpr int64_t kSplitLen = 2048, kMinSplitLen = 64;
-constexpr int64_t kTailWaves = 64, kFullWaves = 11;
+constexpr int64_t kTailWaves = 64, kFullWaves = 11, kFullBodies = 100;
 
 // Splits of at most len bodies of a cluster of nc bodies; less than 7/4 of
 // len stays whole (and needs no merge).
@@ -341,7 +347,9 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     int64_t len = kSplitLen;
     if (c->forced_splits <= 0 && !c->coarse) {
         if (waves(len) < kTailWaves * cus) len /= 2;
-        while (len > kMinSplitLen && waves(len) < kFullWaves * cus) len /= 2;
+        const double bodies = total_work / std::max<double>(1.0, (double)c->i_off[(size_t)C]);
+        const double full = (double)cus * std::min<double>(kFullWaves, bodies / kFullBodies);
+        while (len > kMinSplitLen && (double)waves(len) < full) len /= 2;
     }
     const int64_t U = c->forced_splits > 0 ? nb::kSplitUnit
                                            : std::min<int64_t>(len, nb::kSplitUnit);
