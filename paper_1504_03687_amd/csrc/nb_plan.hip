@@ -57,11 +57,19 @@ static int64_t row_groups(int32_t n_i, int mapping, int rows)
 // FP64 / mixed, 1024 rows of 1024 24.0 / 36.0 against 17.4 / 29.8 us, 256 of
 // 4096 22.7 / 32.3 against 18.3 / 28.1, 1024 of 4096 (one wave per SIMD) 26.4
 // / 38.6 against 24.7 / 37.6; past that it loses, 4096 of 4096 (four waves)
-// 46.6 / 51.2 against 50.3 / 58.3.
+// 46.6 / 51.2 against 50.3 / 58.3.  128 above kShortSplitBodies bodies, whose
+// splits of 64 would be more than 2048 a row: splits of 64 against 128, 41 rows
+// of 200000 37.0 / 34.0 against 34.8 / 31.8 us, 41 of 262144 41.7 / 40.0 against
+// 37.6 / 36.8, 64 of 262144 44.0 / 41.9 against 39.8 / 40.7, 100 of 262144 62.0 /
+// 57.0 against 57.0 / 54.3; 41 of 131072 26.8 / 33.8 against 27.2 / 34.4, 64 of
+// 131072 28.0 / 27.0 against 28.8 / 28.0.
+constexpr int64_t kShortSplitBodies = 131072;
+
 static int64_t min_split(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, int rows)
 {
     if (mapping == 2) return 4 * nb::kWave;
     if (pack_pays(mapping, rows, n, n_i)) return 2 * nb::kTile;
+    if (n > kShortSplitBodies) return 2 * nb::kWave;
     const int64_t simds = 4 * (int64_t)(ctx->cu_count > 0 ? ctx->cu_count : 256);
     const int64_t waves = row_groups(n_i, mapping, rows) * (mapping == 1 ? nb::kBlock / nb::kWave : 1) *
                           ((n + nb::kWave - 1) / nb::kWave);

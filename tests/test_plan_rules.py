@@ -46,3 +46,14 @@ def test_refinement_grid_of_small_calls(rules):
     assert rules("redo 1048576 1025 2")[0] == [2048, 2048]
     assert rules("redo 1024 300 2")[0] == [300, 2048]      # a work-group per row
     assert rules("redo 2049 1 2")[0] == [2, 2048]          # two chunks of one row
+
+
+def test_short_splits_of_long_ranges(rules):
+    """Small blocks: splits of 64 bodies up to 131072 bodies, of 128 above."""
+    for n, n_i, length in ((131072, 41, 64), (131072, 64, 64), (131073, 41, 128),
+                           (200000, 64, 128), (262144, 100, 128), (262144, 41, 128),
+                           (1 << 20, 64, 256)):
+        for mixed in (0, 1):
+            mapping, rows, splits, got = rules(f"plan {n} {n_i} {mixed}")[0]
+            assert (mapping, rows, got) == (3, 1, length)
+            assert splits == -(-n // length)
