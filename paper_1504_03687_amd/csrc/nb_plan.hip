@@ -114,10 +114,14 @@ constexpr int64_t kRowWaveMaxSplits = 4096;
 // (8.1) 535 and 685, 1280 538 and 678, 2048 (4.06) 632 and 785.  (100 a record:
 // 1500 of 131072 211 and 269, with 40 203 and 261.)  Not to less than kMinPerCu
 // work-groups per CU: at little more than fit at once (10000 of 30000, 6.6 per
-// CU instead of 9.1) the last ones run alone, 312 us against 290; blocks that
-// have fewer take 256.  Nor past kWave splits where 512 gives no more, which a
-// row's wave merges in one turn (10000 of 30000 291 and 402 us with 59, 300 and
-// 410 with 94).  Whole calls with 512 and with this rule, mixed / FP64: 9000 of
+// CU instead of 9.1) the last ones run alone, 312 us against 290.  Nor past
+// kWave splits where 512 gives no more, which a row's wave merges in one turn
+// (10000 of 30000 291 and 402 us with 59, 300 and 410 with 94); but blocks that
+// come to fewer than kMinPerCu at the shortest length of those take 256 however
+// many splits that is: 2500 of 30000 109 and 124 us with 118, 131 and 151 with
+// 59, 4099 of 24576 136 and 163 with 96, 146 and 173 with 64 of 384, 4099 of
+// 32768 163 and 200 with 128, 185 and 222 with 64; 6000 of 17000 136 and 165
+// with 67, 131 and 156 with 54 is the largest loss.  Whole calls with 512 and with this rule, mixed / FP64: 9000 of
 // 16384 188 / 237 and 167 / 217 us, 3000 of 50000 185 / 228 and 164 / 210, 2049
 // of 65544 185 / 220 and 163 / 200, 1500 of 200000 321 / 412 and 302 / 393, 4099
 // of 131072 501 / 646 and 487 / 627, 7000 794 / 1065 and 771 / 1030; 4000 of

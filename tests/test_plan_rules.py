@@ -57,3 +57,13 @@ def test_short_splits_of_long_ranges(rules):
             mapping, rows, splits, got = rules(f"plan {n} {n_i} {mixed}")[0]
             assert (mapping, rows, got) == (3, 1, length)
             assert splits == -(-n // length)
+
+
+def test_even_splits_of_packed_blocks(rules):
+    """Packed launches: at most 64 splits where 512 bodies a split give no more,
+    but 256 bodies a split where even that leaves a CU few work-groups."""
+    for n, n_i, splits, length in ((30000, 10000, 59, 512), (32768, 16384, 64, 512),
+                                   (24576, 4099, 96, 256), (30000, 2500, 118, 256),
+                                   (16384, 9000, 64, 256), (131072, 4099, 187, 704)):
+        for mixed in (0, 1):
+            assert rules(f"plan {n} {n_i} {mixed}")[0] == [1, 1, splits, length]
