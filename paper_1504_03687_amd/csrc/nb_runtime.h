@@ -80,7 +80,9 @@ struct nb_ctx {
     double ms[NB_NCLASS] = {};
     int64_t launches[NB_NCLASS] = {};
     // device words owned by the context for its whole life (never reallocated):
-    // [0] the refinement counter of nb_regular_force
+    // [0] the refinement counter of nb_regular_force, [16] the refinement's
+    // arrival word, [kSchedWord ...] the counts of a scheduler build of up to
+    // 16384 items
     int32_t *words = nullptr;
     // device address of the library's fixed workspace on this context's
     // device (nb_regular_force_noalloc); shared by every context on the device
@@ -95,6 +97,8 @@ struct nb_ctx {
 };
 
 namespace nbrt {
+constexpr int kSchedWord = 64, kSchedWords = 320;
+constexpr size_t kWordBytes = (kSchedWord + kSchedWords) * sizeof(int32_t);
 int hip_fail(nb_ctx *ctx, hipError_t e);
 int ensure_scratch(nb_ctx *ctx, size_t bytes);
 int ensure_aux(nb_ctx *ctx, size_t bytes);

@@ -193,9 +193,9 @@ int nb_ctx_create(nb_ctx **out, int device, void *hip_stream)
         int prev = 0;
         (void)hipGetDevice(&prev);
         hipError_t e = hipSetDevice(device);
-        if (e == hipSuccess) e = hipMalloc((void **)&ctx->words, 256);
+        if (e == hipSuccess) e = hipMalloc((void **)&ctx->words, nbrt::kWordBytes);
         // the refinement's arrival word must start at zero (it resets itself)
-        if (e == hipSuccess) e = hipMemset(ctx->words, 0, 256);
+        if (e == hipSuccess) e = hipMemset(ctx->words, 0, nbrt::kWordBytes);
         if (e == hipSuccess) e = fixed_scratch_of(device, &ctx->fixed_scratch);
         (void)hipSetDevice(prev);
         if (e != hipSuccess) {

@@ -22,9 +22,9 @@
 // of that level (a running per-wave count in LDS); the per-level wave counts
 // are then scanned across waves (and work-groups) in item order, so the
 // build is stable.  All rounds' gathers are issued before any is used.
-//   <= 8192 items, or <= 16384 while the context holds no scratch: one
-//            work-group of 1024 threads does the whole sort in one launch, in
-//            place (every read of the list precedes the first write);
+//   <= 10240 items (an update: <= 16384): one work-group of 1024 threads does the
+//            whole sort in one launch, in place (every read of the list
+//            precedes the first write);
 //   larger:  two launches: count (4096 items per work-group: per-level
 //            counts stored level-major [K][blocks], a per-block range flag,
 //            and for an update a copy of the prefix), then scatter (each
@@ -51,10 +51,11 @@ constexpr int kMwItems = kMwThreads * kMwRounds;
 // single-work-group path
 constexpr int kSwThreads = 1024;
 constexpr int kSwItems = kSwThreads * kRounds;
-// a build of more than this many items is faster in two launches (16384 items:
-// 16 us in one work-group, 10 in two launches), which are taken if their scratch
-// is there; an update is not (10766 items 10.9 against 12.9 us)
-constexpr int kSwFewItems = 8192;
+// a build of more than this many items is faster in two launches (8193 items 10.7
+// us in one work-group, 11.1 in two launches, 10000 11.7 and 11.4, 12000 13.2 and
+// 11.1, 16384 16.5 and 11.2; with an update of 500 items behind it 10000 16.7 and
+// 17.4, 16384 21.4 and 17.2); an update is not (10766 items 10.9 against 12.9)
+constexpr int kSwFewItems = 10240;
 
 __device__ __forceinline__ uint32_t lane_rank(uint64_t mask)
 {
@@ -362,18 +363,27 @@ struct SchedScratch {
 };
 
 // Scratch of the multi-work-group path: hist [K][nblk], bad_blk [nblk] and
-// (update) a copy of the prefix; null for the single-work-group path, which
-// sorts up to kSwItems items without scratch.
+// (update) a copy of the prefix; null for the single-work-group path.  Builds
+// of up to kSwItems items keep theirs in the context's own words: such a call
+// allocates nothing, so it can be captured on a fresh context, and a captured
+// one outlives the growth of the context's scratch.
+constexpr int kSchedCtxBlocks = kSwItems / kMwItems;
+static_assert((kMaxLevels + 1) * kSchedCtxBlocks <= nbrt::kSchedWords, "room in the context's words");
+
 int sched_prepare(nb_ctx *ctx, int32_t n_items, int32_t K, bool in_place, SchedScratch &s)
 {
     s = SchedScratch{};
     if (n_items <= (in_place ? kSwItems : kSwFewItems)) return NB_OK;
     const int32_t nblk = (n_items + kMwItems - 1) / kMwItems;
+    if (n_items <= kSwItems) {
+        s.hist = ctx->words + nbrt::kSchedWord;
+        s.bad_blk = s.hist + (int64_t)K * nblk;
+        return NB_OK;
+    }
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t h = up(sizeof(int32_t) * (size_t)nblk * K);
     const size_t f = up(sizeof(int32_t) * (size_t)nblk);
     const size_t c = in_place ? up(sizeof(int32_t) * (size_t)n_items) : 0;
-    if (n_items <= kSwItems && ctx->scratch_bytes < h + f + c) return NB_OK;
     const int rc = nbrt::ensure_scratch(ctx, h + f + c);
     if (rc != NB_OK) return rc;
     char *p = (char *)ctx->scratch;
