@@ -531,10 +531,11 @@ static int32_t redo_chunks_for(int64_t max_len)
 // work-group then holds the whole sum, and partial, arrival and final pass only
 // add memory round trips (mixed calls, through the buffer against straight to
 // the outputs: 1024 rows of 1024 29.7 against 23.9 us, 2048 of 2048 36.0
-// against 32.3; of two chunks a row is no faster one after the other).
+// against 32.3; of two chunks a row is no faster one after the other).  limit: at
+// most so many rows (0: automatic, negative: none, the least scratch).
 static int32_t redo_rcap_for(int32_t n_i, int32_t chunks, int32_t limit)
 {
-    if (chunks == 1) return 0;
+    if (chunks == 1 || limit < 0) return 0;
     int64_t r = kRedoPartItems / chunks;
     if (limit > 0 && r > limit) r = limit;
     if (r < 1) r = 1;

@@ -265,4 +265,66 @@ void finish_plan(Plan &p, int64_t n, int32_t n_i, int64_t *split_len)
     (void)n_i;
 }
 
+// Fewest splits that a call without room for its plan's is lowered to: splits of
+// 512 bodies, or of 128 in one-wave work-groups, as many as still put 16 waves
+// on each SIMD (4 of the one-wave work-groups).  With fewer most of the chip
+// would idle, so the call is refused instead.
+int least_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, const Plan &p)
+{
+    if (p.mapping == 2) return p.splits;
+    const int64_t cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
+    const int64_t u1 = row_groups(n_i, 1, 1), u3 = row_groups(n_i, 3, 1);
+    const bool narrow = u1 * nb::kBlock * 5 > u3 * nb::kWave * 6;
+    const int64_t unit = narrow ? nb::kWave : nb::kTile;
+    const int64_t s = std::min(narrow ? (16 * cus + u3 - 1) / u3 : (64 * cus + u1 - 1) / u1,
+                               (n + 2 * unit - 1) / (2 * unit));
+    const int64_t len = ((n + unit - 1) / unit + s - 1) / s * unit;
+    return (int)std::min<int64_t>(p.splits, (n + len - 1) / len);
+}
+
+// The plan and its scratch within 'budget' bytes: what does not fit shrinks the
+// refinement's chunk partials to half of the budget first (rows past them
+// are summed one work-group each, to the same bits), then the split count down
+// to 'least', then the partials further; the packed j-set takes what is left,
+// if that is enough.  total() > budget: not even the least fits.
+ForceScratch fit_scratch(const nb_ctx *ctx, int64_t n, int32_t n_i, const Plan &wanted,
+                         bool refine, int least, size_t budget)
+{
+    ForceScratch f{};
+    f.p = wanted;
+    finish_plan(f.p, n, n_i, &f.split_len);
+    f.rcap = ctx->redo_rows_limit;
+    f.redo = refine ? nb::redo_scratch_bytes(n_i, n, f.rcap) : 0;
+    f.slots = nb::force_scratch_bytes(f.p, n_i);
+    const size_t pack = pack_pays(f.p.mapping, f.p.rows_per_lane, n, n_i) ? nb::packed_bytes(n) : 0;
+    f.pack = pack;
+    if (f.total() <= budget) {
+        f.least = f.total() == 0;
+        return f;
+    }
+    f.pack = 0;
+    auto shrink_redo = [&](size_t most) {
+        if (f.redo > most && f.rcap == 0) f.rcap = n_i;
+        while (f.redo > most && f.rcap > 0) {
+            f.rcap = f.rcap > 1 ? f.rcap / 2 : -1;
+            f.redo = nb::redo_scratch_bytes(n_i, n, f.rcap);
+        }
+    };
+    shrink_redo(budget / 2);
+    const size_t room = budget > f.redo ? budget - f.redo : 0;
+    const size_t per_split = (nb::kSlotComp * sizeof(double) + sizeof(int32_t) +
+                              nb::kSegCap * sizeof(int32_t)) * (size_t)std::max(n_i, 1);
+    while (f.p.splits > least && f.slots > room) {
+        const int64_t s = std::max<int64_t>(
+            least, std::min<int64_t>((int64_t)(room / per_split), f.p.splits - 1));
+        f.p.splits = (int)std::max<int64_t>(1, s);
+        finish_plan(f.p, n, n_i, &f.split_len);
+        f.slots = nb::force_scratch_bytes(f.p, n_i);
+    }
+    if (f.slots + f.redo > budget) shrink_redo(budget > f.slots ? budget - f.slots : 0);
+    if (f.total() + pack <= budget) f.pack = pack;
+    f.least = f.p.splits <= least && f.pack == 0 && (f.redo == 0 || f.rcap < 0);
+    return f;
+}
+
 }  // namespace nbrt

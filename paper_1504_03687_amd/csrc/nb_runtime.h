@@ -44,6 +44,15 @@ struct PlanNote {
     int64_t split_len;
     bool asked_mixed, mixed, fixed, packed;
 };
+// Plan and scratch of a single-block call in a given memory budget.
+struct ForceScratch {
+    nb::Plan p;
+    int64_t split_len;
+    int32_t rcap;               // limit of the refinement's buffered rows (redo_scratch_bytes)
+    size_t redo, slots, pack;   // bytes (pack 0: the LDS kernels)
+    bool least;                 // no smaller one is left to try
+    size_t total() const { return redo + slots + pack; }
+};
 struct BatchedCache;   // defined in nb_batched.hip
 void batched_release(nb_ctx *ctx);
 }  // namespace nbrt
@@ -112,4 +121,7 @@ int64_t default_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, i
 bool pack_pays(int mapping, int rows_per_lane, int64_t n, int32_t n_i);
 int split_step(int mapping, int64_t splits, int64_t n);
 void finish_plan(nb::Plan &p, int64_t n, int32_t n_i, int64_t *split_len);
+int least_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, const nb::Plan &p);
+ForceScratch fit_scratch(const nb_ctx *ctx, int64_t n, int32_t n_i, const nb::Plan &p,
+                         bool refine, int least, size_t budget);
 }  // namespace nbrt

@@ -76,6 +76,14 @@ static int ensure_buffer(nb_ctx *ctx, void **buf, size_t *have, size_t bytes)
 {
     if (bytes <= *have) return NB_OK;
     if (ctx->scratch_limit && bytes > ctx->scratch_limit) return NB_ERR_OOM;
+    // nothing can be allocated while the stream is being captured; trying would
+    // end the capture
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return NB_ERR_OOM;
+    }
+    if (cap != hipStreamCaptureStatusNone) return NB_ERR_OOM;
     if (*buf) {
         // the old buffer may still be in use by queued work on the stream
         hipError_t e = hipStreamSynchronize(ctx->stream);
@@ -341,7 +349,8 @@ namespace nbrt {
 // otherwise it is the caller-supplied device workspace of fixed_bytes, no
 // allocation and no event creation happens, and the plan's split count is
 // lowered until its scratch fits (NB_ERR_TOO_LARGE when even one split does
-// not).
+// not).  Automatic split counts are also lowered, to least_splits, where the
+// scratch limit or the device has no room for theirs.
 static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const double *vp,
                               const double *m, int32_t n_i, const int32_t *i_block,
                               const double *rs2, int32_t nb_cap, nb_precision prec,
@@ -375,9 +384,6 @@ static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const do
         p.f64 = ctx->forced.f64;   // a forced plan runs the requested kernels
     }
     const bool mixed = prec == NB_MIXED && !p.f64;
-    int64_t split_len = 0;
-    finish_plan(p, n, n_i, &split_len);
-
     nb::ForceArgs fa{};
     fa.n = n;
     fa.xp = xp;
@@ -396,52 +402,32 @@ static int regular_force_impl(nb_ctx *ctx, int64_t n, const double *xp, const do
     fa.redo_k = mixed ? redo_k(ctx) : 0.0;
     fa.near_factor = n >= nb::kNearMinBodies ? nb::kNearFactor : 1.0f;
     const int32_t groups = nb::redo_groups_for(ctx->cu_count);
-    void *base = nullptr;
-    int32_t rcap_limit = ctx->redo_rows_limit;   // 0: automatic
-    size_t redo_bytes = fa.redo_k > 0.0 ? nb::redo_scratch_bytes(n_i, n, rcap_limit) : 0;
+    // an explicit split count is lowered for the fixed workspace only
+    const bool refine = fa.redo_k > 0.0;
+    const int least = fixed ? 1
+                      : ctx->has_forced && ctx->forced.splits ? ctx->forced.splits
+                                                              : least_splits(ctx, n, n_i, p);
+    const size_t limit = fixed ? fixed_bytes : ctx->scratch_limit ? ctx->scratch_limit : SIZE_MAX;
+    ForceScratch f = fit_scratch(ctx, n, n_i, p, refine, least, limit);
+    void *base = fixed;
     if (fixed) {
-        // the refinement's chunk partials shrink first (rows past them are
-        // summed one work-group each, to the same bits), then the splits
-        for (rcap_limit = rcap_limit > 0 ? rcap_limit : (int32_t)nb::kRedoPartItems;
-             redo_bytes > fixed_bytes / 2 && rcap_limit > 1; rcap_limit /= 2)
-            redo_bytes = nb::redo_scratch_bytes(n_i, n, rcap_limit / 2);
-        if (redo_bytes > fixed_bytes) return NB_ERR_TOO_LARGE;
-        const size_t room = fixed_bytes - redo_bytes;
-        while (p.splits > 1 && nb::force_scratch_bytes(p, n_i) > room) {
-            // largest split count whose slots fit, then re-normalised
-            const size_t per_slot = nb::kSlotComp * sizeof(double) + sizeof(int32_t) +
-                                    nb::kSegCap * sizeof(int32_t);
-            const int64_t fit = (int64_t)(room / per_slot) / std::max<int32_t>(n_i, 1);
-            p.splits = (int)std::max<int64_t>(1, std::min<int64_t>(fit, p.splits - 1));
-            finish_plan(p, n, n_i, &split_len);
-        }
-        base = fixed;
-    }
-    fa.splits = p.splits;
-    fa.split_len = split_len;
-    const size_t slot_bytes = nb::force_scratch_bytes(p, n_i);
-    // under a scratch limit the refinement's chunk partials shrink as well
-    if (!fixed && ctx->scratch_limit) {
-        int32_t rows = rcap_limit > 0 ? std::min(rcap_limit, n_i) : n_i;
-        while (redo_bytes && redo_bytes + slot_bytes > ctx->scratch_limit && rows > 1) {
-            rows /= 2;
-            rcap_limit = rows;
-            redo_bytes = nb::redo_scratch_bytes(n_i, n, rcap_limit);
-        }
-    }
-    // the packed j-set, where it pays and its memory is there: a workspace or
-    // scratch limit that is too small for it runs the LDS kernels as before
-    size_t pack_bytes = pack_pays(p.mapping, p.rows_per_lane, n, n_i) ? nb::packed_bytes(n) : 0;
-    if (fixed && redo_bytes + slot_bytes + pack_bytes > fixed_bytes) pack_bytes = 0;
-    if (!fixed && redo_bytes + slot_bytes + pack_bytes > 0) {
-        int rc = ensure_scratch(ctx, redo_bytes + slot_bytes + pack_bytes);
-        if (rc == NB_ERR_OOM && pack_bytes) {
-            pack_bytes = 0;
-            rc = redo_bytes + slot_bytes > 0 ? ensure_scratch(ctx, redo_bytes + slot_bytes) : NB_OK;
+        if (f.total() > fixed_bytes) return NB_ERR_TOO_LARGE;
+    } else if (f.total() > 0) {
+        int rc = ensure_scratch(ctx, f.total());
+        // no room on the device (or none to be had during a capture): smaller
+        while (rc == NB_ERR_OOM && !f.least) {
+            f = fit_scratch(ctx, n, n_i, p, refine, least, f.total() / 2);
+            rc = f.total() > 0 ? ensure_scratch(ctx, f.total()) : NB_OK;
         }
         if (rc != NB_OK) return rc;
         base = ctx->scratch;
     }
+    p = f.p;
+    const size_t redo_bytes = f.redo, pack_bytes = f.pack;
+    const int32_t rcap_limit = f.rcap;
+    const int64_t split_len = f.split_len;
+    fa.splits = p.splits;
+    fa.split_len = split_len;
     if (pack_bytes) {
         fa.packed = (nb::JRec *)base;
         base = (char *)base + pack_bytes;

@@ -29,6 +29,16 @@ int main()
             int32_t words[64] = {};
             nb::bind_redo_scratch(a, nullptr, words, nb::redo_groups_for(ctx.cu_count), n);
             std::printf("%d %d\n", nb::redo_grid(a, (int)per), nb::redo_groups_for(ctx.cu_count));
+        } else if (!std::strcmp(what, "fit")) {   // n n_i mixed budget fixed
+            long long n, n_i, mixed, budget, fixed;
+            if (std::scanf("%lld %lld %lld %lld %lld", &n, &n_i, &mixed, &budget, &fixed) != 5)
+                return 1;
+            const nb::Plan p = nbrt::auto_plan(&ctx, n, (int32_t)n_i, mixed != 0);
+            const int least = fixed ? 1 : nbrt::least_splits(&ctx, n, (int32_t)n_i, p);
+            const nbrt::ForceScratch f = nbrt::fit_scratch(&ctx, n, (int32_t)n_i, p,
+                                                           mixed && !p.f64, least, (size_t)budget);
+            std::printf("%d %lld %lld %d %d\n", f.p.splits, (long long)f.split_len,
+                        (long long)f.total(), f.pack > 0, f.least);
         } else {
             return 1;
         }

@@ -67,3 +67,40 @@ def test_even_splits_of_packed_blocks(rules):
                                    (16384, 9000, 64, 256), (131072, 4099, 187, 704)):
         for mixed in (0, 1):
             assert rules(f"plan {n} {n_i} {mixed}")[0] == [1, 1, splits, length]
+
+
+def _up(a, b):
+    return -(-a // b)
+
+
+def _coarse_bytes(n, n_i, mixed):
+    """Scratch of splits of 512 bodies (128 in one-wave work-groups), at most 64
+    (16) work-groups per CU: what a call may always be given instead of its
+    plan's."""
+    if n_i <= 40:
+        return None
+    u1, u3 = _up(n_i, 256), _up(n_i, 64)
+    narrow = u1 * 256 * 5 > u3 * 64 * 6
+    unit = 64 if narrow else 256
+    s = min(_up(4096, u3), _up(n, 128)) if narrow else min(_up(16384, u1), _up(n, 512))
+    k = _up(n, _up(_up(n, unit), s) * unit)
+    slots = 0 if k == 1 else sum(_up(k * n_i * b, 256) * 256 for b in (64, 4, 384))
+    return slots + (3 * _up(4 * n_i, 256) * 256 if mixed else 0)
+
+
+def test_scratch_fits_a_small_budget(rules):
+    """Every block runs in the scratch of the coarse splits, with the most splits
+    that fit; with less than that it is refused."""
+    cases = [(n, n_i, mixed, _coarse_bytes(n, n_i, mixed))
+             for n in (300, 512, 1024, 3001, 8192, 16384, 65537, 131072, 200000, 1 << 20)
+             for n_i in (41, 64, 130, 300, 520, 777, 1024, 4099, 8192, n) if 40 < n_i <= n
+             for mixed in (0, 1)]
+    at = [rules(*[f"fit {n} {n_i} {m} {budget(room)} 0" for n, n_i, m, room in cases])
+          for budget in (lambda room: room, lambda room: 1 << 50, lambda room: 4096)]
+    for case, coarse, free, none in zip(cases, *at):
+        assert coarse[2] <= case[3] and coarse[0] <= free[0], case
+        if case[3] > 8 * 4096:
+            assert none[4] and none[2] > 4096, case
+    # most splits that fit: 8192 of 8192 in 64 MiB, 452 bytes a row and split
+    splits, _, total, _, _ = rules(f"fit 8192 8192 0 {64 << 20} 0")[0]
+    assert 16 <= splits <= 18 and total <= 64 << 20
