@@ -283,10 +283,12 @@ int least_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, const Plan &p)
 }
 
 // The plan and its scratch within 'budget' bytes: what does not fit shrinks the
-// refinement's chunk partials to half of the budget first (rows past them
-// are summed one work-group each, to the same bits), then the split count down
-// to 'least', then the partials further; the packed j-set takes what is left,
-// if that is enough.  total() > budget: not even the least fits.
+// refinement's chunk partials to an eighth of the budget first (rows past them
+// are summed one work-group each, to the same bits; with half of the budget for
+// them the splits of 1272 rows of 2^20 fell to 62 in the fixed workspace, 2665
+// us mixed against 1558 with 100), then the split count down to 'least', then
+// the partials further; the packed j-set takes what is left, if that is enough.
+// total() > budget: not even the least fits.
 ForceScratch fit_scratch(const nb_ctx *ctx, int64_t n, int32_t n_i, const Plan &wanted,
                          bool refine, int least, size_t budget)
 {
@@ -310,19 +312,35 @@ ForceScratch fit_scratch(const nb_ctx *ctx, int64_t n, int32_t n_i, const Plan &
             f.redo = nb::redo_scratch_bytes(n_i, n, f.rcap);
         }
     };
-    shrink_redo(budget / 2);
+    shrink_redo(budget / 8);
     const size_t room = budget > f.redo ? budget - f.redo : 0;
     const size_t per_split = (nb::kSlotComp * sizeof(double) + sizeof(int32_t) +
                               nb::kSegCap * sizeof(int32_t)) * (size_t)std::max(n_i, 1);
     while (f.p.splits > least && f.slots > room) {
-        const int64_t s = std::max<int64_t>(
+        int64_t s = std::max<int64_t>(
             least, std::min<int64_t>((int64_t)(room / per_split), f.p.splits - 1));
+        // few waves per SIMD: no more splits than fill the SIMDs evenly.  In the 64
+        // MiB of the fixed workspace, FP64, as many as fit / this rule: 1024 rows of
+        // 131072 244 us (548 work-groups) / 192 (512, two per CU), 2048 of 65536 251
+        // / 200, 4099 of 131072 881 / 775, 16384 of 131072 3647 / 2900, 1272 of 2^20
+        // 2217 / 1812; the one loss seen: 10000 of 30000 mixed 395 / 424.
+        const int64_t u = row_groups(n_i, f.p.mapping, f.p.rows_per_lane);
+        const int64_t at_once = (f.p.mapping == 1 ? 1 : 4) *
+                                (int64_t)(ctx->cu_count > 0 ? ctx->cu_count : 256);
+        const int64_t k = (u * s + at_once - 1) / at_once, even = (k - 1) * at_once / u;
+        if (even >= std::max(1, least) && (k - 1) * ((n + even - 1) / even) < k * ((n + s - 1) / s))
+            s = even;
         f.p.splits = (int)std::max<int64_t>(1, s);
         finish_plan(f.p, n, n_i, &f.split_len);
         f.slots = nb::force_scratch_bytes(f.p, n_i);
     }
     if (f.slots + f.redo > budget) shrink_redo(budget > f.slots ? budget - f.slots : 0);
-    if (f.total() + pack <= budget) f.pack = pack;
+    // few waves per SIMD wait for scalar loads; blocks of many row tiles gain all the
+    // same (in the fixed workspace, mixed, LDS / packed: 1500 rows of 100003 205 /
+    // 229 us, 2048 of 65536 177 / 191, 10000 of 30000 424 both, 50000 of 50000 3785
+    // / 3582; 16384 of 16384 FP64 429 / 416)
+    const bool lowered = f.p.splits < wanted.splits;
+    if (f.total() + pack <= budget && !(lowered && n_i < 4096)) f.pack = pack;
     f.least = f.p.splits <= least && f.pack == 0 && (f.redo == 0 || f.rcap < 0);
     return f;
 }

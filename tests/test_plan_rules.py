@@ -104,3 +104,17 @@ def test_scratch_fits_a_small_budget(rules):
     # most splits that fit: 8192 of 8192 in 64 MiB, 452 bytes a row and split
     splits, _, total, _, _ = rules(f"fit 8192 8192 0 {64 << 20} 0")[0]
     assert 16 <= splits <= 18 and total <= 64 << 20
+
+
+def test_fixed_workspace_plans(rules):
+    """In the 64 MiB of the allocation-free call the splits fill the CUs evenly, and
+    the refinement leaves them most of the room."""
+    ws = nb.fixed_workspace_bytes()
+    for n, n_i in ((131072, 1024), (65536, 2048), (262144, 1024), (16384, 16384),
+                   (1 << 20, 1272), (100003, 1500), (131072, 4099)):
+        for mixed in (0, 1):
+            splits, length, total, packed, _ = rules(f"fit {n} {n_i} {mixed} {ws} 1")[0]
+            most = ws // (452 * n_i)
+            assert total <= ws and splits >= 0.8 * most
+            groups = _up(n_i, 256) * splits
+            assert groups / 256 > 0.85 * _up(groups, 256), (n, n_i, splits)
