@@ -571,8 +571,8 @@ int nb_potential(nb_ctx *ctx, int64_t n, const double *x, const double *m, doubl
     hipEvent_t ev[2];
     hipError_t e;
     // one evaluation per pair of bodies, in panels of blocks whose entries take
-    // at most kPotBytes (one panel up to about 370000 bodies); under a scratch
-    // limit smaller panels, or, without room for one block, the plain kernel
+    // at most kPotBytes (one panel up to about 370000 bodies); without room for
+    // them smaller panels, or, not even for one block, the plain kernel
     const PotShape sh = pot_shape(n);
     const int64_t blocks = (n + sh.block - 1) / sh.block;
     const int64_t sum_wgs = (n + nb::kWave - 1) / nb::kWave;
@@ -581,11 +581,16 @@ int nb_potential(nb_ctx *ctx, int64_t n, const double *x, const double *m, doubl
         const int64_t cells = pb == blocks ? blocks * n : pb * n + blocks * pb * sh.block;
         return (size_t)(cells + sum_wgs + 1) * sizeof(double);
     };
-    const size_t most = ctx->scratch_limit ? std::min(ctx->scratch_limit, kPotBytes) : kPotBytes;
-    while (panel > 1 && pot_bytes(panel) > most) panel = (panel + 1) / 2;
-    if (!ctx->scratch_limit || pot_bytes(panel) <= ctx->scratch_limit) {
-        int rc = ensure_scratch(ctx, pot_bytes(panel));
-        if (rc != NB_OK) return rc;
+    size_t most = ctx->scratch_limit ? std::min(ctx->scratch_limit, kPotBytes) : kPotBytes;
+    int rc = NB_ERR_OOM;
+    while (rc == NB_ERR_OOM && panel > 0) {
+        while (panel > 1 && pot_bytes(panel) > most) panel = (panel + 1) / 2;
+        rc = ensure_scratch(ctx, pot_bytes(panel));
+        most = pot_bytes(panel) / 2;   // no room on the device: smaller panels
+        if (rc == NB_ERR_OOM && panel == 1) panel = 0;
+    }
+    if (rc != NB_OK && rc != NB_ERR_OOM) return rc;
+    if (panel > 0) {
         double *wg = (double *)ctx->scratch;
         double *cells = wg + sum_wgs + 1;
         e = timed_begin(ctx, NB_CLASS_STEP, ev);
@@ -628,7 +633,7 @@ int nb_potential(nb_ctx *ctx, int64_t n, const double *x, const double *m, doubl
     const int64_t split_len = (tiles + splits - 1) / splits * nb::kTile;
     splits = (n + split_len - 1) / split_len;
     const size_t bytes = (size_t)(splits * n + red_wgs + 1) * sizeof(double) + 512;
-    int rc = ensure_scratch(ctx, bytes);
+    rc = ensure_scratch(ctx, bytes);
     if (rc != NB_OK) return rc;
     double *part = (double *)ctx->scratch;
     double *wg = part + splits * n;
