@@ -16,8 +16,8 @@
 // values.  Every pair is evaluated once for its row and its body (a row pass
 // and a body pass used to recompute the same geometry, about half of the 111
 // FP64 instructions that the two spent on a pair): each lane holds R rows in
-// registers, bodies pass through LDS in tiles of 64, and at step s lane l
-// meets body l ^ s, so the lanes of a wave work on 64 different bodies.  The
+// registers, bodies pass through LDS in tiles of 64 or 128, and at step s lane l
+// meets body l ^ s of a run of 64, so the lanes of a wave work on 64 different bodies.  The
 // row's sums stay in registers; the body's seven shares of the lane's R rows
 // are added in registers and then to the wave's own LDS sums, without conflict
 // and in a fixed order.  Row sums per block of bodies and body sums per block
@@ -352,7 +352,7 @@ void launch_pairs(const AdjointArgs &a, const AdjPlan &p, int64_t items, hipStre
 
 }  // namespace
 
-// Rows per block, LDS tile, bodies per block and row blocks per panel.  Two
+// Rows per block, tile, bodies per block and row blocks per panel.  Two
 // rows per lane (512 a block) where there are enough rows for it, one (256)
 // else: 4096 of 16384 234 us with two, 252 with one.  Tiles of 64 bodies where
 // there are few bodies, or fewer than two work-groups per CU with tiles of
@@ -360,6 +360,11 @@ void launch_pairs(const AdjointArgs &a, const AdjPlan &p, int64_t items, hipStre
 // 35 us with 64, 57 with 128; 256 of 16384 33 and 49; 1024 of 12000 (376
 // work-groups) 61 and 72; 1024 of 16384 (512) 75.5 both; 4096 of 16384 222 and
 // 217; 2500 of 65536 517 and 497.
+// Body blocks are multiples of the tile.  512-row blocks stage tiles of 128 in
+// either case: a kernel with tiles of 64 for their body blocks of 64 takes as
+// long (2048 of 9000 92.6 us against 93.2, 2049 of 12000 112.7 and 112.8, 2500 of
+// 12000 118.6 and 118.7), and blocks of 128 bodies or 256 rows there take longer
+// on few work-groups (2048 of 9000 111 and 97 us, 2500 of 9000 113 and 101).
 // Body blocks for about 24 items per CU (48 give the same time and twice the
 // row partials), entries of at most kAdjointBytes by smaller panels, then by
 // longer body blocks; a call under a scratch limit needs no more than

@@ -159,7 +159,7 @@ struct AdjointArgs {
 };
 struct AdjointShape {
     int32_t row_block;       // rows per row block: 256 or 512
-    int32_t tile;            // bodies per LDS tile: 64 or 128
+    int32_t tile;            // 64 or 128: bodies per LDS tile of 256-row blocks (512: 128)
     int64_t body_len;        // bodies per body block
     int64_t panel_blocks;    // row blocks per launch (their body sums are kept apart)
     bool index_in_gm;        // the bodies' row index lives in the gm output
