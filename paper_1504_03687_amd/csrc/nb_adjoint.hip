@@ -365,25 +365,31 @@ void launch_pairs(const AdjointArgs &a, const AdjPlan &p, int64_t items, hipStre
 // long (2048 of 9000 92.6 us against 93.2, 2049 of 12000 112.7 and 112.8, 2500 of
 // 12000 118.6 and 118.7), and blocks of 128 bodies or 256 rows there take longer
 // on few work-groups (2048 of 9000 111 and 97 us, 2500 of 9000 113 and 101).
-// Body blocks for about 24 items per CU (48 give the same time and twice the
-// row partials), entries of at most kAdjointBytes by smaller panels, then by
-// longer body blocks; a call under a scratch limit needs no more than
-// 7 n + 12 n_i values at the least.
-AdjointShape adjoint_shape(int64_t n, int32_t n_i, int cus, size_t limit)
+// Body blocks for about 24 items per CU in a launch (48 give the same time and
+// twice the row partials).  Entries of at most kAdjointBytes by smaller panels,
+// whose launches then take more body blocks (with those of the whole call they
+// had 768, 192 and 48 work-groups at 2^18, 2^19 and 2^20 bodies and rows: 195 and
+// 1199 ms at the first two, 187 and 749 so, and 3014 at 2^20), then by longer
+// body blocks; a call without room for more needs 7 n + 12 n_i values.
+AdjointShape adjoint_shape(int64_t n, int32_t n_i, int cus, size_t budget)
 {
     AdjointShape sh{};
     sh.row_block = n_i >= 2048 && n > 8192 ? 512 : 256;
     const int64_t blocks = std::max<int64_t>(1, ((int64_t)n_i + sh.row_block - 1) / sh.row_block);
     sh.tile = n > 8192 && blocks * ((n + 127) / 128) >= 2 * (int64_t)cus ? 128 : 64;
-    const int64_t want = ((int64_t)cus * 24 + blocks - 1) / blocks;
     const int64_t tiles = (n + sh.tile - 1) / sh.tile;
-    sh.body_len = (tiles + want - 1) / want * sh.tile;
-    sh.panel_blocks = blocks;
-    const size_t most = limit ? std::min(limit, kAdjointBytes) : kAdjointBytes;
+    // the row sums are the call's own size and no reason for smaller panels
+    const size_t most = std::min(budget, kAdjointBytes + 6 * (size_t)n_i * sizeof(double));
+    auto take_panel = [&](int64_t panel_blocks) {
+        const int64_t want = ((int64_t)cus * 24 + panel_blocks - 1) / panel_blocks;
+        sh.panel_blocks = panel_blocks;
+        sh.body_len = (tiles + want - 1) / want * sh.tile;
+    };
+    take_panel(std::min(blocks, kAdjointPanelRows / sh.row_block));
     while (sh.panel_blocks > 1 && adjoint_scratch_bytes(n, n_i, sh) > most)
-        sh.panel_blocks = (sh.panel_blocks + 1) / 2;
+        take_panel((sh.panel_blocks + 1) / 2);
     while (sh.body_len < n && adjoint_scratch_bytes(n, n_i, sh) > most) sh.body_len *= 2;
-    sh.index_in_gm = limit && adjoint_scratch_bytes(n, n_i, sh) > limit;
+    sh.index_in_gm = adjoint_scratch_bytes(n, n_i, sh) > budget;
     return sh;
 }
 

@@ -164,9 +164,12 @@ struct AdjointShape {
     int64_t panel_blocks;    // row blocks per launch (their body sums are kept apart)
     bool index_in_gm;        // the bodies' row index lives in the gm output
 };
-// Most scratch an adjoint call asks for by itself.
+// Most scratch an adjoint call asks for by itself (next to the 6 n_i row sums),
+// and most rows of a panel (the threads of its row reduction fit 32 bits).
 constexpr size_t kAdjointBytes = size_t(1) << 30;
-AdjointShape adjoint_shape(int64_t n, int32_t n_i, int cus, size_t limit);
+constexpr int64_t kAdjointPanelRows = int64_t(1) << 25;
+// budget: bytes of scratch there may be (SIZE_MAX: any)
+AdjointShape adjoint_shape(int64_t n, int32_t n_i, int cus, size_t budget);
 size_t adjoint_scratch_bytes(int64_t n, int32_t n_i, const AdjointShape &sh);
 hipError_t launch_adjoint(const AdjointArgs &a, const AdjointShape &sh, void *scratch,
                           hipStream_t s);

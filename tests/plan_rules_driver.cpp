@@ -1,5 +1,6 @@
 // Prints what the library's host-side plan rules decide, for queries read from
 // stdin, one line each: a context of 256 CUs that launches nothing.
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 
@@ -39,6 +40,14 @@ int main()
                                                            mixed && !p.f64, least, (size_t)budget);
             std::printf("%d %lld %lld %d %d\n", f.p.splits, (long long)f.split_len,
                         (long long)f.total(), f.pack > 0, f.least);
+        } else if (!std::strcmp(what, "adjoint")) {   // n n_i budget (0: any)
+            long long n, n_i, budget;
+            if (std::scanf("%lld %lld %lld", &n, &n_i, &budget) != 3) return 1;
+            const nb::AdjointShape sh = nb::adjoint_shape(n, (int32_t)n_i, ctx.cu_count,
+                                                          budget ? (size_t)budget : SIZE_MAX);
+            std::printf("%d %d %lld %lld %d %lld\n", sh.row_block, sh.tile, (long long)sh.body_len,
+                        (long long)sh.panel_blocks, sh.index_in_gm,
+                        (long long)nb::adjoint_scratch_bytes(n, (int32_t)n_i, sh));
         } else {
             return 1;
         }

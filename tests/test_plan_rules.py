@@ -118,3 +118,23 @@ def test_fixed_workspace_plans(rules):
             assert total <= ws and splits >= 0.8 * most
             groups = _up(n_i, 256) * splits
             assert groups / 256 > 0.85 * _up(groups, 256), (n, n_i, splits)
+
+
+def test_adjoint_panels_fill_the_chip(rules):
+    """Gradients in several panels keep the launches of one: about 24 work-groups
+    per CU; the entries stay within 1 GiB next to the row sums."""
+    for n, n_i in ((65536, 65536), (1 << 18, 1 << 18), (1 << 19, 1 << 19), (1 << 20, 1 << 20),
+                   (1 << 21, 1 << 21), (1 << 20, 5000), (1 << 22, 1 << 16), (64, 1 << 25),
+                   (1000, 1 << 24)):
+        block, tile, length, panel, in_gm, total = rules(f"adjoint {n} {n_i} 0")[0]
+        assert total <= (1 << 30) + 2 * (48 * n_i + 256) and not in_gm
+        items = min(panel, _up(n_i, block)) * _up(n, length)
+        assert items >= 20 * 256 or length == tile, (n, n_i)
+        assert items * 256 < 1 << 32 and panel * block <= 1 << 25
+    # a million rows of few bodies are one panel
+    assert rules(f"adjoint 64 {1 << 20} 0")[0][3] == (1 << 20) // 256
+    # the least: 7 n + 12 n_i values
+    for n, n_i in ((3000, 2000), (9000, 5000), (1 << 18, 1 << 18)):
+        room = 8 * (7 * n + 12 * n_i) + 768
+        _, _, _, panel, _, total = rules(f"adjoint {n} {n_i} {room}")[0]
+        assert panel == 1 and total <= room
