@@ -542,9 +542,17 @@ int nb_regular_force_adjoint(nb_ctx *ctx, int64_t n, const double *xp, const dou
     if (n_i > 0 && (!i_block || !rs2 || !w_a || !w_j)) return NB_ERR_INVALID_ARG;
     if (!ctx->usable) return NB_ERR_UNSUPPORTED;
     const int cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
-    const nb::AdjointShape sh =
-        nb::adjoint_shape(n, n_i, cus, ctx->scratch_limit ? ctx->scratch_limit : SIZE_MAX);
-    int rc = n_i > 0 ? ensure_scratch(ctx, nb::adjoint_scratch_bytes(n, n_i, sh)) : NB_OK;
+    size_t budget = ctx->scratch_limit ? ctx->scratch_limit : SIZE_MAX;
+    nb::AdjointShape sh = nb::adjoint_shape(n, n_i, cus, budget);
+    size_t bytes = nb::adjoint_scratch_bytes(n, n_i, sh);
+    int rc = n_i > 0 ? ensure_scratch(ctx, bytes) : NB_OK;
+    // no room on the device: smaller panels and longer body blocks, to the least
+    while (rc == NB_ERR_OOM && !(sh.panel_blocks == 1 && sh.body_len >= n && sh.index_in_gm)) {
+        budget = bytes / 2;
+        sh = nb::adjoint_shape(n, n_i, cus, budget);
+        bytes = nb::adjoint_scratch_bytes(n, n_i, sh);
+        rc = ensure_scratch(ctx, bytes);
+    }
     if (rc != NB_OK) return rc;
     nb::AdjointArgs aa{};
     aa.n = n;
