@@ -249,6 +249,7 @@ struct BatchedCache {
     nb::BatchArgs args{};
     bool packed = false;
     bool coarse = false;      // splits of kSplitLen only (the finer ones found no memory)
+    bool lean = false;        // no chunk partials of the refinement (nor did those)
     int grid = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -424,13 +425,13 @@ static int build_cache(nb_ctx *ctx, BatchedCache *c, const nb::ForceArgs &f, boo
     int64_t max_len = 1;
     for (int32_t k = 0; k < C; ++k) max_len = std::max<int64_t>(max_len, c->j_off[k + 1] - c->j_off[k]);
     const size_t b_other = b_queue + b_cl + 2 * b_mr + b_it + b_slots + (c->packed ? b_rec : 0);
-    // under a scratch limit the refinement buffers fewer rows
-    int32_t rcap_limit = 0;
-    size_t b_redo = c->redo_k > 0.0 ? nb::redo_scratch_bytes(f.n_i, max_len) : 0;
-    for (int32_t rows = f.n_i; ctx->scratch_limit && b_redo && b_other + b_redo > ctx->scratch_limit &&
-                               rows > 1;) {
+    // under a scratch limit the refinement buffers fewer rows, or none
+    int32_t rcap_limit = c->lean ? -1 : 0;
+    size_t b_redo = c->redo_k > 0.0 ? nb::redo_scratch_bytes(f.n_i, max_len, rcap_limit) : 0;
+    for (int32_t rows = f.n_i; ctx->scratch_limit && b_redo && rcap_limit >= 0 &&
+                               b_other + b_redo > ctx->scratch_limit;) {
         rows /= 2;
-        rcap_limit = rows;
+        rcap_limit = rows > 0 ? rows : -1;
         b_redo = nb::redo_scratch_bytes(f.n_i, max_len, rcap_limit);
     }
     const size_t total = b_other + b_redo;
@@ -671,6 +672,10 @@ extern "C" int nb_regular_force_batched(nb_ctx *ctx, int32_t n_clusters, const i
         }
         if (rc == NB_ERR_OOM && c->packed) {   // no room for the packed bodies
             c->packed = false;
+            rc = build_cache(ctx, c, f, mixed);
+        }
+        if (rc == NB_ERR_OOM && rk > 0.0) {   // no room for the refinement's partials
+            c->lean = true;
             rc = build_cache(ctx, c, f, mixed);
         }
         if (rc != NB_OK) {
