@@ -25,8 +25,7 @@
 // deterministic; the "-" terms reach a body in row order.
 #include <algorithm>
 
-#include "nb_internal.h"
-#include "nb_pair.h"
+#include "nb_rows.h"
 
 namespace nb {
 namespace {
@@ -40,7 +39,7 @@ struct AdjPlan {
     int32_t add;             // body sums of an earlier panel are added to
     double *row_partial;     // [body_blocks][6][panel_rows]
     double *body_partial;    // [row blocks of a panel][7][n]
-    int2 *index;             // per body: its first row (n_i: none), its number of rows
+    int2 *index;             // per body: its first row (n_i: none), 1 if it has others
 };
 
 // Exclusion (self pair or neighbour) by the canonical test, run only for
@@ -234,6 +233,18 @@ __global__ __launch_bounds__(kWave * W) __attribute__((amdgpu_waves_per_eu(R == 
 // component, 8 so).
 constexpr int kReduceWaves = 16;
 
+// Enters a row in its body's index.  A row behind one that is there already only
+// sets the flag, if it is not set: where one body has many rows, their atomics and
+// stores would queue on one address.
+__device__ __forceinline__ void enter_row(int2 *t, int32_t row, int32_t none)
+{
+    const uint64_t seen = __hip_atomic_load((const uint64_t *)t, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+    if ((int32_t)seen > row && atomicMin(&t->x, row) == none) return;   // the first to come
+    if (seen >> 32 == 0)
+        __hip_atomic_store(&t->y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __global__ __launch_bounds__(kWave * kReduceWaves) void adj_rows_reduce(AdjointArgs a, AdjPlan p)
 {
     __shared__ double part[kReduceWaves][kWave];
@@ -260,60 +271,141 @@ __global__ __launch_bounds__(kWave * kReduceWaves) void adj_rows_reduce(AdjointA
         if (comp == 0) {
             const int64_t i = a.i_block[row];
             bad = i < 0 || i >= a.n;
-            if (!bad) {
-                atomicMin(&p.index[i].x, (int32_t)row);
-                atomicAdd(&p.index[i].y, 1);
-            }
+            if (!bad) enter_row(p.index + i, (int32_t)row, a.n_i);
         }
     }
     const uint64_t bb = __ballot(bad);
     if ((threadIdx.x & (kWave - 1)) == 0 && bb && a.status) atomicOr(a.status, kStBadIndex);
 }
 
-// A body's gradient: its partials over the row blocks (fixed order) times its
-// mass, less the row sums of the rows whose body it is, in row order.  A body
-// of one row finds it in the index; for the others (duplicate rows) the wave
-// looks through the block's rows from the first one on.
-__global__ __launch_bounds__(256) void adj_bodies_reduce(AdjointArgs a, AdjPlan p,
-                                                         int32_t row_blocks)
+// Row sums of rows [b0, b1) added to the bodies [j0, j0 + 64) that they belong to
+// (lane l: body j0 + l), in a fixed order, by one wave: per run of 64 rows each
+// body finds its rows as a mask (a ballot per bit of the body's place) and takes
+// their sums from the lanes that hold them, all bodies at once; a body with many
+// of the run's rows gets the wave's sum.
+__device__ __forceinline__ void add_rows(const AdjointArgs &a, int64_t j0, int64_t b0, int64_t b1,
+                                         double (&D)[6])
 {
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const bool live = j < a.n;
+    constexpr int kAhead = 4;   // runs whose loads go out together
     const int lane = threadIdx.x & (kWave - 1);
-    double v[7] = {0, 0, 0, 0, 0, 0, 0}, D[6] = {0, 0, 0, 0, 0, 0};
-    int32_t first = 0, count = 0;
-    if (live) {
-        for (int32_t q = 0; q < row_blocks; ++q) {
+    for (; b0 < b1; b0 += kAhead * kWave) {
+        int32_t rel[kAhead];
+        double v[kAhead][6];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t b = b0 + u * kWave + lane;
+            const int64_t d = b < b1 ? a.i_block[b] - j0 : -1;
+            rel[u] = d >= 0 && d < kWave && j0 + d < a.n ? (int32_t)d : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+                v[u][k] = rel[u] >= 0
+                              ? a.row_part[(int64_t)k * a.n_i + b0 + u * kWave + lane] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            uint64_t mine = __ballot(rel[u] >= 0);   // the rows of body j0 + lane
+            if (mine == 0) continue;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                const uint64_t bit = __ballot((rel[u] >> k) & 1);
+                mine &= (lane >> k) & 1 ? bit : ~bit;
+            }
+            uint64_t heavy = __ballot(__popcll(mine) >= 16);
+            while (heavy) {   // a body with many of them: the wave's sum
+                const int l = __builtin_ctzll(heavy);
+                heavy &= heavy - 1;
+                double x[6];
+#pragma unroll
+                for (int k = 0; k < 6; ++k) x[k] = rel[u] == l ? v[u][k] : 0.0;
+                group_sums<kWave, 6>(x);
+                if (lane == l) {
+                    mine = 0;
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) D[k] += x[k];
+                }
+            }
+            while (__ballot(mine != 0) != 0) {   // a turn per row of the body with most
+                const int src = mine ? __builtin_ctzll(mine) : lane;
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    const double x = __shfl(v[u][k], src, kWave);
+                    D[k] += mine ? x : 0.0;
+                }
+                mine &= mine - 1;
+            }
+        }
+    }
+}
+
+// A body's gradient: its partials over the row blocks (fixed order) times its
+// mass, less the row sums of the rows whose body it is.  W waves take 64 bodies
+// and share the row blocks (W = 1: four waves of a work-group, each on its own).
+// A body of one row finds it in the index; where one of the 64 has several
+// (duplicate rows), the waves share the call's rows, and their sums are added in
+// wave order.  Gradient calls, one wave looking through the rows for one body
+// after another / so: 65536 rows of 1024 bodies 12.9 ms / 0.35, 65536 of one body
+// 25.3 / 11.8, 20011 rows, a third of them of one body, 2.85 / 1.23, every body of
+// 20011 twice 2.75 / 1.16; with the pass over all pairs for the bodies' sums that
+// found a body's rows on its way 0.47, 16.0, 1.79 and 1.77.
+template <int W>
+__global__ __launch_bounds__(W == 1 ? 256 : kWave * W) void adj_bodies_reduce(AdjointArgs a,
+                                                                              AdjPlan p,
+                                                                              int32_t row_blocks,
+                                                                              int64_t first)
+{
+    __shared__ double part[W][7][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int w = W == 1 ? 0 : wave;
+    const int64_t j0 = first + (W == 1 ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.x) * kWave;
+    const int64_t j = j0 + lane;
+    const bool live = j < a.n;
+    double v[7] = {0, 0, 0, 0, 0, 0, 0};
+    const int32_t share = (row_blocks + W - 1) / W;
+    const int32_t q1 = row_blocks < (w + 1) * share ? row_blocks : (w + 1) * share;
+    if (live)
+#pragma unroll 4
+        for (int32_t q = w * share; q < q1; ++q) {
             const double *src = p.body_partial + (int64_t)q * 7 * a.n + j;
 #pragma unroll
             for (int k = 0; k < 7; ++k) v[k] += src[(int64_t)k * a.n];
         }
-        const int2 t = p.index[j];
-        first = t.x;
-        count = t.y;
-        if (count == 1)
+    const int2 t = live ? p.index[j] : make_int2(a.n_i, 0);
+    if constexpr (W > 1) {
 #pragma unroll
-            for (int k = 0; k < 6; ++k) D[k] = a.row_part[(int64_t)k * a.n_i + first];
+        for (int k = 0; k < 7; ++k) part[w][k][lane] = v[k];
     }
-    uint64_t dup = __ballot(count > 1);
-    while (dup) {   // uniform over the wave
-        const int l = __builtin_ctzll(dup);
-        dup &= dup - 1;
-        const int32_t body = __shfl((int32_t)j, l, kWave);
-        int32_t left = __shfl(count, l, kWave);
-        for (int64_t b0 = __shfl(first, l, kWave); b0 < a.n_i && left > 0; b0 += kWave) {
-            const int64_t b = b0 + lane;
-            uint64_t hit = __ballot(b < a.n_i && a.i_block[b < a.n_i ? b : 0] == body);
-            left -= __popcll(hit);
-            while (hit) {
-                const int64_t row = b0 + __builtin_ctzll(hit);
-                hit &= hit - 1;
-                if (lane == l)
+    const bool several = W > 1 ? __syncthreads_or(t.y) != 0 : __ballot(t.y != 0) != 0;
+    if (W > 1 && w == 0)
 #pragma unroll
-                    for (int k = 0; k < 6; ++k) D[k] += a.row_part[(int64_t)k * a.n_i + row];
-            }
+        for (int k = 0; k < 7; ++k) {
+            v[k] = 0.0;
+#pragma unroll
+            for (int u = 0; u < W; ++u) v[k] += part[u][k][lane];
         }
+    double D[6] = {0, 0, 0, 0, 0, 0};
+    if (several) {   // uniform over the work-group
+        const int64_t rows = ((a.n_i + kWave - 1) / kWave + W - 1) / W * kWave;
+        const int64_t b1 = a.n_i < (w + 1) * rows ? a.n_i : (w + 1) * rows;
+        add_rows(a, j0, w * rows, b1, D);
+        if constexpr (W > 1) {
+            __syncthreads();   // the body sums are read
+#pragma unroll
+            for (int k = 0; k < 6; ++k) part[w][k][lane] = D[k];
+            __syncthreads();
+            if (w == 0)
+#pragma unroll
+                for (int k = 0; k < 6; ++k)
+#pragma unroll
+                    for (int u = 1; u < W; ++u) D[k] += part[u][k][lane];
+        }
+    } else if (w == 0 && t.x < a.n_i) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) D[k] = a.row_part[(int64_t)k * a.n_i + t.x];
     }
+    if (w > 0) return;
     bool nonfin = false;
     if (live) {
         const double m = a.m[j];
@@ -448,8 +540,21 @@ hipError_t launch_adjoint(const AdjointArgs &a0, const AdjointShape &sh, void *s
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(adj_bodies_reduce, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a,
-                       p, used);
+    // waves per 64 bodies of the body sums: few where few rows leave nothing to
+    // share (one row of 2^20 bodies, 16 waves against one 555 and 413 us, 2048 rows
+    // 6162 and 5790), many where the rows are looked through
+    // slices of bodies whose threads fit 32 bits
+    constexpr int64_t kSlice = int64_t(1) << 27;
+    for (int64_t first = 0; first < a.n; first += kSlice) {
+        const int64_t groups = (std::min(kSlice, a.n - first) + kWave - 1) / kWave;
+        const dim3 wgs((unsigned)groups), wgs4((unsigned)((groups + 3) / 4));
+        if (a.n_i <= 1024)
+            hipLaunchKernelGGL(adj_bodies_reduce<1>, wgs4, dim3(256), 0, s, a, p, used, first);
+        else if (a.n_i <= 8192)
+            hipLaunchKernelGGL(adj_bodies_reduce<4>, wgs, dim3(kWave * 4), 0, s, a, p, used, first);
+        else
+            hipLaunchKernelGGL(adj_bodies_reduce<16>, wgs, dim3(kWave * 16), 0, s, a, p, used, first);
+    }
     return hipGetLastError();
 }
 
