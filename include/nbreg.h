@@ -283,10 +283,11 @@ int nb_autotune_batched(nb_ctx *ctx, int32_t n_clusters, const int64_t *j_off_ho
                         int32_t *nb_count, int32_t *nb_list, int32_t *overflow,
                         uint32_t *status, const char *cache_path, int flags);
 
-/* Autotuner: times the candidate plans (rows per lane, splits, mapping) on
- * synthetic Plummer-like data for a ladder of block sizes at the given n,
- * for both precisions (for NB_MIXED blocks of up to 256 rows, also the FP64
- * kernels), and stores the fastest per (precision, n bucket, n_i bucket).
+/* Autotuner: times the automatic plan and candidates (rows per lane, splits,
+ * mapping) on synthetic Plummer-like data for a ladder of block sizes at the
+ * given n, for both precisions (for NB_MIXED blocks of up to 256 rows, also the
+ * FP64 kernels), and stores the fastest per (precision, n bucket, n_i bucket);
+ * a candidate has to beat the automatic plan by 2%.
  * If cache_path names a readable file written by an earlier run (text, first
  * line "nbreg-tune 2"), the table is loaded from it instead (flags & 1
  * forces re-tuning); after tuning the table is written there.  Synchronises

@@ -8,11 +8,14 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <iterator>
 #include <numeric>
 #include <vector>
 
 #include "nbreg.h"
 #include "nb_runtime.h"
+
+using nb::Plan;
 
 namespace nbrt {
 namespace {
@@ -57,6 +60,49 @@ void synth(int64_t n, std::vector<double> &x, std::vector<double> &v, std::vecto
 }
 
 }  // namespace
+
+// Plans that the tuner times for a block of ni rows: the automatic one (mapping
+// 0), then the automatic split count of every mapping, halved and doubled.  The
+// automatic plan is one of its own because the others do not hold it: its split
+// length may be evened for the block (187 splits of 704 bodies for 4099 rows of
+// 131072, against 64, 128 and 256 here).
+std::vector<Plan> tune_candidates(const nb_ctx *ctx, int64_t n, int32_t ni, bool mixed)
+{
+    std::vector<Plan> cands;
+    for (int mapping = 1; mapping <= 3; ++mapping) {
+        if (mapping == 1 && ni < 64) continue;
+        if (mapping == 3 && (ni < 16 || ni > 1024)) continue;
+        for (int rows : {1, 2, 4}) {
+            if (mapping == 1 && rows == 4) continue;
+            if (mapping == 2 && rows > ni) continue;
+            if (mapping == 3 && rows != 1) continue;
+            const int64_t base = default_splits(ctx, n, ni, mapping, rows);
+            for (int64_t sc : {base / 2, base, base * 2}) {
+                const int64_t maxs = max_splits(ctx, n, ni, mapping, rows);
+                const int s = (int)std::max<int64_t>(1, std::min<int64_t>(sc, maxs));
+                const Plan p{mapping, rows, s, 0, split_step(mapping, s, n)};
+                bool dup = false;
+                for (auto &q : cands)
+                    dup |= q.mapping == p.mapping && q.rows_per_lane == p.rows_per_lane &&
+                           q.splits == p.splits;
+                if (!dup) cands.push_back(p);
+            }
+        }
+    }
+    // a mixed request on a small block may be served faster by the FP64 kernels
+    // (latency-bound, and no refinement)
+    if (mixed && ni <= 256) {
+        const size_t k = cands.size();
+        for (size_t q = 0; q < k; ++q) {
+            Plan p = cands[q];
+            p.f64 = 1;
+            cands.push_back(p);
+        }
+    }
+    cands.insert(cands.begin(), Plan{});
+    return cands;
+}
+
 }  // namespace nbrt
 
 using namespace nbrt;
@@ -75,8 +121,10 @@ static int load_table(nb_ctx *ctx, const char *path, int64_t n_bucket, bool *fou
     long long nb, nib;
     while (std::fscanf(f, "%d %lld %lld %d %d %d %d", &prec, &nb, &nib, &mapping, &rows, &splits,
                        &f64) == 7) {
-        if (mapping < 1 || mapping > 3 || splits < 1 ||
-            !(rows == 1 || rows == 2 || rows == 4) || f64 < 0 || f64 > 1)
+        // all zero: the automatic plan was the fastest
+        const bool automatic = mapping == 0 && rows == 0 && splits == 0 && f64 == 0;
+        if (!automatic && (mapping < 1 || mapping > 3 || splits < 1 ||
+                           !(rows == 1 || rows == 2 || rows == 4) || f64 < 0 || f64 > 1))
             continue;
         ctx->tuned[std::make_tuple(prec, (int64_t)nb, (int64_t)nib)] =
             nb::Plan{mapping, rows, splits, prec == 1 ? f64 : 0, 0};
@@ -146,49 +194,21 @@ extern "C" int nb_autotune(nb_ctx *ctx, int64_t n, const char *cache_path, int f
     for (int32_t ni = 1; ni <= max_ni; ni *= 4) ladder.push_back(ni);
     if (ladder.back() != max_ni) ladder.push_back(max_ni);
 
+    // the automatic plan is timed without what an earlier tuning put in its place
+    const auto tuned_before = ctx->tuned;
+    for (auto it = ctx->tuned.begin(); it != ctx->tuned.end();)
+        it = std::get<1>(it->first) == nbk ? ctx->tuned.erase(it) : std::next(it);
+
     for (int prec = 0; prec < 2 && rc == NB_OK; ++prec) {
         std::vector<std::pair<int64_t, nb::Plan>> best_at;
         for (int32_t ni : ladder) {
-            // candidates around the automatic plan of each mapping
             ctx->has_forced = false;
-            std::vector<nb::Plan> cands;
-            for (int mapping = 1; mapping <= 3; ++mapping) {
-                if (mapping == 1 && ni < 64) continue;
-                if (mapping == 3 && (ni < 16 || ni > 1024)) continue;
-                const int rows_opts[3] = {1, 2, 4};
-                for (int rows : rows_opts) {
-                    if (mapping == 1 && rows == 4) continue;
-                    if (mapping == 2 && rows > ni) continue;
-                    if (mapping == 3 && rows != 1) continue;
-                    // the automatic split count of this mapping, halved and doubled
-                    const int64_t base = default_splits(ctx, n, ni, mapping, rows);
-                    for (int64_t sc : {base / 2, base, base * 2}) {
-                        const int64_t maxs = max_splits(ctx, n, ni, mapping, rows);
-                        const int s = (int)std::max<int64_t>(1, std::min<int64_t>(sc, maxs));
-                        nb::Plan p{mapping, rows, s, 0, split_step(mapping, s, n)};
-                        bool dup = false;
-                        for (auto &q : cands)
-                            dup |= q.mapping == p.mapping && q.rows_per_lane == p.rows_per_lane &&
-                                   q.splits == p.splits;
-                        if (!dup) cands.push_back(p);
-                    }
-                }
-            }
-            // a mixed request on a small block may be served faster by the
-            // FP64 kernels (latency-bound, and no refinement)
-            if (prec == 1 && ni <= 256) {
-                const size_t k = cands.size();
-                for (size_t q = 0; q < k; ++q) {
-                    nb::Plan p = cands[q];
-                    p.f64 = 1;
-                    cands.push_back(p);
-                }
-            }
+            const std::vector<nb::Plan> cands = tune_candidates(ctx, n, ni, prec == 1);
             float best_ms = 1e30f;
             nb::Plan best{};
             for (const nb::Plan &p : cands) {
                 ctx->forced = p;
-                ctx->has_forced = true;
+                ctx->has_forced = p.mapping != 0;   // else the automatic plan
                 float ms_min = 1e30f;
                 for (int rep = 0; rep < 4 && rc == NB_OK; ++rep) {
                     (void)hipEventRecord(t0, ctx->stream);
@@ -201,8 +221,16 @@ extern "C" int nb_autotune(nb_ctx *ctx, int64_t n, const char *cache_path, int f
                     (void)hipEventElapsedTime(&ms, t0, t1);
                     if (rep > 0) ms_min = std::min(ms_min, ms);
                 }
+                // a plan that finds no room is no candidate (the automatic one,
+                // which takes fewer splits then, is the first)
+                if (rc == NB_ERR_OOM && p.mapping != 0) {
+                    rc = NB_OK;
+                    continue;
+                }
                 if (rc != NB_OK) break;
-                if (ms_min < best_ms) {
+                // a fixed split count serves sizes that the automatic plan is made
+                // for one by one: it has to be clearly the faster one
+                if (ms_min < (best.mapping == 0 ? 0.98f : 1.0f) * best_ms) {
                     best_ms = ms_min;
                     best = p;
                 }
@@ -226,7 +254,10 @@ extern "C" int nb_autotune(nb_ctx *ctx, int64_t n, const char *cache_path, int f
     (void)hipEventDestroy(t1);
     (void)hipStreamSynchronize(ctx->stream);
     (void)hipFree(buf);
-    if (rc != NB_OK) return rc;
+    if (rc != NB_OK) {
+        ctx->tuned = tuned_before;
+        return rc;
+    }
 
     if (cache_path) {
         FILE *f = std::fopen(cache_path, "w");

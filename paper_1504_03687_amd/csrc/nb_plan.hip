@@ -208,12 +208,12 @@ constexpr int32_t kWaveMaxRows = 40;
 constexpr int32_t kMixedAsF64MaxRows = kWaveMaxRows;
 
 // Automatic plan for a block of n_i rows against n bodies: the autotuned
-// entry for the size buckets if there is one, else the mapping for its size
-// (above).
+// entry for the size buckets if there is one (mapping 0: the tuner found none
+// faster), else the mapping for its size (above).
 Plan auto_plan(const nb_ctx *ctx, int64_t n, int32_t n_i, bool mixed)
 {
     auto it = ctx->tuned.find(std::make_tuple((int)mixed, bucket_log2(n), bucket_log2(n_i)));
-    if (it != ctx->tuned.end()) {
+    if (it != ctx->tuned.end() && it->second.mapping != 0) {
         Plan p = it->second;
         p.step = split_step(p.mapping, p.splits, n);
         return p;

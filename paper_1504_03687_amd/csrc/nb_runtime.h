@@ -121,6 +121,7 @@ int64_t default_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, int mapping, i
 bool pack_pays(int mapping, int rows_per_lane, int64_t n, int32_t n_i);
 int split_step(int mapping, int64_t splits, int64_t n);
 void finish_plan(nb::Plan &p, int64_t n, int32_t n_i, int64_t *split_len);
+std::vector<nb::Plan> tune_candidates(const nb_ctx *ctx, int64_t n, int32_t ni, bool mixed);
 int least_splits(const nb_ctx *ctx, int64_t n, int32_t n_i, const nb::Plan &p);
 ForceScratch fit_scratch(const nb_ctx *ctx, int64_t n, int32_t n_i, const nb::Plan &p,
                          bool refine, int least, size_t budget);

@@ -48,6 +48,13 @@ int main()
             std::printf("%d %d %lld %lld %d %lld\n", sh.row_block, sh.tile, (long long)sh.body_len,
                         (long long)sh.panel_blocks, sh.index_in_gm,
                         (long long)nb::adjoint_scratch_bytes(n, (int32_t)n_i, sh));
+        } else if (!std::strcmp(what, "tune")) {   // n n_i mixed: candidates, first mapping
+            long long n, n_i, mixed;
+            if (std::scanf("%lld %lld %lld", &n, &n_i, &mixed) != 3) return 1;
+            const auto c = nbrt::tune_candidates(&ctx, n, (int32_t)n_i, mixed != 0);
+            int automatic = 0;
+            for (const nb::Plan &p : c) automatic += p.mapping == 0;
+            std::printf("%d %d %d\n", (int)c.size(), c[0].mapping, automatic);
         } else {
             return 1;
         }

@@ -138,3 +138,11 @@ def test_adjoint_panels_fill_the_chip(rules):
         room = 8 * (7 * n + 12 * n_i) + 768
         _, _, _, panel, _, total = rules(f"adjoint {n} {n_i} {room}")[0]
         assert panel == 1 and total <= room
+
+
+def test_tuner_times_the_automatic_plan(rules):
+    """The automatic plan is the first candidate, for every size and precision."""
+    for n, n_i in ((64, 1), (1024, 64), (16384, 4096), (131072, 4096), (1 << 20, 65536)):
+        for mixed in (0, 1):
+            count, first, automatic = rules(f"tune {n} {n_i} {mixed}")[0]
+            assert count > 1 and first == 0 and automatic == 1
