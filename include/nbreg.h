@@ -96,20 +96,27 @@ const char *nb_error_string(int code);
 int nb_version(void);
 
 /* Plan override used by tests and the autotuner: 0 in a field means "choose
- * automatically".  mapping: 1 = one row per lane with j-tiles in LDS
- * (256-lane work-groups; with one row per lane, blocks of more than 2^27
- * pairs read a packed copy of the bodies by scalar loads instead, to the same
- * bits), 2 = 1, 2 or 4 rows per wavefront with j spread over lanes (the
- * smallest blocks), 3 = one row per lane in one-wave work-groups with 64-body
- * LDS tiles (automatic for smaller blocks above 40 rows whose rows fill 64-row
- * tiles more than 1.2 times better than 256-row ones, so at most 832 rows).  rows_per_lane: 1, 2 or 4 (mapping 1; rows per wave for mapping 2;
- * ignored by mapping 3).  splits: number of contiguous j ranges whose partial
- * sums are combined in FP64 (>= 1).  The override holds until changed; pass
- * all zeros to go back to automatic plans. */
+ * automatically".  mapping: 1 = one row per lane with j-tiles in LDS (256-lane
+ * work-groups); with one row per lane, blocks of 1024 rows or more and above
+ * 2^26 pairs, or of 512 rows or more and above 2^27, read a packed copy of the
+ * bodies by scalar loads instead, where there is scratch for it: lists and FP64
+ * sums, and mixed sums below 2^18 bodies, to the same bits; at 2^18 and above the
+ * packed pass adds the FP64 terms of a mixed row's near pairs in another order.
+ * 2 = 1, 2 or 4 rows per wavefront with j spread over lanes (the smallest
+ * blocks).  3 = one row per lane in one-wave work-groups with 64-body LDS tiles
+ * (automatic for blocks above 40 rows that are not packed and whose rows fill
+ * 64-row tiles more than 1.2 times better than 256-row ones, so at most 832 rows).
+ * rows_per_lane: 1, 2 or 4 (mapping 1; rows per wave for mapping 2; ignored by
+ * mapping 3).  splits: number of contiguous j ranges whose partial sums are
+ * combined in FP64 (>= 1).  The override holds until changed; pass all zeros to
+ * go back to automatic plans. */
 int nb_ctx_set_plan(nb_ctx *ctx, int mapping, int rows_per_lane, int splits);
 /* Describes the plan of the last nb_regular_force call into buf (text). */
 int nb_ctx_last_plan(nb_ctx *ctx, char *buf, int len);
-/* Upper bound on scratch bytes the context may hold (0 = no bound). */
+/* Upper bound on scratch bytes the context may hold (0 = no bound).  Calls whose
+ * automatic plan has no room, under the bound or on the device, run with fewer
+ * splits, smaller panels or without packed bodies before they return
+ * NB_ERR_OOM; an explicit split count (nb_ctx_set_plan) is kept. */
 int nb_ctx_set_scratch_limit(nb_ctx *ctx, int64_t bytes);
 
 /* Kernel timing: when enabled, every launch (or launch sequence) of the
@@ -253,14 +260,16 @@ int nb_regular_force_batched(nb_ctx *ctx, int32_t n_clusters, const int64_t *j_o
 /* Batched kernel shape override (tests and the batched tuner): the LDS tile
  * length (j bodies staged per tile), the work-group width in lanes, the rows
  * each lane holds, and the work cap (the ensemble's pair work is cut into
- * items of about 1/(items_per_cu x CUs) of the total, by j-splits of whole
- * 256-body units).  Built shapes (tile, lanes, rows_per_lane): (256, 256, 1)
- * (the default), (256, 256, 2), (128, 128, 1), (64, 64, 1), (512, 512, 1),
- * (256, 512, 1); others give NB_ERR_UNSUPPORTED.  items_per_cu in [1, 4096]
- * (0 = 64).  All zero = automatic (tuned shape if nb_autotune_batched has
- * tuned this ensemble, else the default).  Results do not depend on the
- * shape: a row's sums follow the j order of its cluster's splits, which
- * depend only on the split count. */
+ * items of about 1/(items_per_cu x CUs) of the total, by j-splits).  Built shapes
+ * (tile, lanes, rows_per_lane): (256, 256, 1) (the default; ensembles of 256
+ * bodies a cluster or more run it over packed bodies), (256, 256, 2), (128, 128,
+ * 1), (64, 64, 1), (512, 512, 1), (256, 512, 1); others give NB_ERR_UNSUPPORTED.
+ * items_per_cu in [1, 4096] (0 = 64).  All zero = automatic (tuned shape if
+ * nb_autotune_batched has tuned this ensemble, else the default).  Lists do not
+ * depend on the shape, nor do sums at equal splits (a count set by
+ * nb_ctx_set_plan), but for mixed clusters of 2^18 bodies or more, whose near
+ * pairs the packed pass adds in another order; automatic split counts follow the
+ * shape's rows per item. */
 int nb_ctx_set_batched_shape(nb_ctx *ctx, int tile, int lanes, int rows_per_lane,
                              int items_per_cu);
 

@@ -3,15 +3,17 @@
 // The paper integrates one cluster at a time; running many uneven clusters
 // (an ensemble of star-cluster models) through one launch is this library's
 // own extension of the regular-force step of section 3.2.1.  Each cluster's
-// rows are cut into row tiles of kBlock rows (one work-group) and, for large
-// clusters, its bodies into j-splits; every (cluster, row tile, split) is one
-// work item.  Items are sorted longest-first on the host; a persistent grid
-// of (CUs x resident work-groups) pulls them from an atomic counter, so short
-// and long clusters share the chip without per-cluster launches.  Clusters
-// with one split write their outputs directly; the others go through split
-// slots and the same merge as the single-block launch.  The launch sequence
-// (counter reset, overflow reset, persistent kernel, merge) is captured once
-// per shape into a HIP graph and replayed.
+// rows are cut into row tiles (kWave rows for the packed kernel, whose waves
+// each take items of their own, a work-group's rows for the LDS kernels) and its
+// bodies into j-splits as the ensemble's size asks for; every (cluster, row
+// tile, split) is one work item.  Items are sorted longest-first on the host; a
+// persistent grid of as many work-groups as are resident starts on the first
+// ones and takes the others from an atomic counter, so short and long clusters
+// share the chip without per-cluster launches.  Clusters with one split write
+// their outputs directly; the others go through split slots and the same merge
+// as the single-block launch.  The launch sequence (pack or clears, persistent
+// kernel, merge, refinement) is captured once per shape into a HIP graph and
+// replayed.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>

@@ -8,7 +8,9 @@
 //    one thread per entry, with the second and third force derivatives from
 //    the cubic Hermite interpolant (used by step-size criteria);
 //  * the O(N^2) potential (section 3.2.1 and the energy check / scaling of
-//    section 3.3.2), FP64, one body per lane with j-tiles in LDS, and a
+//    section 3.3.2), FP64, every pair of bodies evaluated once for both (pairs
+//    of blocks, one block's bodies in registers and the other's in LDS), or,
+//    without scratch for that, one body per lane with j-tiles in LDS; and a
 //    fixed-order reduction of the total potential energy.
 #include "nbreg.h"
 #include "nb_rows.h"
