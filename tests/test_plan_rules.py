@@ -57,6 +57,8 @@ def test_short_splits_of_long_ranges(rules):
             mapping, rows, splits, got = rules(f"plan {n} {n_i} {mixed}")[0]
             assert (mapping, rows, got) == (3, 1, length)
             assert splits == -(-n // length)
+    # lengths between are multiples of 64
+    assert rules("plan 262144 300 1")[0] == [3, 1, 1366, 192]
 
 
 def test_even_splits_of_packed_blocks(rules):
