@@ -656,7 +656,8 @@ __device__ __forceinline__ int32_t (*near_queue())[kBlock]
 // ms mixed and 79.1 ms FP64 through LDS and take 51.4 and 74.2 ms here (1.34
 // and 0.93e12 pairs/s).  What bounds it now is VALU issue: the loop's
 // instructions, timed one by one at four waves per SIMD, add up to 53 ns
-// (mixed) and 67 ns (FP64) per 64 pairs and SIMD; it takes 49 and 70.
+// (mixed) and 67 ns (FP64) per 64 pairs and SIMD; it takes 47 to 49 and 66 to 71
+// (FP32 instructions partly pair up, so the sum is no floor).
 // Order and fold points are those of rows_pass, and so are the results but for
 // the order of a mixed row's near terms (queue: their queues, mixed pass only).
 // Records past j1 up
